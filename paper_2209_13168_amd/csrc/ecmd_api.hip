@@ -527,7 +527,7 @@ static int run_search(ecmd_ctx* c, const ecmd_sensor* sensor, const Inputs& in, 
     sp.gamma_key = search->gamma > 0.0 ? (long long)floor(search->gamma * (double)M * (double)M) : -1;
     sp.M = M;
     sp.cert = (search->flags & ECMD_SEARCH_EXACT_BOUNDS) ? 0 : 1;
-    sp.pad = 0;
+    sp.max_steps = kMaxSteps;
     const int T = g.T;
     set_groups(c, B, sp, T);
     HIPCHK(c, c->state.ensure(sizeof(WinState) * B));
@@ -550,26 +550,24 @@ static int run_search(ecmd_ctx* c, const ecmd_sensor* sensor, const Inputs& in, 
     int nb = 0;
     HIPCHK(c, eval_setup(c, lds, nt, &nb));
     int active = B;
-    auto run_step = [&](bool timed) -> hipError_t {
-        // one step: evaluate the step's hypotheses (queue set 0), frontier
-        // phase 0 (queues the exact bounds of failed certificates in set 1),
-        // evaluate those, frontier phase 1 (queues the next step in set 0)
-        for (int parity = 0; parity < 2; ++parity) {
-            hipEvent_t a = nullptr, b = nullptr;
-            if (timed) tm.pair(0, a, b);
-            hipError_t e = launch_eval(c->stream, g, nb, nt, lds, c->ev.as<float4>(), c->seg_off.as<long long>(),
-                                       c->seg_own.as<int>(), c->wp.as<WinParam>(), c->hyps.as<Hyp>(), c->act.as<int>(),
-                                       c->items.as<Item>(), qcap, &q[parity * kXcd], &q[(1 - parity) * kXcd],
-                                       c->part.as<Part>(), sp.HS, nullptr, a, b);
-            if (e != hipSuccess) return e;
-            if (timed) tm.pair(1, a, b);
-            e = launch_frontier(c->stream, parity, sp, c->wp.as<WinParam>(), B, T, c->seg_off.as<long long>(),
-                                c->state.as<WinState>(), c->front.as<Node>(), c->sel.as<Sel>(), c->hyps.as<Hyp>(),
-                                c->act.as<int>(), c->part.as<Part>(), c->items.as<Item>(), qcap,
-                                &q[(1 - parity) * kXcd], c->n_active.as<int>(), a, b);
-            if (e != hipSuccess) return e;
-        }
-        return hipSuccess;
+    // A round evaluates the queued hypotheses and runs the frontier.  It is a
+    // step of every window but those with failed certificates, whose step
+    // takes the next round too (their exact bounds).  Two queue sets
+    // alternate: round r reads set r mod 2 and queues into the other.
+    auto run_round = [&](int r, bool timed) -> hipError_t {
+        const int parity = r & 1;
+        hipEvent_t a = nullptr, b = nullptr;
+        if (timed) tm.pair(0, a, b);
+        hipError_t e = launch_eval(c->stream, g, nb, nt, lds, c->ev.as<float4>(), c->seg_off.as<long long>(),
+                                   c->seg_own.as<int>(), c->wp.as<WinParam>(), c->hyps.as<Hyp>(), c->act.as<int>(),
+                                   c->items.as<Item>(), qcap, &q[parity * kXcd], &q[(1 - parity) * kXcd],
+                                   c->part.as<Part>(), sp.HS, nullptr, a, b);
+        if (e != hipSuccess) return e;
+        if (timed) tm.pair(1, a, b);
+        return launch_frontier(c->stream, sp, c->wp.as<WinParam>(), B, T, c->seg_off.as<long long>(),
+                               c->state.as<WinState>(), c->front.as<Node>(), c->sel.as<Sel>(), c->hyps.as<Hyp>(),
+                               c->act.as<int>(), c->part.as<Part>(), c->items.as<Item>(), qcap,
+                               &q[(1 - parity) * kXcd], c->n_active.as<int>(), a, b);
     };
     const bool graph = c->tune.graph && !c->profiling;
     if (graph) {
@@ -591,7 +589,8 @@ static int run_search(ecmd_ctx* c, const ecmd_sensor* sensor, const Inputs& in, 
             c->gexec = nullptr;
             hipGraph_t gr = nullptr;
             HIPCHK(c, hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
-            hipError_t e1 = run_step(false);
+            hipError_t e1 = run_round(0, false);
+            if (e1 == hipSuccess) e1 = run_round(1, false);
             hipError_t e2 = hipStreamEndCapture(c->stream, &gr);
             HIPCHK(c, e1);
             HIPCHK(c, e2);
@@ -601,7 +600,7 @@ static int run_search(ecmd_ctx* c, const ecmd_sensor* sensor, const Inputs& in, 
             c->gkey = key;
         }
     }
-    // Blocks of four steps.  After each block the host copies the count of
+    // Blocks of four rounds.  After each block the host copies the count of
     // finished windows (and the event records) to pinned memory, but waits
     // for block b's copy only once block b + 1 is enqueued, so the device
     // never idles on the host; the block after the last is empty work.
@@ -612,9 +611,9 @@ static int run_search(ecmd_ctx* c, const ecmd_sensor* sensor, const Inputs& in, 
     auto enqueue_block = [&](int b) -> hipError_t {
         hipError_t e;
         for (int k = 0; k < 4; ++k) {
-            if (graph) {
-                if ((e = hipGraphLaunch(c->gexec, c->stream)) != hipSuccess) return e;
-            } else if ((e = run_step(true)) != hipSuccess) {
+            if (graph) {  // two rounds a launch
+                if (k % 2 == 0 && (e = hipGraphLaunch(c->gexec, c->stream)) != hipSuccess) return e;
+            } else if ((e = run_round(k, true)) != hipSuccess) {
                 return e;
             }
         }
@@ -644,7 +643,7 @@ static int run_search(ecmd_ctx* c, const ecmd_sensor* sensor, const Inputs& in, 
             tm.cut();
             ++rebins;
         }
-        const bool more = blocks * 4 < kMaxSteps;
+        const bool more = blocks * 4 < 2 * kMaxSteps;  // a step takes two rounds at most
         if (more) HIPCHK(c, enqueue_block(blocks++));
         const int done = more ? blocks - 2 : blocks - 1;  // the block whose copy is awaited
         HIPCHK(c, hipEventSynchronize(pev[done & 1]));
@@ -872,7 +871,7 @@ static int plan_shape(ecmd_ctx* c, const ecmd_sensor* sensor, const ecmd_search*
     sp.gamma_key = search->gamma > 0.0 ? (long long)floor(search->gamma * (double)M * (double)M) : -1;
     sp.M = M;
     sp.cert = (search->flags & ECMD_SEARCH_EXACT_BOUNDS) ? 0 : 1;
-    sp.pad = 0;
+    sp.max_steps = L2.max_steps;
     sp.G = 1;
     sp.B = 1;
     sp.gslots = 0;
@@ -929,18 +928,18 @@ static int plan_enqueue(ecmd_ctx* c, const PlanShape& sh, void* const* b, const 
     HIPCHK(c, plan_prep(sh, b, s, x, y, t_rel, pol, off, B));
     HIPCHK(c, launch_init(s, sp, wp, d_seeds, B, st, sel, hyps, act, items, sh.qcap, &q[0], T, seg_off,
                           InitCheck{(const int*)b[PB_WSTAT], (const int*)b[PB_WERR], (long long)sh.lim.max_records}));
-    for (int step = 0; step < sh.lim.max_steps; step += 4) {
-        for (int k = 0; k < 8; ++k) {  // four steps of two phases
-            const int parity = k & 1;
-            HIPCHK(c, launch_eval(s, g, sh.nb, sh.nt, sh.lds, (const float4*)b[PB_EV], seg_off,
-                                  (const int*)b[PB_SEG_OWN], wp, hyps, act, items, sh.qcap, &q[parity * kXcd],
-                                  &q[(1 - parity) * kXcd], part, sp.HS, nullptr));
-            HIPCHK(c, launch_frontier(s, parity, sp, wp, B, T, seg_off, st, (Node*)b[PB_FRONT], sel, hyps, act, part,
-                                      items, sh.qcap, &q[(1 - parity) * kXcd], (int*)b[PB_NACTIVE]));
-        }
+    // rounds as in the synchronous call; a step takes two at most
+    const int rounds = 2 * sh.lim.max_steps;
+    for (int r = 0; r < rounds; ++r) {
+        const int parity = r & 1;
+        HIPCHK(c, launch_eval(s, g, sh.nb, sh.nt, sh.lds, (const float4*)b[PB_EV], seg_off, (const int*)b[PB_SEG_OWN],
+                              wp, hyps, act, items, sh.qcap, &q[parity * kXcd], &q[(1 - parity) * kXcd], part, sp.HS,
+                              nullptr));
+        HIPCHK(c, launch_frontier(s, sp, wp, B, T, seg_off, st, (Node*)b[PB_FRONT], sel, hyps, act, part, items,
+                                  sh.qcap, &q[(1 - parity) * kXcd], (int*)b[PB_NACTIVE]));
         // bin again with the live ranges, at the synchronous call's polling
         // points (unconditionally: the host does not see the copy count)
-        if (step / 4 < kMaxRebins && step + 4 < sh.lim.max_steps) {
+        if (r % 4 == 3 && r / 4 < kMaxRebins && r + 1 < rounds) {
             HIPCHK(c, launch_live_range(s, sp, st, (const Node*)b[PB_FRONT], sel, wp, B));
             HIPCHK(c, plan_prep(sh, b, s, x, y, t_rel, pol, off, B));
         }

@@ -108,7 +108,7 @@ struct Search {
     long long gamma_key;  // stop when best K_bar - K_inc <= gamma_key (-1: gamma = 0)
     long long M;          // pixels
     int cert;             // endpoint certificates allowed (ECMD_SEARCH_EXACT_BOUNDS not set)
-    int pad;
+    int max_steps;        // a window that has taken this many steps stays as it is
 };
 
 struct WinState {
@@ -127,7 +127,7 @@ struct WinState {
     long long nodes_expanded, nodes_pruned, point_evals, bound_evals;
     long long event_hyp, pixel_updates;
     long long cert_evals;  // certificates that kept their node
-    int n_repair;          // children whose certificate failed, bounded again this step
+    int n_repair;          // children whose certificate failed, bounded in the evaluation launch under way
     int overflow;          // the frontier outgrew its capacity this step
     int n_front0;          // queued nodes before this step's children
     int pad2;
@@ -190,13 +190,13 @@ struct InitCheck {
 hipError_t launch_init(hipStream_t s, const Search& sp, const WinParam* wp, const float* seeds, int B,
                        WinState* st, Sel* sel, Hyp* hyps, int* act, Item* items, int qcap, Queue* q, int T,
                        const long long* seg_off, InitCheck chk);
-// One step of Algorithm 1 in two launches around an evaluation launch:
-// phase 0 absorbs the step's evaluations (incumbent, children) and queues
-// the exact bound of every child whose endpoint certificate failed (in
-// q_fill, usually nothing); phase 1 absorbs those bounds, prunes, stops or
-// selects the next nodes and queues their hypotheses in q_fill.
+// One launch of Algorithm 1's frontier, after an evaluation launch: every
+// window absorbs its evaluations, prunes, stops or selects the next nodes and
+// queues their hypotheses in q_fill.  A window with children whose endpoint
+// certificate failed queues their exact bounds instead and ends its step in
+// the next launch.
 // t0, t1 (nullable): events that take the kernel's own start and end times
-hipError_t launch_frontier(hipStream_t s, int phase, const Search& sp, const WinParam* wp, int B, int T,
+hipError_t launch_frontier(hipStream_t s, const Search& sp, const WinParam* wp, int B, int T,
                            const long long* seg_off, WinState* st, Node* front, Sel* sel, Hyp* hyps, int* act,
                            const Part* part, Item* items, int qcap, Queue* q_fill, int* n_active,
                            hipEvent_t t0 = nullptr, hipEvent_t t1 = nullptr);

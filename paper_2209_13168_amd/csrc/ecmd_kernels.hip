@@ -618,6 +618,11 @@ __global__ __launch_bounds__(NT) void k_eval(
         q_reset[tid].n_items = 0;
         q_reset[tid].next = 0;
     }
+    {  // nothing queued (the rounds after the last step): leave before the clear
+        int any = 0;
+        for (int r = 0; r < kXcd; ++r) any |= q[r].n_items;
+        if (any == 0) return;
+    }
     {  // every counter of the tile region starts at zero and is zeroed again
        // by the pass that sums each hypothesis's squares
         uint4* const t4 = reinterpret_cast<uint4*>(tile);
@@ -1200,152 +1205,23 @@ __device__ __forceinline__ void queue_append(Node* fr, int& n, int CAP, bool kee
     n = min(n + tot, CAP);
 }
 
-// Phase 0 of one step of Algorithm 1 for window blockIdx.x: absorb the
+// One frontier launch of Algorithm 1 for window blockIdx.x: absorb the
 // evaluated hypotheses, update the incumbent and queue the improvable
-// children.  A child evaluated by its endpoint certificate L <= K_bar is
+// children (phase 0), then drop queued nodes that can no longer improve,
+// decide whether to stop, select the next nodes and emit their hypotheses
+// (phase 1).  A child evaluated by its endpoint certificate L <= K_bar is
 // queued with key L (marked kNodeCert) when L already shows it improvable;
 // otherwise it is queued in its place as a placeholder (kNodeRepair) and its
-// exact bound goes to the evaluation launch between the phases, so the
-// queue keeps the exact search's order.  Every order below is the array
-// order (scans, no atomic slot races), so the search is reproducible.
-__global__ __launch_bounds__(NTF) void k_frontier_a(
-    Search sp, const WinParam* __restrict__ wp, int B, int T, const long long* __restrict__ seg_off,
-    WinState* __restrict__ st, Node* __restrict__ front, Sel* __restrict__ sel, Hyp* __restrict__ hyps,
-    int* __restrict__ act, const Part* __restrict__ part, Item* __restrict__ items, int qcap,
-    Queue* __restrict__ qf, int* __restrict__ n_active) {
-    const int w = blockIdx.x, tid = threadIdx.x;
-    __shared__ WinState s;
-    __shared__ long long s_hi[NTF];
-    __shared__ unsigned long long s_lo[NTF];
-    __shared__ unsigned s_j[NTF];
-    __shared__ int s_wave[NWF], s_tiles[kMaxTiles], s_nt;
-    __shared__ unsigned long long s_pix;
-    __shared__ long long s_nbound, s_pruned, s_ncert;
-    if (tid == 0) s = st[w];
-    __syncthreads();
-    if (!s.active) return;
-    const int F = sp.F, HS = sp.HS, CAP = sp.CAP;
-    const long long M = sp.M;
-    const WinParam p = wp[w];
-    Node* fr = front + (long long)w * CAP;
-    Sel* sl = sel + (long long)w * F;
-    Hyp* hy = hyps + (long long)w * HS;
-    int* ac = act + (long long)w * HS;
-    const Part* pw = part + (long long)w * HS * T;
-    nonempty_tiles(w, T, seg_off, s_tiles, &s_nt, s_wave);
-    const int nt = s_nt;
-    const int n_sel = s.n_sel;
-
-    // (1) centre points: lexicographic max of (K, -j) with the incumbent
-    i128 bK = mk128(s.Kinc_hi, s.Kinc_lo);
-    unsigned bJ = s.j_inc;
-    for (int i = tid; i < n_sel; i += NTF) {
-        unsigned long long S, U;
-        long long N;
-        slot_sums(pw, i, T, s_tiles, nt, S, N, U);
-        const i128 K = (i128)M * (i128)S - (i128)N * (i128)N;
-        const unsigned jc = sl[i].jc;
-        if (K > bK || (K == bK && jc < bJ)) { bK = K; bJ = jc; }
-    }
-    block_argmax(bK, bJ, s_hi, s_lo, s_j);
-    const i128 Kinc = bK;
-    const unsigned jinc = bJ;
-    if (tid == 0) {
-        sp128(Kinc, s.Kinc_hi, s.Kinc_lo);
-        s.j_inc = jinc;
-        s.point_evals += n_sel;
-        s.event_hyp += (long long)n_sel * p.n_events;
-        s_pix = 0;
-        s_nbound = 0;
-        s_pruned = 0;
-        s_ncert = 0;
-    }
-    __syncthreads();
-
-    // (2) children of the expanded nodes, appended in slot order
-    int n = s.n_front;
-    const int n0 = n;
-    int overflow = 0, nrep = 0;
-    for (int c0 = 0; c0 < 2 * n_sel; c0 += NTF) {
-        const int c = c0 + tid;
-        bool keep = false, rep = false;
-        Node nd;
-        if (c < 2 * n_sel && sl[c >> 1].kids) {
-            unsigned long long S, U;
-            long long N;
-            slot_sums(pw, F + c, T, s_tiles, nt, S, N, U);
-            const Sel x = sl[c >> 1];
-            nd.ja = (c & 1) ? x.jc : x.ja;
-            nd.jb = (c & 1) ? x.jb : x.jc;
-            nd.ub = x.ub;  // every grid point of the child is one of the parent's
-            if (hy[F + c].kind == HYP_CERT) {
-                // S holds U (walk pixels of the events inside at both ends),
-                // a lower bound of sum H_bar.  Two lower bounds of K_bar:
-                // M S_bar >= U^2 (Cauchy-Schwarz over the M cells), and, as
-                // the centre d_c of the expanded node (evaluated this step:
-                // S_c, N_c) is an end of the child, H_bar >= H(d_c) pixel by
-                // pixel, so with X = H_bar - H(d_c) >= 0,
-                // S_bar >= S_c + (sum X)^2 / M and sum X >= U - N_c.
-                unsigned long long Sc, Uc;
-                long long Nc;
-                slot_sums(pw, c >> 1, T, s_tiles, nt, Sc, Nc, Uc);
-                const i128 N2 = (i128)N * (i128)N;
-                const i128 L1 = (i128)S * (i128)S - N2;
-                const i128 X = (long long)S > Nc ? (i128)((long long)S - Nc) : (i128)0;
-                const i128 L2 = (i128)M * (i128)Sc + X * X - N2;
-                const i128 Lb = L1 > L2 ? L1 : L2;
-                nd.lc = child_cert(S, N);
-                keep = true;
-                if (improvable(Lb, nd.ja, Kinc, jinc)) {
-                    sp128(Lb, nd.khi, nd.klo);
-                    nd.jb |= kNodeCert;
-                    atomicAdd((unsigned long long*)&s_ncert, 1ull);
-                } else {
-                    rep = true;
-                    nd.khi = kNodeRepair;
-                    nd.klo = (unsigned long long)(F + c);
-                }
-            } else {
-                atomicAdd(&s_pix, U);
-                atomicAdd((unsigned long long*)&s_nbound, 1ull);
-                const i128 Kb = (i128)M * (i128)S - (i128)N * (i128)N;
-                sp128(Kb, nd.khi, nd.klo);
-                nd.lc = child_cert(U, N);
-                keep = improvable(Kb, nd.ja, Kinc, jinc);
-                if (!keep) atomicAdd((unsigned long long*)&s_pruned, 1ull);
-            }
-        }
-        queue_append(fr, n, CAP, keep, nd, s_wave, overflow);
-        // the children to bound exactly between the phases
-        int tot;
-        const int r = block_scan(rep ? 1 : 0, s_wave, tot);
-        if (rep) {
-            hy[F + c].kind = HYP_INTERVAL;  // same end rates
-            ac[nrep + r] = F + c;
-        }
-        nrep += tot;
-    }
-    __syncthreads();
-    if (tid == 0) {
-        s.bound_evals += s_nbound;
-        s.event_hyp += s_nbound * p.n_events;
-        s.pixel_updates += (long long)s_pix;
-        s.nodes_pruned += s_pruned;
-        s.cert_evals += s_ncert;
-        s.n_front = n;
-        s.n_front0 = n0;
-        s.overflow = overflow;
-        s.n_repair = nrep;
-        st[w] = s;
-    }
-    if (nrep) emit_items(sp, w, s_tiles, nt, nrep, items, qcap, qf);
-}
-
-// Phase 1 of the step: put the exact bounds of the children whose
-// certificate failed into their placeholders, drop queued nodes that can no
-// longer improve, decide whether to stop, select the next nodes, emit their
-// hypotheses.
-__global__ __launch_bounds__(NTF) void k_frontier_b(
+// exact bound goes to the next evaluation launch, so the queue keeps the
+// exact search's order; only then does the window's phase 1 wait for the
+// next frontier launch (WinState::n_repair > 0).  Windows are independent, so
+// each takes its own steps: a step without a failed certificate costs one
+// evaluation and one frontier launch.  A small search is a chain of launches
+// (with a launch per phase and an evaluation between them, usually empty, one
+// 10k-event window of 128x128 took 901 us, with this 763 us; 32 windows of
+// 346x260 7.60 and 7.29 ms).  Every order below is the array order (scans, no
+// atomic slot races), so the search is reproducible.
+__global__ __launch_bounds__(NTF) void k_frontier(
     Search sp, const WinParam* __restrict__ wp, int B, int T, const long long* __restrict__ seg_off,
     WinState* __restrict__ st, Node* __restrict__ front, Sel* __restrict__ sel, Hyp* __restrict__ hyps,
     int* __restrict__ act, const Part* __restrict__ part, Item* __restrict__ items, int qcap,
@@ -1359,20 +1235,134 @@ __global__ __launch_bounds__(NTF) void k_frontier_b(
     __shared__ int s_hist[130];
     __shared__ int s_bstar, s_quota, s_stop, s_take, s_anycert, s_ubmax;
     __shared__ unsigned long long s_pix;
-    __shared__ long long s_nbound, s_pruned;
+    __shared__ long long s_nbound, s_pruned, s_ncert;
     if (tid == 0) s = st[w];
     __syncthreads();
-    if (!s.active) return;
+    if (!s.active || s.steps >= sp.max_steps) return;
     const int F = sp.F, HS = sp.HS, CAP = sp.CAP;
     const long long M = sp.M;
     const WinParam p = wp[w];
     Node* fr = front + (long long)w * CAP;
     Sel* sl = sel + (long long)w * F;
+    Hyp* hy = hyps + (long long)w * HS;
+    int* ac = act + (long long)w * HS;
     const Part* pw = part + (long long)w * HS * T;
     nonempty_tiles(w, T, seg_off, s_tiles, &s_nt, s_wave);
     const int nt = s_nt;
-    const i128 Kinc = mk128(s.Kinc_hi, s.Kinc_lo);
-    const unsigned jinc = s.j_inc;
+    i128 Kinc = mk128(s.Kinc_hi, s.Kinc_lo);
+    unsigned jinc = s.j_inc;
+    const bool repaired = s.n_repair > 0;  // phase 0 of this step is done
+    if (!repaired) {
+        const int n_sel = s.n_sel;
+
+        // (1) centre points: lexicographic max of (K, -j) with the incumbent
+        i128 bK = Kinc;
+        unsigned bJ = jinc;
+        for (int i = tid; i < n_sel; i += NTF) {
+            unsigned long long S, U;
+            long long N;
+            slot_sums(pw, i, T, s_tiles, nt, S, N, U);
+            const i128 K = (i128)M * (i128)S - (i128)N * (i128)N;
+            const unsigned jc = sl[i].jc;
+            if (K > bK || (K == bK && jc < bJ)) { bK = K; bJ = jc; }
+        }
+        block_argmax(bK, bJ, s_hi, s_lo, s_j);
+        Kinc = bK;
+        jinc = bJ;
+        if (tid == 0) {
+            sp128(Kinc, s.Kinc_hi, s.Kinc_lo);
+            s.j_inc = jinc;
+            s.point_evals += n_sel;
+            s.event_hyp += (long long)n_sel * p.n_events;
+            s_pix = 0;
+            s_nbound = 0;
+            s_pruned = 0;
+            s_ncert = 0;
+        }
+        __syncthreads();
+
+        // (2) children of the expanded nodes, appended in slot order
+        int n = s.n_front;
+        const int n0 = n;
+        int overflow = 0, nrep = 0;
+        for (int c0 = 0; c0 < 2 * n_sel; c0 += NTF) {
+            const int c = c0 + tid;
+            bool keep = false, rep = false;
+            Node nd;
+            if (c < 2 * n_sel && sl[c >> 1].kids) {
+                unsigned long long S, U;
+                long long N;
+                slot_sums(pw, F + c, T, s_tiles, nt, S, N, U);
+                const Sel x = sl[c >> 1];
+                nd.ja = (c & 1) ? x.jc : x.ja;
+                nd.jb = (c & 1) ? x.jb : x.jc;
+                nd.ub = x.ub;  // every grid point of the child is one of the parent's
+                if (hy[F + c].kind == HYP_CERT) {
+                    // S holds U (walk pixels of the events inside at both ends),
+                    // a lower bound of sum H_bar.  Two lower bounds of K_bar:
+                    // M S_bar >= U^2 (Cauchy-Schwarz over the M cells), and, as
+                    // the centre d_c of the expanded node (evaluated this step:
+                    // S_c, N_c) is an end of the child, H_bar >= H(d_c) pixel by
+                    // pixel, so with X = H_bar - H(d_c) >= 0,
+                    // S_bar >= S_c + (sum X)^2 / M and sum X >= U - N_c.
+                    unsigned long long Sc, Uc;
+                    long long Nc;
+                    slot_sums(pw, c >> 1, T, s_tiles, nt, Sc, Nc, Uc);
+                    const i128 N2 = (i128)N * (i128)N;
+                    const i128 L1 = (i128)S * (i128)S - N2;
+                    const i128 X = (long long)S > Nc ? (i128)((long long)S - Nc) : (i128)0;
+                    const i128 L2 = (i128)M * (i128)Sc + X * X - N2;
+                    const i128 Lb = L1 > L2 ? L1 : L2;
+                    nd.lc = child_cert(S, N);
+                    keep = true;
+                    if (improvable(Lb, nd.ja, Kinc, jinc)) {
+                        sp128(Lb, nd.khi, nd.klo);
+                        nd.jb |= kNodeCert;
+                        atomicAdd((unsigned long long*)&s_ncert, 1ull);
+                    } else {
+                        rep = true;
+                        nd.khi = kNodeRepair;
+                        nd.klo = (unsigned long long)(F + c);
+                    }
+                } else {
+                    atomicAdd(&s_pix, U);
+                    atomicAdd((unsigned long long*)&s_nbound, 1ull);
+                    const i128 Kb = (i128)M * (i128)S - (i128)N * (i128)N;
+                    sp128(Kb, nd.khi, nd.klo);
+                    nd.lc = child_cert(U, N);
+                    keep = improvable(Kb, nd.ja, Kinc, jinc);
+                    if (!keep) atomicAdd((unsigned long long*)&s_pruned, 1ull);
+                }
+            }
+            queue_append(fr, n, CAP, keep, nd, s_wave, overflow);
+            // the children to bound exactly between the phases
+            int tot;
+            const int r = block_scan(rep ? 1 : 0, s_wave, tot);
+            if (rep) {
+                hy[F + c].kind = HYP_INTERVAL;  // same end rates
+                ac[nrep + r] = F + c;
+            }
+            nrep += tot;
+        }
+        __syncthreads();
+        if (tid == 0) {
+            s.bound_evals += s_nbound;
+            s.event_hyp += s_nbound * p.n_events;
+            s.pixel_updates += (long long)s_pix;
+            s.nodes_pruned += s_pruned;
+            s.cert_evals += s_ncert;
+            s.n_front = n;
+            s.n_front0 = n0;
+            s.overflow = overflow;
+            s.n_repair = nrep;
+            if (nrep) st[w] = s;
+        }
+        if (nrep) {
+            emit_items(sp, w, s_tiles, nt, nrep, items, qcap, qf);
+            return;
+        }
+    }
+    __syncthreads();
     if (tid == 0) {
         s_pix = 0;
         s_nbound = 0;
@@ -1388,7 +1378,7 @@ __global__ __launch_bounds__(NTF) void k_frontier_b(
     // one that cannot improve is dropped below with the other such nodes
     const int n = s.n_front;
     const int overflow = s.overflow;
-    if (s.n_repair) {
+    if (repaired) {
         for (int i = s.n_front0 + tid; i < n; i += NTF) {
             Node nd = fr[i];
             if (nd.khi != kNodeRepair) continue;
@@ -1561,8 +1551,11 @@ __global__ __launch_bounds__(NTF) void k_frontier_b(
         s.n_sel = nsel;
         s.nodes_expanded += nsel;
         s.steps += 1;
+        s.n_repair = 0;
         st[w] = s;
     }
+    __syncthreads();
+    if (s.steps >= sp.max_steps) return;  // cut short: nothing more is evaluated
     emit_hyps(sp, p, w, T, s_tiles, nt, sl, nsel, out, nkids, (float)i128_to_double(Kinc), hyps + (long long)w * HS,
               act + (long long)w * HS, items, qcap, qf, s_wave);
 }
@@ -1615,17 +1608,13 @@ hipError_t launch_live_range(hipStream_t s, const Search& sp, const WinState* st
     return hipGetLastError();
 }
 
-hipError_t launch_frontier(hipStream_t s, int phase, const Search& sp, const WinParam* wp, int B, int T,
+hipError_t launch_frontier(hipStream_t s, const Search& sp, const WinParam* wp, int B, int T,
                            const long long* seg_off, WinState* st, Node* front, Sel* sel, Hyp* hyps, int* act,
                            const Part* part, Item* items, int qcap, Queue* q_fill, int* n_active, hipEvent_t t0,
                            hipEvent_t t1) {
     if (B <= 0) return hipSuccess;
-    if (phase == 0)
-        hipExtLaunchKernelGGL(k_frontier_a, dim3(B), dim3(NTF), 0u, s, t0, t1, 0u, sp, wp, B, T, seg_off, st, front,
-                              sel, hyps, act, part, items, qcap, q_fill, n_active);
-    else
-        hipExtLaunchKernelGGL(k_frontier_b, dim3(B), dim3(NTF), 0u, s, t0, t1, 0u, sp, wp, B, T, seg_off, st, front,
-                              sel, hyps, act, part, items, qcap, q_fill, n_active);
+    hipExtLaunchKernelGGL(k_frontier, dim3(B), dim3(NTF), 0u, s, t0, t1, 0u, sp, wp, B, T, seg_off, st, front, sel,
+                          hyps, act, part, items, qcap, q_fill, n_active);
     return hipGetLastError();
 }
 
