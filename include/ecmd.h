@@ -185,8 +185,8 @@ const char *ecmd_version(void);
  * last reset. */
 typedef struct {
     int64_t calls;
-    int64_t eval_launches;     /* hypothesis evaluation kernel (eqs. (13)-(20)) */
-    double eval_ms;
+    int64_t eval_launches;     /* hypothesis evaluations (eqs. (13)-(20)), one per round */
+    double eval_ms;            /* their kernels: single hypotheses and node groups */
     int64_t frontier_launches; /* frontier step kernel (Algorithm 1) */
     double frontier_ms;
     double prep_ms;            /* window prep (event binning) */

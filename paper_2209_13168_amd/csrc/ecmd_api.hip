@@ -72,6 +72,7 @@ constexpr int kDefaultF = 96;         // nodes expanded together (measured: 64 t
 constexpr int kDefaultCap = 16384;    // queued nodes per window
 constexpr int kMaxSteps = 1 << 20;    // hard stop of the step loop
 constexpr int kMaxRebins = 2;         // re-binnings of the events per search
+constexpr int kListCap = 1024;        // moved events per wave of a node group (node_list_bytes)
 
 }  // namespace
 
@@ -86,12 +87,14 @@ struct ecmd_ctx {
     size_t eval_lds = 0;   // LDS bytes of the last evaluation set-up (0 = none yet)
     int eval_nt = 0;       // threads per evaluation workgroup of that set-up
     int eval_nb = 0;       // evaluation workgroups for that size
+    size_t nodes_lds = 0;  // LDS bytes and workgroups of the node groups' kernel on the same tiles
+    int nodes_nb = 0;      // (0: its sums do not fit beside the counters)
     // staging of host inputs
     DevBuf sx, sy, st, soff, stau, sseed, spol;
     // prep
     DevBuf wp, blk, cnt_own, cnt_guest, seg_off, seg_own, cursor, ev, err_flag;
     // search
-    DevBuf state, front, sel, hyps, act, items, queues, part, n_active;
+    DevBuf state, front, sel, hyps, act, items, queues, part, n_active, lists;
     // probes / window selection / downsample
     DevBuf pix, img, keep, counts, misc;
     HostBuf pinned;
@@ -109,7 +112,7 @@ struct ecmd_ctx {
     size_t ev_used = 0;
 };
 
-// Event pair around a launch when profiling (kind: 0 eval, 1 frontier, 2 prep).
+// Event pair around a launch when profiling (kind: 0 eval, 1 frontier, 2 prep, 3 node groups).
 struct Mark {
     hipEvent_t a, b;
     int kind;
@@ -173,6 +176,7 @@ struct Timers {
             float ms = 0.0f;
             if (hipEventElapsedTime(&ms, m.a, m.b) != hipSuccess) continue;
             if (m.kind == 0) { c->prof.eval_ms += ms; c->prof.eval_launches += 1; }
+            else if (m.kind == 3) c->prof.eval_ms += ms;  // node groups: part of the round's evaluation
             else if (m.kind == 1) { c->prof.frontier_ms += ms; c->prof.frontier_launches += 1; }
             else c->prof.prep_ms += ms;
         }
@@ -458,7 +462,8 @@ static bool choose_tiling(size_t max_lds, const ecmd_tuning& tu, int W, int H, f
 // LDS: as many as fit at once, at most 4 per CU.  The kernel's dynamic LDS
 // limit is raised to the device maximum once per context, so that every
 // context's launches fit whatever another context set.
-static hipError_t eval_setup(ecmd_ctx* c, size_t lds, int nt, int* nb) {
+static hipError_t eval_setup(ecmd_ctx* c, int ring_px, int nt, int* nb) {
+    const size_t lds = eval_lds_bytes(ring_px);
     if (c->eval_lds != lds || c->eval_nt != nt) {
         hipError_t e = eval_set_lds(c->max_lds);
         if (e != hipSuccess) return e;
@@ -467,6 +472,9 @@ static hipError_t eval_setup(ecmd_ctx* c, size_t lds, int nt, int* nb) {
         c->eval_lds = lds;
         c->eval_nt = nt;
         c->eval_nb = c->num_cu * std::min(per_cu, 8);
+        c->nodes_lds = nodes_lds_bytes(ring_px);
+        if (c->nodes_lds > c->max_lds || nodes_occupancy(&per_cu, c->nodes_lds, nt) != hipSuccess) per_cu = 0;
+        c->nodes_nb = c->num_cu * std::min(per_cu, 8);
     }
     *nb = c->eval_nb;
     return hipSuccess;
@@ -492,6 +500,26 @@ static void set_groups(ecmd_ctx* c, int B, Search& sp, int T) {
     sp.G = group_for(c, B, sp, T);
     sp.B = B;
     sp.gslots = c->tune.group > 0 ? 0 : std::max((long long)c->num_cu * 48, 1ll);
+}
+
+// Bytes of the node groups' lists for nb workgroups of nt threads.
+static size_t list_bytes(int nb, int nt, int cap) { return (size_t)nb * (nt / 64) * node_list_bytes(cap); }
+
+// Node groups of a search of B windows of T segments, on nb workgroups of nt
+// threads (0: none) with lists of mcap events per wave.  Below kMinSegments
+// segments most of the chip is idle with or without groups, and the launch
+// that they cost per round is not repaid (one 346x260 window of 100k events:
+// 1.45 ms without, 1.53 with; four: 2.38 and 2.21; one 640x480 window of 1M
+// events, 24 segments: 3.54 and 3.20).  The lists keep a third of their room
+// for windows whose events move more than the mean.
+constexpr int kMinSegments = 24;
+
+static void set_nodes(Search& sp, int B, int T, int nb, int nt, int mcap) {
+    sp.nmax = nb > 0 && mcap >= 64 && (long long)B * T >= kMinSegments ? kMaxNodes : 0;
+    sp.nwave = nt / 64;
+    sp.nlist = mcap * 3 / 8;
+    sp.npad = 0;
+    sp.nslots = 2ll * nb;
 }
 
 // Whole batched search on staged inputs; fills out[0..B).
@@ -530,6 +558,11 @@ static int run_search(ecmd_ctx* c, const ecmd_sensor* sensor, const Inputs& in, 
     sp.max_steps = kMaxSteps;
     const int T = g.T;
     set_groups(c, B, sp, T);
+    const size_t lds = eval_lds_bytes(g.ring_px);
+    int nb = 0;
+    HIPCHK(c, eval_setup(c, g.ring_px, nt, &nb));
+    set_nodes(sp, B, T, c->nodes_nb, nt, kListCap);
+    if (sp.nmax > 0) HIPCHK(c, c->lists.ensure(list_bytes(c->nodes_nb, nt, kListCap)));
     HIPCHK(c, c->state.ensure(sizeof(WinState) * B));
     HIPCHK(c, c->front.ensure(sizeof(Node) * (size_t)B * sp.CAP));
     HIPCHK(c, c->sel.ensure(sizeof(Sel) * (size_t)B * sp.F));
@@ -537,18 +570,15 @@ static int run_search(ecmd_ctx* c, const ecmd_sensor* sensor, const Inputs& in, 
     HIPCHK(c, c->act.ensure(sizeof(int) * (size_t)B * sp.HS));
     const int qcap = ((B + kXcd - 1) / kXcd) * sp.HS * T;  // windows w = r (mod kXcd) share queue r
     HIPCHK(c, c->items.ensure(sizeof(Item) * (size_t)kXcd * qcap));
-    HIPCHK(c, c->queues.ensure(sizeof(Queue) * 2 * kXcd));
+    HIPCHK(c, c->queues.ensure(sizeof(Queue) * kQueues));
     HIPCHK(c, c->part.ensure(sizeof(Part) * (size_t)B * sp.HS * T));
     HIPCHK(c, c->n_active.ensure(sizeof(int)));
-    HIPCHK(c, hipMemsetAsync(c->queues.p, 0, sizeof(Queue) * 2 * kXcd, c->stream));
+    HIPCHK(c, hipMemsetAsync(c->queues.p, 0, sizeof(Queue) * kQueues, c->stream));
     HIPCHK(c, hipMemsetAsync(c->n_active.p, 0, sizeof(int), c->stream));
     Queue* q = c->queues.as<Queue>();
     HIPCHK(c, launch_init(c->stream, sp, c->wp.as<WinParam>(), in.seeds, B, c->state.as<WinState>(),
                           c->sel.as<Sel>(), c->hyps.as<Hyp>(), c->act.as<int>(), c->items.as<Item>(), qcap, &q[0],
                           T, c->seg_off.as<long long>(), InitCheck{nullptr, nullptr, 0}));
-    const size_t lds = eval_lds_bytes(g.ring_px);
-    int nb = 0;
-    HIPCHK(c, eval_setup(c, lds, nt, &nb));
     int active = B;
     // A round evaluates the queued hypotheses and runs the frontier.  It is a
     // step of every window but those with failed certificates, whose step
@@ -563,6 +593,14 @@ static int run_search(ecmd_ctx* c, const ecmd_sensor* sensor, const Inputs& in, 
                                    c->items.as<Item>(), qcap, &q[parity * kXcd], &q[(1 - parity) * kXcd],
                                    c->part.as<Part>(), sp.HS, nullptr, a, b);
         if (e != hipSuccess) return e;
+        if (sp.nmax > 0) {
+            if (timed) tm.pair(3, a, b);
+            e = launch_nodes(c->stream, g, c->nodes_nb, nt, c->nodes_lds, c->ev.as<float4>(),
+                             c->seg_off.as<long long>(), c->seg_own.as<int>(), c->wp.as<WinParam>(),
+                             c->hyps.as<Hyp>(), c->act.as<int>(), c->items.as<Item>(), qcap, &q[(2 + parity) * kXcd],
+                             &q[(3 - parity) * kXcd], c->part.as<Part>(), sp.HS, c->lists.as<float4>(), kListCap, a, b);
+            if (e != hipSuccess) return e;
+        }
         if (timed) tm.pair(1, a, b);
         return launch_frontier(c->stream, sp, c->wp.as<WinParam>(), B, T, c->seg_off.as<long long>(),
                                c->state.as<WinState>(), c->front.as<Node>(), c->sel.as<Sel>(), c->hyps.as<Hyp>(),
@@ -578,7 +616,7 @@ static int run_search(ecmd_ctx* c, const ecmd_sensor* sensor, const Inputs& in, 
             key.insert(key.end(), b, b + n);
         };
         void* ptrs[] = {c->ev.p, c->seg_off.p, c->seg_own.p, c->hyps.p, c->act.p, c->items.p, c->queues.p, c->part.p,
-                        c->wp.p, c->state.p, c->front.p, c->sel.p, c->n_active.p, (void*)c->stream};
+                        c->wp.p, c->state.p, c->front.p, c->sel.p, c->n_active.p, c->lists.p, (void*)c->stream};
         put(ptrs, sizeof ptrs);
         put(&g, sizeof g);
         put(&sp, sizeof sp);
@@ -772,12 +810,15 @@ struct PlanShape {
     size_t lds = 0;
     int nt = 0;        // threads per evaluation workgroup
     int nb = 0;
+    size_t nodes_lds = 0;  // the node groups' kernel
+    int nodes_nb = 0;      // (0: not launched)
+    int mcap = 0;          // listed events per wave of a node group
 };
 
 // Device buffers of a plan, in this order.
 enum PlanBuf {
     PB_WP, PB_BLK, PB_CNT, PB_SEG_OFF, PB_SEG_OWN, PB_CURSOR, PB_EV, PB_WERR, PB_WSTAT, PB_STATE, PB_FRONT, PB_SEL,
-    PB_HYPS, PB_ACT, PB_ITEMS, PB_QUEUES, PB_PART, PB_NACTIVE, PB_COUNT
+    PB_HYPS, PB_ACT, PB_ITEMS, PB_QUEUES, PB_PART, PB_NACTIVE, PB_LISTS, PB_COUNT
 };
 
 // Bytes of each device buffer for the shape's limits.
@@ -800,9 +841,10 @@ static void plan_sizes(const PlanShape& sh, size_t* bytes) {
     bytes[PB_HYPS] = sizeof(Hyp) * (size_t)Bm * sp.HS;
     bytes[PB_ACT] = sizeof(int) * (size_t)Bm * sp.HS;
     bytes[PB_ITEMS] = sizeof(Item) * (size_t)kXcd * sh.qcap;
-    bytes[PB_QUEUES] = sizeof(Queue) * 2 * kXcd;
+    bytes[PB_QUEUES] = sizeof(Queue) * kQueues;
     bytes[PB_PART] = sizeof(Part) * (size_t)Bm * sp.HS * T;
     bytes[PB_NACTIVE] = sizeof(int);
+    bytes[PB_LISTS] = list_bytes(sh.nodes_nb, sh.nt, sh.mcap);
 }
 
 // Device buffers of batched searches up to fixed limits; a launch only
@@ -880,7 +922,12 @@ static int plan_shape(ecmd_ctx* c, const ecmd_sensor* sensor, const ecmd_search*
     sh.qcap = ((Bm + kXcd - 1) / kXcd) * sp.HS * g.T;
     sh.lds = eval_lds_bytes(g.ring_px);
     sh.nt = nt;
-    HIPCHK(c, eval_setup(c, sh.lds, sh.nt, &sh.nb));
+    HIPCHK(c, eval_setup(c, g.ring_px, sh.nt, &sh.nb));
+    sh.nodes_lds = c->nodes_lds;
+    sh.nodes_nb = c->nodes_nb;
+    sh.mcap = kListCap;
+    set_nodes(sp, Bm, g.T, sh.nodes_nb, nt, sh.mcap);
+    if (sp.nmax == 0) sh.mcap = 0;  // no launch forms groups
     return ECMD_OK;
 }
 
@@ -911,6 +958,7 @@ static int plan_enqueue(ecmd_ctx* c, const PlanShape& sh, void* const* b, const 
     const int T = g.T;
     Search sp = sh.sp;
     set_groups(c, B, sp, T);
+    set_nodes(sp, B, T, sh.nodes_nb, sh.nt, sh.mcap);
     const long long* off = (const long long*)offsets;
     const signed char* pol = (const signed char*)polarity;
     WinParam* wp = (WinParam*)b[PB_WP];
@@ -935,6 +983,10 @@ static int plan_enqueue(ecmd_ctx* c, const PlanShape& sh, void* const* b, const 
         HIPCHK(c, launch_eval(s, g, sh.nb, sh.nt, sh.lds, (const float4*)b[PB_EV], seg_off, (const int*)b[PB_SEG_OWN],
                               wp, hyps, act, items, sh.qcap, &q[parity * kXcd], &q[(1 - parity) * kXcd], part, sp.HS,
                               nullptr));
+        if (sp.nmax > 0)
+            HIPCHK(c, launch_nodes(s, g, sh.nodes_nb, sh.nt, sh.nodes_lds, (const float4*)b[PB_EV], seg_off,
+                                   (const int*)b[PB_SEG_OWN], wp, hyps, act, items, sh.qcap, &q[(2 + parity) * kXcd],
+                                   &q[(3 - parity) * kXcd], part, sp.HS, (float4*)b[PB_LISTS], sh.mcap));
         HIPCHK(c, launch_frontier(s, sp, wp, B, T, seg_off, st, (Node*)b[PB_FRONT], sel, hyps, act, part, items,
                                   sh.qcap, &q[(1 - parity) * kXcd], (int*)b[PB_NACTIVE]));
         // bin again with the live ranges, at the synchronous call's polling
@@ -1018,7 +1070,7 @@ void ecmd_ctx_destroy(ecmd_ctx* c) {
     (void)hipStreamSynchronize(c->stream);
     DevBuf* bufs[] = {&c->sx, &c->sy, &c->st, &c->soff, &c->stau, &c->sseed, &c->spol, &c->wp, &c->blk, &c->cnt_own,
                       &c->cnt_guest, &c->seg_off, &c->seg_own, &c->cursor, &c->ev, &c->err_flag, &c->state,
-                      &c->front, &c->sel, &c->hyps, &c->act, &c->items, &c->queues, &c->part, &c->n_active, &c->pix,
+                      &c->front, &c->sel, &c->hyps, &c->act, &c->items, &c->queues, &c->part, &c->n_active, &c->lists, &c->pix,
                       &c->img, &c->keep, &c->counts, &c->misc};
     for (DevBuf* b : bufs) b->release();
     // networks and plans outlive their context only as empty handles
@@ -1314,10 +1366,13 @@ int ecmd_estimate_divergence_batched_noalloc(ecmd_ctx* c, const ecmd_sensor* sen
     if (!base) return fail(c, ECMD_EDEVICE, "no scratch address on device %d", c->device);
     void* b[PB_COUNT];
     size_t used = 0;
-    for (int k = 0; k < PB_COUNT; ++k) {
+    for (int k = 0; k < PB_LISTS; ++k) {
         b[k] = (char*)base + used;
         used += (bytes[k] + 255) / 256 * 256;  // every buffer on a 256-byte boundary
     }
+    // the node groups' lists take what is left: shorter ones, or no groups
+    b[PB_LISTS] = (char*)base + used;
+    while (sh.mcap >= 64 && used + list_bytes(sh.nodes_nb, sh.nt, sh.mcap) > kScratchBytes) sh.mcap /= 2;
     if (used > kScratchBytes)
         return fail(c, ECMD_ENOMEM,
                     "%d windows of up to %lld events need %zu bytes of scratch, more than the %zu the "
@@ -1533,7 +1588,7 @@ static int probe_impl(ecmd_ctx* c, const ecmd_sensor* sensor, const float* x, co
     }
     const size_t lds = eval_lds_bytes(g.ring_px);
     int nb = 0;
-    HIPCHK(c, eval_setup(c, lds, nt, &nb));
+    HIPCHK(c, eval_setup(c, g.ring_px, nt, &nb));
     Queue* q = c->queues.as<Queue>();
     HIPCHK(c, launch_eval(c->stream, g, nb, nt, lds, c->ev.as<float4>(), c->seg_off.as<long long>(),
                           c->seg_own.as<int>(), c->wp.as<WinParam>(), c->hyps.as<Hyp>(), c->act.as<int>(),

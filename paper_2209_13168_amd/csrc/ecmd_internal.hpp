@@ -32,6 +32,14 @@ constexpr int kFrontThreads = 256;  // threads of a frontier workgroup
 // HYP_CERT: the endpoint certificate of an interval (owned events only, no
 // walk): partial sums S = U (walk pixels of the events inside at both ends),
 // N = N_low; K_bar >= U^2 - N_low^2.
+constexpr int kMaxF = 1024;   // nodes expanded together, at most
+constexpr int kMaxNodes = 8;  // nodes of a node group, at most
+constexpr int kStepCap = 4;      // steps of a wave's list per moved event
+// Bytes of a wave's lists (k_nodes): mcap moved events, the steps.
+__host__ __device__ constexpr size_t node_list_bytes(int mcap) {
+    return (16 + 4 * (size_t)kStepCap) * (size_t)mcap;
+}
+
 enum HypKind : int { HYP_NONE = 0, HYP_POINT = 1, HYP_INTERVAL = 2, HYP_CERT = 3 };
 
 struct Hyp {
@@ -108,6 +116,11 @@ struct Search {
     long long gamma_key;  // stop when best K_bar - K_inc <= gamma_key (-1: gamma = 0)
     long long M;          // pixels
     int cert;             // endpoint certificates allowed (ECMD_SEARCH_EXACT_BOUNDS not set)
+    int nmax;             // nodes of a node group, at most (0: no groups)
+    int nwave;            // waves of a node item
+    int nlist;            // events a wave's list should hold
+    int npad;
+    long long nslots;     // groups are cut so that a step has at least this many items
     int max_steps;        // a window that has taken this many steps stays as it is
 };
 
@@ -135,7 +148,8 @@ struct WinState {
 
 // A work item: tile t of window w for the hypotheses act[w * HS + r0 + k],
 // k < cnt (a group of consecutive active slots, evaluated one after another
-// by one workgroup so that the item's set-up is paid once per group).
+// by one workgroup so that the item's set-up is paid once per group), or for
+// the node group of the selected nodes act[w * HS + r0 + k], k < cnt.
 struct Item {
     int w;
     int t;
@@ -146,11 +160,16 @@ struct Item {
 // Work queues: one per XCD (workgroups are dispatched to the 8 XCDs in
 // round-robin order of their index), so that the items of a window are
 // evaluated on one XCD and its events stay in that XCD's L2.  Queue r owns
-// the item slots [r * qcap, (r + 1) * qcap).
+// the item slots [r * qcap, (r + 1) * qcap).  Hypothesis items fill them from
+// the start, node items (counted by a queue of their own) from the end: each
+// node of a group has at least one hypothesis, so the two never meet.
+// Queue array of a search: hypotheses of even rounds, of odd rounds, then
+// nodes of even and of odd rounds, kXcd each.
 // Events per window stay below 2^28, so every event of a (window, tile)
 // segment is reached with a 32-bit byte offset from the segment start.
 constexpr long long kMaxWindowEvents = 1ll << 28;
 constexpr int kXcd = 8;
+constexpr int kQueues = 4 * kXcd;
 
 struct Queue {
     int n_items;
@@ -192,7 +211,8 @@ hipError_t launch_init(hipStream_t s, const Search& sp, const WinParam* wp, cons
                        const long long* seg_off, InitCheck chk);
 // One launch of Algorithm 1's frontier, after an evaluation launch: every
 // window absorbs its evaluations, prunes, stops or selects the next nodes and
-// queues their hypotheses in q_fill.  A window with children whose endpoint
+// queues their hypotheses in q_fill (node groups in the queues 2 kXcd further
+// on).  A window with children whose endpoint
 // certificate failed queues their exact bounds instead and ends its step in
 // the next launch.
 // t0, t1 (nullable): events that take the kernel's own start and end times
@@ -205,6 +225,13 @@ hipError_t launch_eval(hipStream_t s, const Geometry& g, int nblocks, int nt, si
                        const float4* ev, const long long* seg_off, const int* seg_own, const WinParam* wp,
                        const Hyp* hyps, const int* act, const Item* items, int qcap, Queue* q, Queue* q_reset,
                        Part* part, int HS, unsigned* img_out, hipEvent_t t0 = nullptr, hipEvent_t t1 = nullptr);
+// Node groups; lists: node_list_bytes(mcap) per wave of the grid (mcap a multiple of 4, below 2^16).
+hipError_t launch_nodes(hipStream_t s, const Geometry& g, int nblocks, int nt, size_t lds_bytes, const float4* ev,
+                        const long long* seg_off, const int* seg_own, const WinParam* wp, const Hyp* hyps,
+                        const int* act, const Item* items, int qcap, Queue* q, Queue* q_reset, Part* part, int HS,
+                        float4* lists, int mcap, hipEvent_t t0 = nullptr, hipEvent_t t1 = nullptr);
+size_t nodes_lds_bytes(int ring_px);
+hipError_t nodes_occupancy(int* blocks_per_cu, size_t lds_bytes, int nt);
 hipError_t launch_rates(hipStream_t s, const float* d_a, const float* d_b, int m, float tau, Hyp* hyps);
 hipError_t launch_probe_pixels(hipStream_t s, const float* x, const float* y, const float* t_rel,
                                long long n, float tau, float d, int W, int H, float cx, float cy,

@@ -886,6 +886,567 @@ __global__ __launch_bounds__(NT) void k_eval(
     }
 }
 
+// ------------------------------------------------------------ node groups (a2, a3)
+//
+// Late in a search the nodes are narrow and many lie side by side.  A node
+// asks for its centre's point image and, unless it is a leaf, for the
+// upper-bound images of its two children, which meet in the centre: three
+// passes over the events, in which nearly every event adds the same single
+// increment to every image.  k_nodes evaluates a group of up to kMaxNodes
+// nodes of a window, in grid order, in one pass: an event whose pixel is the
+// same at both ends of the group's hull [ra, rb] has that pixel at every rate
+// between (the warp is monotone in the rate).  All events are binned at ra,
+// the others are listed, and the counters then go from image to image by the
+// listed events' changes alone: to node k's point image (phase 3k), to its
+// first child's (3k + 1: the walks' pixels before the centre's) and back, to
+// its second child's (3k + 2: the walks' pixels after the centre's) and back.
+// A change of a counter from c to c + 1 changes the sum of squares by 2c + 1
+// (the atomic returns c), whatever the order of the changes within a phase,
+// so each phase's sum of these changes and the sums over the last image give
+// every image's S and count of increments exactly.  N of a point image is its
+// count of increments; N_low of an interval is the point count at its far
+// end (an event inside the image there is inside at every smaller rate).
+//
+// Each wave makes the changes of its own strip of the tile's rows, so no wave
+// waits for another between phases: a wave's LDS operations complete in
+// order.  Bound by VALU issue (55% of its limit: 25 instructions an event in
+// the pass for up to 3 kMaxNodes images, where k_eval takes about 27 per event
+// and image) and by the latency of the returned counts in the phases.  Per
+// batch, without and with node groups: 32 windows of 346x260 7.29 and 5.11 ms,
+// 64 of 640x480 40.3 and 23.7 ms, 64 of 1280x720 (0.1M-5M events) 207 and
+// 170 ms; a late step of the 640x480 batch 4.3 and 0.8 ms.
+constexpr int kNodePhases = 3 * kMaxNodes;
+static_assert(kNodePhases <= 64, "one lane per phase");
+
+// LDS of k_nodes after the counters: [S and count of the last image][phase
+// sums of S][of the count][changes of N, per node][steps, per wave][s_full][work item, queue sizes].
+constexpr int kNodeLds = 16 + 12 * kNodePhases + 4 * kMaxNodes + 4 * kEvalWaves + 4 + 4 * (1 + kXcd);
+size_t nodes_lds_bytes(int ring_px) { return (size_t)eval_counter_words(ring_px) * 4 + kNodeLds; }
+
+// A step (see k_nodes): the counter before in the low 16 bits, then these.
+constexpr int kStepRate = 16, kStepX = 21, kStepY = 23;  // rate index, 2-bit signed direction
+constexpr unsigned kStepIn0 = 1u << 25, kStepIn1 = 1u << 26;  // the pixels before, after lie in the strip
+constexpr unsigned kStepNone = 31u << kStepRate;
+static_assert(3 * kMaxNodes <= 31, "rate index of a step");
+
+// The pixels of walk_tile's walk after its start, handed to `visit` (the end
+// comes last).
+template <class V>
+__device__ __forceinline__ void walk_pixels(int kx, int ky, int kxb, int kyb, const float4& ev, V&& visit) {
+    const bool px = kxb > kx, py = kyb > ky;
+    const int sx = px ? 1 : -1, sy = py ? 1 : -1;
+    if (kx != kxb && ky != kyb) {
+        const double xo = (double)ev.x - (double)px, yo = (double)ev.y - (double)py;
+        const double aax = fabs((double)ev.z), aay = fabs((double)ev.w);
+        const double thr = (aax + aay) * 0.00390625;
+        do {
+            const double ex = fabs((double)kx - xo) * aay;
+            const double ey = fabs((double)ky - yo) * aax;
+            const double e = ex - ey;
+            const bool lo = e < -thr, hi = e > thr;
+            if (!lo && !hi) {
+                visit(kx + sx, ky);
+                visit(kx, ky + sy);
+            }
+            kx += !hi ? sx : 0;
+            ky += !lo ? sy : 0;
+            visit(kx, ky);
+        } while (kx != kxb && ky != kyb);
+    }
+    while (kx != kxb || ky != kyb) {
+        kx += kx != kxb ? sx : 0;
+        ky += ky != kyb ? sy : 0;
+        visit(kx, ky);
+    }
+}
+
+__device__ __forceinline__ float lane_f(float v, int k) {
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), k));
+}
+
+template <int NT>
+__global__ __launch_bounds__(NT, NT == 1024 ? 4 : 6) void k_nodes(
+    Geometry g, const float4* __restrict__ ev, const long long* __restrict__ seg_off,
+    const int* __restrict__ seg_own, const WinParam* __restrict__ wp, const Hyp* __restrict__ hyps,
+    const int* __restrict__ act, const Item* __restrict__ items, int qcap, Queue* __restrict__ q,
+    Queue* __restrict__ q_reset, Part* __restrict__ part, int HS, float4* __restrict__ lists, int mcap) {
+    constexpr int NW = NT / 64;
+    extern __shared__ __align__(16) unsigned smem[];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    unsigned* const tile = smem;
+    unsigned long long* const s_fin = reinterpret_cast<unsigned long long*>(smem + eval_counter_words(g.ring_px));
+    unsigned long long* const s_dS = s_fin + 2;
+    int* const s_dH = reinterpret_cast<int*>(s_dS + kNodePhases);
+    int* const s_dN = s_dH + kNodePhases;
+    int* const s_cnt = s_dN + kMaxNodes;
+    int* const s_full = s_cnt + kEvalWaves;
+    int* const s_item = s_full + 1;
+    if (blockIdx.x == 0 && tid < kXcd) {
+        q_reset[tid].n_items = 0;
+        q_reset[tid].next = 0;
+    }
+    {  // nothing queued: leave before the clear
+        int any = 0;
+        for (int r = 0; r < kXcd; ++r) any |= q[r].n_items;
+        if (any == 0) return;
+    }
+    {  // counters and sums start at zero and are cleared again by each item
+        uint4* const t4 = reinterpret_cast<uint4*>(tile);
+        const int n4 = eval_counter_words(g.ring_px) >> 2;
+        for (int i = tid; i < n4; i += NT) t4[i] = make_uint4(0u, 0u, 0u, 0u);
+        unsigned* const rest = reinterpret_cast<unsigned*>(s_fin);
+        for (int i = tid; i < kNodeLds / 4 - 1 - kXcd; i += NT) rest[i] = 0u;
+    }
+    const int home = blockIdx.x % kXcd;
+    int qi = 0;
+    int* const qn = s_item + 1;
+    if (tid == 0)
+        for (int r = 0; r < kXcd; ++r) qn[r] = q[(home + r) % kXcd].n_items;
+    const int F = HS / 3;
+    for (;;) {
+        if (tid == 0) {
+            int got = -1;
+            while (qi < kXcd) {
+                const int r = (home + qi) % kXcd;
+                if (qn[qi] > 0) {
+                    const int k = atomicAdd(&q[r].next, 1);
+                    if (k < qn[qi]) {
+                        got = (r + 1) * qcap - 1 - k;  // node items fill a queue's slots from the end
+                        break;
+                    }
+                }
+                ++qi;
+            }
+            *s_item = got;
+        }
+        __syncthreads();
+        const int it = *s_item;
+        if (it < 0) break;
+        const Item item = items[it];
+        const int w = item.w, t = item.t, m = item.cnt;
+        const int ts = t % g.nsp;
+        const int tx = ts % g.ntx, ty = ts / g.ntx;
+        const int x0 = g.colcut[tx], y0 = g.rowcut[ty];
+        const int tw = g.colcut[tx + 1] - x0, th = g.rowcut[ty + 1] - y0;
+        Ring R;
+        R.xlo = x0 - 1;
+        R.xhi = x0 + tw;
+        R.ylo = y0 - 1;
+        R.yhi = y0 + th;
+        R.rw = tw + 2;
+        R.base = -(R.ylo * R.rw + R.xlo);
+        unsigned* const org = tile + R.base;
+        const float fxlo = (float)R.xlo, fxhi = (float)R.xhi, fylo = (float)R.ylo, fyhi = (float)R.yhi;
+        const long long seg = (long long)w * g.T + t;
+        // lane k holds node k: its slot, the rates of its start, centre and
+        // end (a leaf's are its centre's) and whether it has children
+        int slot = 0, kids = 0;
+        float na = INFINITY, nc = 0.0f, nb = -INFINITY;
+        if (lane < m) {
+            slot = act[w * HS + item.r0 + lane];
+            const Hyp* const hy = hyps + w * HS;
+            na = nc = nb = hy[slot].ra;
+            kids = hy[F + 2 * slot].kind != HYP_NONE;
+            if (kids) {
+                na = hy[F + 2 * slot].ra;
+                nb = hy[F + 2 * slot + 1].rb;
+            }
+        }
+        float ra = INFINITY, rb = -INFINITY;  // the hull
+        for (int k = 0; k < m; ++k) {
+            ra = fminf(ra, lane_f(na, k));
+            rb = fmaxf(rb, lane_f(nb, k));
+        }
+        // guest bins read: those whose lower cut lies below the hull's end
+        int nbin = 0;
+        {
+            const float* const gcut = wp[w].gcut;
+#pragma unroll
+            for (int k = 0; k < kGuestBins - 1; ++k) nbin += gcut[k] < rb ? 1 : 0;
+        }
+        const char* __restrict__ sev = reinterpret_cast<const char*>(ev + seg_off[seg]);
+        const auto at = [sev](unsigned k) { return *reinterpret_cast<const float4*>(sev + (k << 4)); };
+        const unsigned nseg = (unsigned)seg_own[seg * (kGuestBins + 1) + 1 + nbin];
+        // strips of sr rows, one per wave; (k + 0.5) / sr stays clear of the
+        // integers by 0.5 / sr, far more than the rounding for k < 2^15
+        const int sr = (th + NW - 1) / NW;
+        const float inv = 1.0f / (float)sr;
+        const auto strip = [&](int ky) {
+            return (int)(((float)clampi(ky - y0, 0, th - 1) + 0.5f) * inv);
+        };
+        // pixels at both ends of the hull, clamped onto the tile's border
+        const auto ends = [&](const float4& e, int& kx, int& ky, int& kxb, int& kyb) {
+            kx = cvt_flr(__builtin_amdgcn_fmed3f(fmaf(e.z, ra, e.x), fxlo, fxhi));
+            ky = cvt_flr(__builtin_amdgcn_fmed3f(fmaf(e.w, ra, e.y), fylo, fyhi));
+            kxb = cvt_flr(__builtin_amdgcn_fmed3f(fmaf(e.z, rb, e.x), fxlo, fxhi));
+            kyb = cvt_flr(__builtin_amdgcn_fmed3f(fmaf(e.w, rb, e.y), fylo, fyhi));
+        };
+        const auto pix = [&](const float4& e, float r, int& kx, int& ky) {  // the pixel in the image
+            kx = flr_clamp(fmaf(e.z, r, e.x), g.W);
+            ky = flr_clamp(fmaf(e.w, r, e.y), g.H);
+        };
+        const auto before = [](unsigned long long mask) {  // lanes of the mask before this one
+            return (int)__builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32),
+                                                  __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0u));
+        };
+        // This wave's part of the lists: the events of its share of the
+        // segment that change pixel inside the hull (mcap records), and what
+        // becomes of them for its strip (kStepCap mcap words: a strip may
+        // hold several times its share of a tile).
+        char* const wg_list = reinterpret_cast<char*>(lists) + (size_t)blockIdx.x * NW * node_list_bytes(mcap);
+        const auto moved_of = [&](int wv) { return reinterpret_cast<float4*>(wg_list + wv * node_list_bytes(mcap)); };
+        const auto steps_of = [&](int wv) { return reinterpret_cast<unsigned*>(moved_of(wv) + mcap); };
+        float4* const moved = moved_of(wave);
+        int nl = 0;
+        const auto bin = [&](const float4& e, bool valid) {
+            int kx, ky, kxb, kyb;
+            ends(e, kx, ky, kxb, kyb);
+            if (valid) lds_inc(ring_at(org, R, kx, ky));
+            const bool mv = valid && (kx != kxb || ky != kyb);
+            const unsigned long long mask = __ballot(mv);
+            const int at_ = nl + before(mask);
+            if (mv && at_ < mcap) moved[at_] = e;
+            nl += __popcll(mask);
+        };
+        constexpr int U = 4;
+        // (the whole wave runs every iteration, so nl stays uniform)
+        unsigned b = (unsigned)wave * 64;
+        for (; b + (U - 1) * NT + 63 < nseg; b += U * NT) {
+            float4 e[U];
+#pragma unroll
+            for (int k = 0; k < U; ++k) e[k] = at(b + lane + k * NT);
+#pragma unroll
+            for (int k = 0; k < U; ++k) bin(e[k], true);
+        }
+        for (; b < nseg; b += NT) bin(at(min(b + lane, nseg - 1)), b + lane < nseg);
+        nl = __builtin_amdgcn_readfirstlane(nl);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+        // Most listed events change each coordinate by one pixel at most over
+        // the hull.  Such a change is kept as a step: the counter before it,
+        // its direction, whether the pixels before and after lie in the strip,
+        // and the first of the rates a_0, c_0, b_0, a_1, .. at which it is
+        // done (3k: node k's start, 3k + 1: its centre, 3k + 2: its end).  Two changes between the same two
+        // rates are one diagonal step, and what its walk visits on the way
+        // (walk_tile's corner test) a step from a pixel to itself, which adds
+        // to the one child's image only.  A list without room, or an event
+        // that moves further, leaves every wave to find its strip's changes
+        // from the segment's events again, at every rate (s_full: the groups
+        // are cut so narrow that ordinary windows meet neither).
+        if (nl > mcap && lane == 0) *s_full = 1;
+        for (int j0 = 0; j0 < min(nl, mcap); j0 += 64) {
+            const bool ok = j0 + lane < nl;
+            const float4 e = ok ? moved[j0 + lane] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            int kx, ky, kxb, kyb;
+            ends(e, kx, ky, kxb, kyb);
+            const bool px = kxb > kx, py = kyb > ky;
+            const float ex = (float)max(kx, kxb), ey = (float)max(ky, kyb);  // the edges stepped over
+            int cx = 1, cy = 1;  // rates at which the step is not done
+            for (int k = 0; k < m; ++k) {
+                const float a = lane_f(na, k), c = lane_f(nc, k), d = lane_f(nb, k);
+                if (k) {
+                    cx += (fmaf(e.z, a, e.x) < ex) == px;
+                    cy += (fmaf(e.w, a, e.y) < ey) == py;
+                }
+                cx += (fmaf(e.z, c, e.x) < ex) == px;
+                cy += (fmaf(e.w, c, e.y) < ey) == py;
+                cx += (fmaf(e.z, d, e.x) < ex) == px;
+                cy += (fmaf(e.w, d, e.y) < ey) == py;
+            }
+            const bool sx = kx != kxb, sy = ky != kyb;
+            if (!ok) continue;
+            const auto in_tile = [&](int x, int y) {
+                return (unsigned)(x - x0) < (unsigned)tw && (unsigned)(y - y0) < (unsigned)th;
+            };
+            // the step (fx, fy) -> (gx, gy) to the strips of its two pixels
+            const auto put = [&](int fx, int fy, int gx, int gy, int rate) {
+                const int s0 = strip(fy), s1 = strip(gy);
+                const bool fin = in_tile(fx, fy), gin = in_tile(gx, gy);
+                const unsigned word = (unsigned)((fy - R.ylo) * R.rw + (fx - R.xlo)) | (unsigned)rate << kStepRate |
+                                      ((unsigned)(gx - fx) & 3u) << kStepX | ((unsigned)(gy - fy) & 3u) << kStepY;
+                for (int u = 0; u < 2; ++u) {
+                    const int s = u ? s1 : s0;
+                    const unsigned in = (fin && s == s0 ? kStepIn0 : 0u) | (gin && s == s1 ? kStepIn1 : 0u);
+                    if (in) {
+                        const int k = atomicAdd(&s_cnt[s], 1);
+                        if (k < kStepCap * mcap) steps_of(s)[k] = word | in;
+                        else *s_full = 1;
+                    }
+                    if (s0 == s1) break;
+                }
+            };
+            if (abs(kx - kxb) > 1 || abs(ky - kyb) > 1) {
+                *s_full = 1;
+                continue;
+            }
+            const bool diag = sx && sy && cx == cy;
+            if (diag && cx % 3 != 0) {
+                // the walk itself runs in the image, not on the tile's border
+                int ax, ay, bx, by;
+                pix(e, ra, ax, ay);
+                pix(e, rb, bx, by);
+                if (abs(ax - bx) > 1 || abs(ay - by) > 1) *s_full = 1;
+                const double xo = (double)e.x - (double)px, yo = (double)e.y - (double)py;
+                const double aax = fabs((double)e.z), aay = fabs((double)e.w);
+                const double thr = (aax + aay) * 0.00390625;
+                const double d = fabs((double)ax - xo) * aay - fabs((double)ay - yo) * aax;
+                // x first, y first, or both sides of the corner (pixels off
+                // the tile go nowhere)
+                if (!(d > thr) && in_tile(bx, ay)) put(bx, ay, bx, ay, cx);
+                if (!(d < -thr) && in_tile(ax, by)) put(ax, by, ax, by, cx);
+            }
+            // the step, or the first of two, to (gx, gy)
+            const bool xfirst = sx && (!sy || cx < cy), two = sx && sy && !diag;
+            const int gx = xfirst || diag ? kxb : kx, gy = xfirst ? ky : kyb;
+            put(kx, ky, gx, gy, xfirst ? cx : cy);
+            if (two) put(gx, gy, kxb, kyb, xfirst ? cy : cx);
+        }
+        __syncthreads();  // the image at ra and the lists are complete
+
+        {
+            const int sy0 = y0 + wave * sr, sh = min(sr, th - wave * sr);
+            const auto in_strip = [&](int kx, int ky) {
+                return (unsigned)(kx - x0) < (unsigned)tw && (unsigned)(ky - sy0) < (unsigned)sh;
+            };
+            const bool full = *s_full != 0;
+            const int ns = full ? 0 : s_cnt[wave];
+            const unsigned* const steps = steps_of(wave);
+            // four chunks of steps at a time, kept in registers when they are all
+            constexpr int C = 4;
+            unsigned sp[C];
+            const auto load = [&](int j0) {
+#pragma unroll
+                for (int i = 0; i < C; ++i) {
+                    const int j = j0 + i * 64 + lane;
+                    sp[i] = j < ns ? steps[j] : kStepNone;
+                }
+            };
+            load(0);
+            // f(step) of every step whose rate index lies in [lo, lo + cnt)
+            const auto each_step = [&](int lo, unsigned cnt, auto&& f) {
+                for (int j0 = 0; j0 < ns; j0 += C * 64) {
+                    if (ns > C * 64) load(j0);
+#pragma unroll
+                    for (int i = 0; i < C; ++i) {
+                        if (j0 + i * 64 >= ns) break;
+                        if ((unsigned)((int)(sp[i] >> kStepRate & 31u) - lo) < cnt) f(sp[i]);
+                    }
+                }
+            };
+            // the segment's j-th event (with s_full), and whether it moves
+            const auto moving = [&](unsigned j, float4& e) {
+                int kx, ky, kxb, kyb;
+                e = at(j);
+                ends(e, kx, ky, kxb, kyb);
+                return kx != kxb || ky != kyb;
+            };
+            const auto first = [&](unsigned v) { return tile + (v & 0xFFFFu); };
+            const auto second = [&](unsigned v) {
+                const int dx = (int)(v << (30 - kStepX)) >> 30, dy = (int)(v << (30 - kStepY)) >> 30;
+                return tile + (int)(v & 0xFFFFu) + dx + __mul24(dy, R.rw);
+            };
+            const auto account = [&](int ph, long long dS, int dH) {
+                if (dS != 0) atomicAdd(s_dS + to_vgpr(ph), (unsigned long long)dS);
+                if (dH != 0) atomicAdd(s_dH + to_vgpr(ph), dH);
+            };
+            // The extra pixels of an interval's image over the point image at
+            // c, found from the events: those of a walk between the rates c
+            // and o, less the pixel at c.  sgn = 1 adds them (phase ph of node
+            // k), -1 takes them away again, back to the point image.
+            const auto extras = [&](float c, float o, int sgn, int k, int ph) {
+                const bool fwd = o > c;
+                for (unsigned j = lane; j < nseg; j += 64) {
+                    float4 e;
+                    if (!moving(j, e)) continue;
+                    int cx, cy, ox, oy;
+                    pix(e, c, cx, cy);
+                    pix(e, o, ox, oy);
+                    if (ox == cx && oy == cy) continue;
+                    long long dS = 0;
+                    int dH = 0;
+                    const auto step = [&](int kx, int ky) {
+                        if (in_strip(kx, ky) && (kx != cx || ky != cy)) {
+                            dS += 2 * (long long)(int)atomicAdd(ring_at(org, R, kx, ky), (unsigned)sgn) + 1;
+                            dH += 1;
+                        }
+                    };
+                    if (!fwd) step(ox, oy);
+                    walk_pixels(fwd ? cx : ox, fwd ? cy : oy, fwd ? ox : cx, fwd ? oy : cy, e, step);
+                    if (sgn > 0) {
+                        account(ph, dS, dH);
+                        const int d = (int)in_strip(ox, oy) - (int)in_strip(cx, cy);
+                        if (fwd && d) atomicAdd(s_dN + to_vgpr(k), d);
+                    }
+                }
+            };
+            float c0 = ra, b0 = ra;  // centre and end of the image in the counters (at first: points at ra)
+            for (int k = 0; (full || ns > 0) && k < m; ++k) {
+                const float a = lane_f(na, k), c = lane_f(nc, k), b = lane_f(nb, k);
+#pragma unroll 1
+                for (int st = 0; st < 4; ++st) {
+                    // 0: the last second child's extra pixels go, the points
+                    // move to the next centre; 1: first child's extra pixels;
+                    // 2: they go; 3: second child's
+                    const float fc = st ? c : c0, fo = st == 0 ? b0 : st == 3 ? b : a;
+                    if (st == 0) {
+                        each_step(3 * k - 1, 1u, [&](unsigned v) {
+                            if (v & kStepIn1) atomicSub(second(v), 1u);
+                        });
+                    } else if (st == 2) {
+                        each_step(3 * k + 1, 1u, [&](unsigned v) {
+                            if (v & kStepIn0) atomicSub(first(v), 1u);
+                        });
+                    } else {
+                        each_step(st == 1 ? 3 * k + 1 : 3 * k + 2, 1u, [&](unsigned v) {
+                            if (v & (st == 1 ? kStepIn0 : kStepIn1))
+                                account(st == 1 ? 3 * k + 1 : 3 * k + 2,
+                                        2 * (long long)(int)atomicAdd(st == 1 ? first(v) : second(v), 1u) + 1, 1);
+                            const int d = (int)((v & kStepIn1) != 0) - (int)((v & kStepIn0) != 0);
+                            if (st == 3 && d) atomicAdd(s_dN + to_vgpr(k), d);
+                        });
+                    }
+                    if (full && fc != fo) extras(fc, fo, st & 1 ? 1 : -1, k, st == 1 ? 3 * k + 1 : 3 * k + 2);
+                    if (st == 0) {
+                        each_step(3 * k - 1, 3u, [&](unsigned v) {
+                            const bool in0 = v & kStepIn0, in1 = v & kStepIn1;
+                            unsigned o0 = 0, o1 = 0;
+                            if (in0) o0 = atomicSub(first(v), 1u);
+                            if (in1) o1 = atomicAdd(second(v), 1u);
+                            account(3 * k, (in1 ? 2 * (long long)(int)o1 + 1 : 0) - (in0 ? 2 * (long long)(int)o0 - 1 : 0),
+                                    (int)in1 - (int)in0);
+                        });
+                        for (unsigned j = lane; full && j < nseg; j += 64) {
+                            float4 e;
+                            if (!moving(j, e)) continue;
+                            int cx, cy, kx, ky;
+                            pix(e, c0, cx, cy);
+                            pix(e, c, kx, ky);
+                            if (cx == kx && cy == ky) continue;
+                            long long dS = 0;
+                            int dH = 0;
+                            if (in_strip(cx, cy)) {
+                                dS += 1 - 2 * (long long)(int)atomicSub(ring_at(org, R, cx, cy), 1u);
+                                dH -= 1;
+                            }
+                            if (in_strip(kx, ky)) {
+                                dS += 2 * (long long)(int)atomicAdd(ring_at(org, R, kx, ky), 1u) + 1;
+                                dH += 1;
+                            }
+                            account(3 * k, dS, dH);
+                        }
+                        c0 = c;
+                    }
+                    // the next part's changes stay behind this one's
+                    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                    if (a == b) break;  // a leaf
+                }
+                b0 = b;
+            }
+        }
+        // The sums over the last image: the border's counters come off, then
+        // one pass over the counters, which zeroes them for the next item.
+        __syncthreads();
+        unsigned long long sq = 0, hits = 0;
+        const int nring = 2 * R.rw + 2 * th;
+        for (int k = tid; k < nring; k += NT) {
+            int idx;
+            if (k < R.rw) idx = k;
+            else if (k < 2 * R.rw) idx = (th + 1) * R.rw + (k - R.rw);
+            else idx = (1 + ((k - 2 * R.rw) >> 1)) * R.rw + (((k - 2 * R.rw) & 1) ? R.rw - 1 : 0);
+            const unsigned v = tile[idx];
+            sq -= (unsigned long long)v * v;
+            hits -= v;
+        }
+        __syncthreads();
+        uint4* const t4 = reinterpret_cast<uint4*>(tile);
+        const int n4 = (R.rw * (th + 2) + 3) >> 2;
+        for (int i = tid; i < n4; i += NT) {
+            const uint4 v = t4[i];
+            t4[i] = make_uint4(0u, 0u, 0u, 0u);
+            sq += (unsigned long long)v.x * v.x + (unsigned long long)v.y * v.y + (unsigned long long)v.z * v.z +
+                  (unsigned long long)v.w * v.w;
+            hits += (unsigned long long)v.x + v.y + v.z + v.w;
+        }
+        sq = wave_total(sq);
+        hits = wave_total(hits);
+        if (lane == 63) {
+            atomicAdd(&s_fin[0], sq);
+            atomicAdd(&s_fin[1], hits);
+        }
+        __syncthreads();
+        if (tid < 64) {
+            // lane p: the image of phase p.  The last image's sums less its
+            // extra pixels give the last centre's, less the moves after
+            // centre k that centre's.
+            const int k = lane / 3, side = lane - 3 * k;
+            unsigned long long dS = 0, dH = 0;
+            if (lane < kNodePhases) {
+                dS = s_dS[lane];
+                dH = (unsigned long long)(long long)s_dH[lane];
+            }
+            unsigned long long ss = side ? 0ull : dS, hh = side ? 0ull : dH;
+            for (int o = 1; o < 64; o <<= 1) {
+                const unsigned long long s2 = __shfl_down(ss, o, 64), h2 = __shfl_down(hh, o, 64);
+                if (lane + o < 64) {
+                    ss += s2;
+                    hh += h2;
+                }
+            }
+            const unsigned long long Sc = s_fin[0] - s_dS[3 * m - 1] - (side ? ss : ss - dS);
+            const unsigned long long Nc = s_fin[1] - (unsigned long long)(long long)s_dH[3 * m - 1] - (side ? hh : hh - dH);
+            const int i = __shfl(slot, min(k, 63), 64), hk = __shfl(kids, min(k, 63), 64);
+            if (k < m && (side == 0 || hk)) {
+                Part pt;
+                pt.S = side ? Sc + dS : Sc;
+                pt.N = (long long)Nc + (side == 2 ? s_dN[k] : 0);
+                pt.U = side ? Nc + dH : Nc;
+                pt.pad = 0;
+                part[((long long)w * HS + (side == 0 ? i : F + 2 * i + side - 1)) * g.T + t] = pt;
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            if (lane < kNodePhases) {
+                s_dS[lane] = 0ull;
+                s_dH[lane] = 0;
+            }
+            if (lane < kMaxNodes) s_dN[lane] = 0;
+            if (lane < kEvalWaves + 1) s_cnt[lane] = 0;  // and s_full
+            if (lane < 2) s_fin[lane] = 0ull;
+        }
+    }
+}
+
+static const void* nodes_kernel(int nt) {
+    switch (nt) {
+        case 256: return (const void*)k_nodes<256>;
+        case 512: return (const void*)k_nodes<512>;
+        default: return (const void*)k_nodes<1024>;
+    }
+}
+
+hipError_t nodes_occupancy(int* blocks_per_cu, size_t lds_bytes, int nt) {
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, nodes_kernel(nt), nt, lds_bytes);
+}
+
+hipError_t launch_nodes(hipStream_t s, const Geometry& g, int nblocks, int nt, size_t lds_bytes, const float4* ev,
+                        const long long* seg_off, const int* seg_own, const WinParam* wp, const Hyp* hyps,
+                        const int* act, const Item* items, int qcap, Queue* q, Queue* q_reset, Part* part, int HS,
+                        float4* lists, int mcap, hipEvent_t t0, hipEvent_t t1) {
+    switch (nt) {
+        case 256:
+            hipExtLaunchKernelGGL(k_nodes<256>, dim3(nblocks), dim3(256), (uint32_t)lds_bytes, s, t0, t1, 0u, g, ev,
+                                  seg_off, seg_own, wp, hyps, act, items, qcap, q, q_reset, part, HS, lists, mcap);
+            break;
+        case 512:
+            hipExtLaunchKernelGGL(k_nodes<512>, dim3(nblocks), dim3(512), (uint32_t)lds_bytes, s, t0, t1, 0u, g, ev,
+                                  seg_off, seg_own, wp, hyps, act, items, qcap, q, q_reset, part, HS, lists, mcap);
+            break;
+        default:
+            hipExtLaunchKernelGGL(k_nodes<1024>, dim3(nblocks), dim3(1024), (uint32_t)lds_bytes, s, t0, t1, 0u, g,
+                                  ev, seg_off, seg_own, wp, hyps, act, items, qcap, q, q_reset, part, HS, lists, mcap);
+    }
+    return hipGetLastError();
+}
+
 // The evaluation kernel for nt threads per workgroup (256, 512 or 1024).
 static const void* eval_kernel(int nt) {
     switch (nt) {
@@ -902,6 +1463,8 @@ hipError_t eval_occupancy(int* blocks_per_cu, size_t lds_bytes, int nt) {
 hipError_t eval_set_lds(size_t bytes) {
     for (int nt : {256, 512, 1024}) {
         hipError_t e = hipFuncSetAttribute(eval_kernel(nt), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+        if (e == hipSuccess)
+            e = hipFuncSetAttribute(nodes_kernel(nt), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
@@ -933,6 +1496,13 @@ hipError_t launch_eval(hipStream_t s, const Geometry& g, int nblocks, int nt, si
 
 constexpr int NTF = kFrontThreads;
 constexpr int NWF = NTF / 64;
+
+// A node group lists at most this share of the events, by the estimate lam
+// of emit_hyps.  An event moves at most four times the mean (a corner of the
+// sensor, the start of the window), so by less than a pixel.  Measured on 32
+// windows of 346x260 and 64 of 640x480, per batch: 0.1 5.03 and 23.7 ms, 0.2
+// 5.01 and 23.6, 0.3 5.08 and 23.8 (7.29 and 40.3 without node groups).
+constexpr float kNodeShare = 0.2f;
 
 // Exclusive prefix sum of v over the workgroup (in thread order); `total`
 // receives the sum.  All threads must call it.
@@ -1043,6 +1613,27 @@ __device__ void emit_items(const Search& sp, int w, const int* tiles, int nt, in
     __syncthreads();
 }
 
+// Node items of window w, tile-major, from the end of its queue's slots:
+// group k holds the sorted nodes act[base + gs[k]] up to the next group's start.
+__device__ void emit_node_items(int w, const int* tiles, int nt, int base, const int* gs, int ng, int nodes,
+                                Item* items, int qcap, Queue* nf) {
+    const int qr = w % kXcd;
+    Item* const qlast = items + (long long)(qr + 1) * qcap - 1;
+    __shared__ int s_nbase;
+    if (threadIdx.x == 0) s_nbase = (ng * nt) ? atomicAdd(&nf[qr].n_items, ng * nt) : 0;
+    __syncthreads();
+    for (int k = threadIdx.x; k < ng * nt; k += NTF) {
+        const int ti = k / ng, gi = k % ng;
+        Item it;
+        it.w = w;
+        it.t = tiles[ti];
+        it.r0 = base + gs[gi];
+        it.cnt = (gi + 1 < ng ? gs[gi + 1] : nodes) - gs[gi];
+        *(qlast - (s_nbase + k)) = it;
+    }
+    __syncthreads();
+}
+
 // Hypotheses of the selected nodes, the list of active slots, and the work
 // items.  q_rem: nodes left in the queue; n_kids: selected nodes with
 // children.  When every node the queue can hold after the next step is
@@ -1051,9 +1642,9 @@ __device__ void emit_items(const Search& sp, int w, const int* tiles, int nt, in
 // the children get the endpoint certificate (exact bounds when it fails, in
 // the same step).  For the gamma stop a certified child's points are
 // bounded by its nearest exactly bounded ancestor's bound instead.
-__device__ void emit_hyps(const Search& sp, const WinParam& p, int w, int T, const int* tiles, int nt,
+__device__ void emit_hyps(const Search& sp, const WinParam& p, int w, int T, const int* tiles, int nt, int most,
                           const Sel* sl, int n_sel, int q_rem, int n_kids, float kinc, Hyp* hy, int* act,
-                          Item* items, int qcap, Queue* qf, int* s_wave) {
+                          Item* items, int qcap, Queue* qf, int* s_wave, bool groups) {
     const int F = sp.F, HS = sp.HS;
     const bool cert = sp.cert && sp.max_nodes == 0 && q_rem + 2 * n_kids <= F && q_rem + 2 * n_kids <= sp.CAP;
     // a node's children take the certificate when it is expected to clear
@@ -1061,6 +1652,32 @@ __device__ void emit_hyps(const Search& sp, const WinParam& p, int w, int T, con
     // exact bound (measured on the three batches: margins of 0.5 to 1.5 x
     // K_inc within 3%, 1.0 best; no prediction: +10% on 1280x720, +25% on
     // 346x260)
+    // Nodes that go into node groups.  lam estimates how many pixels an event
+    // moves per unit of rate (the mean of |ax| + |ay| over the sensor and the
+    // window), so lam times a node's width is about the share of the events
+    // that change pixel inside it.
+    __shared__ float s_na[kMaxF], s_nb[kMaxF];
+    __shared__ int s_ord[kMaxF], s_gs[kMaxF];
+    __shared__ int s_ng;
+    const float per = (float)most / (float)max(sp.nwave, 1);  // a wave's events of the fullest tile
+    // the share of the events that a group may list
+    const float share = fminf(kNodeShare, (float)sp.nlist / fmaxf(per, 1.0f));
+    const float lam = p.kscale > 0.0f ? 0.25f * (float)kNB / p.kscale : 0.0f;
+    int nodes = 0;
+    for (int i0 = 0; groups && sp.nmax > 0 && i0 < n_sel; i0 += NTF) {
+        const int i = i0 + threadIdx.x;
+        bool in = false;
+        if (i < n_sel) {
+            const float a = rate_of(grid_d(sp.d_lo, sp.d_hi, sp.L, sl[i].ja), p.tau);
+            const float b = rate_of(grid_d(sp.d_lo, sp.d_hi, sp.L, sl[i].jb), p.tau);
+            in = lam * (b - a) <= share && !(cert && sl[i].kids && sl[i].lc > kinc);
+            s_na[i] = in ? a : INFINITY;
+            s_nb[i] = b;
+        }
+        int tot;
+        block_scan(in ? 1 : 0, s_wave, tot);
+        nodes += tot;
+    }
     int na = 0;  // active slots so far
     for (int h0 = 0; h0 < HS; h0 += NTF) {
         const int h = h0 + threadIdx.x;
@@ -1084,25 +1701,69 @@ __device__ void emit_hyps(const Search& sp, const WinParam& p, int w, int T, con
             }
         }
         if (h < HS) hy[h] = hp;
+        const int node = h < F ? h : (h - F) >> 1;
+        const bool alone = hp.kind != HYP_NONE && !(nodes && s_na[node] < INFINITY);
         int tot;
-        const int r = block_scan(hp.kind != HYP_NONE ? 1 : 0, s_wave, tot);
-        if (hp.kind != HYP_NONE) act[na + r] = h;
+        const int r = block_scan(alone ? 1 : 0, s_wave, tot);
+        if (alone) act[na + r] = h;
         na += tot;
     }
     emit_items(sp, w, tiles, nt, na, items, qcap, qf);
+    if (!nodes) return;
+    // the grouped nodes in grid order
+    for (int i = threadIdx.x; i < n_sel; i += NTF) {
+        const float a = s_na[i];
+        if (!(a < INFINITY)) continue;
+        int r = 0;
+        for (int k = 0; k < n_sel; ++k) r += (s_na[k] < a || (s_na[k] == a && k < i)) ? 1 : 0;
+        s_ord[r] = i;
+        act[na + r] = i;
+    }
+    __syncthreads();
+    // A group takes the nodes that follow while its hull lists at most hull
+    // of the events: s_gs[r] = the node after the group that starts at r.
+    const float hull = share / fmaxf(lam, 1e-7f);
+    const long long alone_items = (long long)sp.B * nodes * nt;  // items with one node each, all windows alike
+    const int gm = (int)max(1ll, min((long long)sp.nmax, alone_items / max(sp.nslots, 1ll)));
+    for (int r = threadIdx.x; r < nodes; r += NTF) {
+        const float lim = s_na[s_ord[r]] + hull;
+        int e = r + 1;
+        while (e < nodes && e < r + gm && s_nb[s_ord[e]] <= lim) ++e;
+        s_gs[r] = e;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        int n = 0;
+        for (int r = 0; r < nodes; ++n) {  // n <= r: entries still needed are not overwritten
+            const int e = s_gs[r];
+            s_gs[n] = r;
+            r = e;
+        }
+        s_ng = n;
+    }
+    __syncthreads();
+    const int ng = s_ng;
+    emit_node_items(w, tiles, nt, na, s_gs, ng, nodes, items, qcap, qf + 2 * kXcd);
 }
 
+// Tiles of window w that hold events; s_nt[0]: how many, s_nt[1]: the events
+// of the fullest.
 __device__ __forceinline__ void nonempty_tiles(int w, int T, const long long* seg_off, int* tiles, int* s_nt,
                                                int* s_wave) {
     const int t = threadIdx.x;
-    int ne = 0;
+    int ne = 0, size = 0;
     if (t < T) {
         const long long seg = (long long)w * T + t;
-        ne = seg_off[seg + 1] > seg_off[seg] ? 1 : 0;
+        size = (int)(seg_off[seg + 1] - seg_off[seg]);  // fewer than 2^28
+        ne = size > 0 ? 1 : 0;
     }
+    if (threadIdx.x == 0) s_nt[1] = 0;
     int tot;
     const int r = block_scan(ne, s_wave, tot);
-    if (ne) tiles[r] = t;
+    if (ne) {
+        tiles[r] = t;
+        atomicMax(&s_nt[1], size);
+    }
     if (threadIdx.x == 0) *s_nt = tot;
     __syncthreads();
 }
@@ -1115,7 +1776,7 @@ __global__ __launch_bounds__(NTF) void k_init(Search sp, const WinParam* __restr
     const int w = blockIdx.x;
     const unsigned top = 1u << sp.L;
     Sel* sl = sel + (long long)w * sp.F;
-    __shared__ int s_nsel, s_nt, s_wave[NWF];
+    __shared__ int s_nsel, s_nt[2], s_wave[NWF];
     __shared__ int s_tiles[kMaxTiles];
     if (chk.wstat) {
         const int bad = chk.wstat[w] ? chk.wstat[w]
@@ -1170,9 +1831,9 @@ __global__ __launch_bounds__(NTF) void k_init(Search sp, const WinParam* __restr
         s_nsel = n_sel;
     }
     __syncthreads();
-    nonempty_tiles(w, T, seg_off, s_tiles, &s_nt, s_wave);
-    emit_hyps(sp, wp[w], w, T, s_tiles, s_nt, sl, s_nsel, 0, 1, -1.0f, hyps + (long long)w * sp.HS,
-              act + (long long)w * sp.HS, items, qcap, q, s_wave);
+    nonempty_tiles(w, T, seg_off, s_tiles, s_nt, s_wave);
+    emit_hyps(sp, wp[w], w, T, s_tiles, s_nt[0], s_nt[1], sl, s_nsel, 0, 1, -1.0f, hyps + (long long)w * sp.HS,
+              act + (long long)w * sp.HS, items, qcap, q, s_wave, false);
 }
 
 hipError_t launch_init(hipStream_t s, const Search& sp, const WinParam* wp, const float* seeds, int B,
@@ -1231,7 +1892,7 @@ __global__ __launch_bounds__(NTF) void k_frontier(
     __shared__ long long s_hi[NTF];
     __shared__ unsigned long long s_lo[NTF];
     __shared__ unsigned s_j[NTF];
-    __shared__ int s_wave[NWF], s_tiles[kMaxTiles], s_nt;
+    __shared__ int s_wave[NWF], s_tiles[kMaxTiles], s_nt[2];
     __shared__ int s_hist[130];
     __shared__ int s_bstar, s_quota, s_stop, s_take, s_anycert, s_ubmax;
     __shared__ unsigned long long s_pix;
@@ -1247,8 +1908,8 @@ __global__ __launch_bounds__(NTF) void k_frontier(
     Hyp* hy = hyps + (long long)w * HS;
     int* ac = act + (long long)w * HS;
     const Part* pw = part + (long long)w * HS * T;
-    nonempty_tiles(w, T, seg_off, s_tiles, &s_nt, s_wave);
-    const int nt = s_nt;
+    nonempty_tiles(w, T, seg_off, s_tiles, s_nt, s_wave);
+    const int nt = s_nt[0];
     i128 Kinc = mk128(s.Kinc_hi, s.Kinc_lo);
     unsigned jinc = s.j_inc;
     const bool repaired = s.n_repair > 0;  // phase 0 of this step is done
@@ -1556,8 +2217,8 @@ __global__ __launch_bounds__(NTF) void k_frontier(
     }
     __syncthreads();
     if (s.steps >= sp.max_steps) return;  // cut short: nothing more is evaluated
-    emit_hyps(sp, p, w, T, s_tiles, nt, sl, nsel, out, nkids, (float)i128_to_double(Kinc), hyps + (long long)w * HS,
-              act + (long long)w * HS, items, qcap, qf, s_wave);
+    emit_hyps(sp, p, w, T, s_tiles, nt, s_nt[1], sl, nsel, out, nkids, (float)i128_to_double(Kinc), hyps + (long long)w * HS,
+              act + (long long)w * HS, items, qcap, qf, s_wave, true);
 }
 
 // Grid range still alive in each active window: the queued nodes and those
@@ -1650,7 +2311,7 @@ __global__ __launch_bounds__(kCheckThreads) void k_plan_check(
     __shared__ long long s_ev[kCheckThreads / 64];
     __shared__ int s_scan[kCheckThreads];
     const int tid = threadIdx.x;
-    if (tid < 2 * kXcd) {
+    if (tid < kQueues) {
         q[tid].n_items = 0;
         q[tid].next = 0;
     }
