@@ -265,7 +265,6 @@ hipError_t launch_stream_trel(hipStream_t s, const double* t, const long long* o
                               double t_start, double tau, float* t_rel);
 
 // learned incumbent (ecmd_cnn.hip)
-size_t cnn_lds_bytes();
 int cnn_nparam();
 hipError_t cnn_set_lds();
 hipError_t launch_cnn(hipStream_t s, const float* P, const uint16_t* imgs, int B, float* out, int mode,
