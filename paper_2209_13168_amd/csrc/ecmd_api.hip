@@ -5,6 +5,7 @@
 // (a2, a3), frontier step (a4)] until every window is certified.  All
 // search state stays in device memory; the host only launches and polls a
 // single counter of windows still running.
+#include <limits.h>
 #include <math.h>
 #include <stdarg.h>
 #include <stdio.h>
@@ -1767,20 +1768,52 @@ static int preproc_impl(ecmd_ctx* c, int kind, const ecmd_sensor* in_s, const ec
         doff = c->soff.as<long long>();
         base = 0;
     }
-    HIPCHK(c, c->keep.ensure(std::max(n, 1ll)));
-    const long long nb = (n + 1023) / 1024;
-    HIPCHK(c, c->misc.ensure(sizeof(long long) * (nb + 1)));
-    unsigned char* keep = (unsigned char*)c->keep.p;
+    // the windows' chunks
+    HIPCHK(c, c->pinned.ensure(sizeof(int) * (B + 1)));
+    int* const blk = (int*)c->pinned.p;
+    long long chunks = 0;
+    for (int w = 0; w <= B; ++w) {
+        if (chunks > INT_MAX) return fail(c, ECMD_EINVAL, "too many events");
+        blk[w] = (int)chunks;
+        if (w < B) chunks += (off[w + 1] - off[w] + kPreChunk - 1) / kPreChunk;
+    }
+    const int nblk = blk[B];
+    const size_t nb1 = std::max(nblk, 1);
+    HIPCHK(c, c->blk.ensure(sizeof(int) * (B + 1)));
+    HIPCHK(c, hipMemcpyAsync(c->blk.p, blk, sizeof(int) * (B + 1), hipMemcpyHostToDevice, c->stream));
+    const int* dblk = c->blk.as<int>();
+    HIPCHK(c, c->keep.ensure(nb1 * (kPreChunk / 8)));
+    HIPCHK(c, c->err_flag.ensure(sizeof(int) * nb1));
+    HIPCHK(c, c->misc.ensure(sizeof(long long) * (nb1 + 1)));
+    unsigned long long* words = c->keep.as<unsigned long long>();
+    int* blk_cnt = c->err_flag.as<int>();
     const int W = in_s->width, H = in_s->height;
     if (kind == 0) {
-        const size_t M = (size_t)W * H;
-        HIPCHK(c, c->counts.ensure(sizeof(unsigned) * M * std::max(B, 1)));
-        HIPCHK(c, hipMemsetAsync(c->counts.p, 0, sizeof(unsigned) * M * std::max(B, 1), c->stream));
-        HIPCHK(c, launch_hot_keep(c->stream, dx, dy, doff, B, n, W, H, c->counts.as<unsigned>(), (unsigned)max_count,
-                                  keep));
+        const size_t M = (size_t)W * H, nwin = std::max(B, 1);
+        int nb = hot_bands(W, H);
+        int* cnt = nullptr;
+        long long* cursor = nullptr;
+        uint16_t* list = nullptr;
+        unsigned long long* hot = nullptr;
+        if (nb > 0) {
+            HIPCHK(c, c->cnt_own.ensure(sizeof(int) * nwin * nb));
+            HIPCHK(c, c->cursor.ensure(sizeof(long long) * (nwin * nb + 1)));
+            HIPCHK(c, c->img.ensure(sizeof(uint16_t) * std::max(n, 1ll)));
+            HIPCHK(c, c->counts.ensure(nwin * ((M + 63) / 64) * 8));
+            HIPCHK(c, hipMemsetAsync(c->cnt_own.p, 0, sizeof(int) * nwin * nb, c->stream));
+            cnt = c->cnt_own.as<int>();
+            cursor = c->cursor.as<long long>();
+            list = c->img.as<uint16_t>();
+            hot = c->counts.as<unsigned long long>();
+        } else {
+            HIPCHK(c, c->counts.ensure(sizeof(unsigned) * M * nwin));
+            HIPCHK(c, hipMemsetAsync(c->counts.p, 0, sizeof(unsigned) * M * nwin, c->stream));
+        }
+        HIPCHK(c, launch_hot_keep(c->stream, dx, dy, doff, B, dblk, nblk, W, H, nb, cnt, cursor, list, hot,
+                                  c->counts.as<unsigned>(), (unsigned)max_count, words, blk_cnt));
     } else {
         const double th = floor((double)keep_frac * 16777216.0);
-        HIPCHK(c, launch_resample_keep(c->stream, doff, B, n, seed, (unsigned)th, keep));
+        HIPCHK(c, launch_resample_keep(c->stream, doff, B, dblk, nblk, seed, (unsigned)th, words, blk_cnt));
     }
     const float sx = kind == 1 ? (float)out_s->width / (float)W : 1.0f;
     const float sy = kind == 1 ? (float)out_s->height / (float)H : 1.0f;
@@ -1793,8 +1826,8 @@ static int preproc_impl(ecmd_ctx* c, int kind, const ecmd_sensor* in_s, const ec
         ot = oy + std::max(n, 1ll);
         ooff = (long long*)(ot + std::max(n, 1ll));
     }
-    HIPCHK(c, launch_compact(c->stream, dx, dy, dt, doff, B, base, n, keep, c->misc.as<long long>(), sx, sy, ox, oy,
-                             ot, ooff));
+    HIPCHK(c, launch_compact(c->stream, dx, dy, dt, doff, B, dblk, nblk, words, blk_cnt, c->misc.as<long long>(), sx,
+                             sy, ox, oy, ot, ooff));
     if (!(flags & ECMD_DEVICE_PTR)) {
         std::vector<long long> ho(B + 1);
         HIPCHK(c, hipMemcpyAsync(ho.data(), ooff, sizeof(long long) * (B + 1), hipMemcpyDeviceToHost, c->stream));
