@@ -236,6 +236,7 @@ hipError_t launch_rates(hipStream_t s, const float* d_a, const float* d_b, int m
 hipError_t launch_probe_pixels(hipStream_t s, const float* x, const float* y, const float* t_rel,
                                long long n, float tau, float d, int W, int H, float cx, float cy,
                                int* pix);
+constexpr int kDownChunk = 32768;  // events per workgroup of launch_downsample (its `chunk`)
 hipError_t launch_downsample(hipStream_t s, const float* x, const float* y, const long long* offsets,
                              int B, int W, int H, const int* blk_start, int nblk, int chunk,
                              unsigned* counts, uint16_t* out);

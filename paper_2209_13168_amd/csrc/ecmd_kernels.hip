@@ -2552,7 +2552,10 @@ __device__ __forceinline__ uint16_t bf16_rne(float v) {
 
 constexpr int kGrid = 64;
 
-__global__ __launch_bounds__(256) void k_downsample_count(const float* __restrict__ x,
+// A workgroup's chunk is large (kDownChunk events): it clears and adds up to
+// 4096 counters however few events it bins (64 windows, 20M events: chunks of
+// 4096 events 81 us, of 32768 48 us).
+__global__ __launch_bounds__(1024) void k_downsample_count(const float* __restrict__ x,
                                                           const float* __restrict__ y,
                                                           const long long* __restrict__ offsets, int B,
                                                           int W, int H, const int* __restrict__ blk_start,
@@ -2591,7 +2594,7 @@ hipError_t launch_downsample(hipStream_t s, const float* x, const float* y, cons
                              uint16_t* out) {
     if (B <= 0) return hipSuccess;
     if (nblk > 0) {
-        k_downsample_count<<<nblk, 256, 0, s>>>(x, y, offsets, B, W, H, blk_start, chunk, counts);
+        k_downsample_count<<<nblk, 1024, 0, s>>>(x, y, offsets, B, W, H, blk_start, chunk, counts);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }

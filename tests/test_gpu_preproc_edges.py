@@ -66,3 +66,20 @@ def test_resample(ctx, sizes, keep):
     want = preproc.resample(x, y, t, off, 346, 260, 43, 32, keep, 77)
     for g, w in zip(got, want):
         assert np.array_equal(g, w), (sizes, keep)
+
+
+@pytest.mark.parametrize("sizes", [[0], [1, 0, 5], [32_767, 32_768, 32_769]])
+def test_downsample(ctx, sizes):
+    from paper_2209_13168_amd import ecmd
+
+    x, y, _, off = _events(sizes, 346, 260, 5)
+    got = ctx.downsample(ecmd.sensor(346, 260, (173, 130)), x, y, off).reshape(len(sizes), 64, 64)
+    for k, n in enumerate(sizes):
+        a, b = off[k], off[k + 1]
+        bx = np.clip(np.floor(x[a:b] * np.float32(64) / np.float32(346)), 0, 63).astype(int)
+        by = np.clip(np.floor(y[a:b] * np.float32(64) / np.float32(260)), 0, 63).astype(int)
+        cnt = np.zeros((64, 64), np.float32)
+        np.add.at(cnt, (by, bx), 1)
+        u = (cnt * (np.float32(4096) / np.float32(max(n, 1)) if n else np.float32(0))).astype(np.float32).view(np.uint32)
+        want = ((u + 0x7FFF + ((u >> 16) & 1)) >> 16).astype(np.uint16)
+        assert np.array_equal(got[k], want)
