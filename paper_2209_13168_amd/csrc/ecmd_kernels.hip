@@ -1504,26 +1504,57 @@ constexpr int NWF = NTF / 64;
 // 5.01 and 23.6, 0.3 5.08 and 23.8 (7.29 and 40.3 without node groups).
 constexpr float kNodeShare = 0.2f;
 
+// Scratch of the workgroup's scans: each call alternates between two rows, so
+// a call needs one barrier (the row it writes was last read before the barrier
+// of the call between).  `turn` starts at 0 in every thread and moves alike.
+// The frontier is a serial chain of such calls on one workgroup per window;
+// with two barriers and a shuffle scan for flags as well a round took 9.9 us
+// on one 128 x 128 window, with this and slot_sums' grouped loads 8.8.
+struct ScanLds {
+    int row[2][NWF];
+};
+
 // Exclusive prefix sum of v over the workgroup (in thread order); `total`
 // receives the sum.  All threads must call it.
-__device__ __forceinline__ int block_scan(int v, int* s_wave, int& total) {
+__device__ __forceinline__ int block_scan(int v, ScanLds* sc, int& turn, int& total) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     int x = v;
     for (int o = 1; o < 64; o <<= 1) {
         const int y = __shfl_up(x, o, 64);
         if (lane >= o) x += y;
     }
-    if (lane == 63) s_wave[wave] = x;
+    int* const row = sc->row[turn & 1];
+    ++turn;
+    if (lane == 63) row[wave] = x;
     __syncthreads();
     int base = 0, tot = 0;
+#pragma unroll
     for (int k = 0; k < NWF; ++k) {
-        const int t = s_wave[k];
+        const int t = row[k];
         if (k < wave) base += t;
         tot += t;
     }
-    __syncthreads();
     total = tot;
     return base + x - v;
+}
+
+// The same for a flag per thread: a wave's flags are one ballot.
+__device__ __forceinline__ int block_rank(bool f, ScanLds* sc, int& turn, int& total) {
+    const int wave = threadIdx.x >> 6;
+    const unsigned long long m = __ballot(f);
+    int* const row = sc->row[turn & 1];
+    ++turn;
+    if ((threadIdx.x & 63) == 0) row[wave] = __popcll(m);
+    __syncthreads();
+    int base = 0, tot = 0;
+#pragma unroll
+    for (int k = 0; k < NWF; ++k) {
+        const int t = row[k];
+        if (k < wave) base += t;
+        tot += t;
+    }
+    total = tot;
+    return base + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
 }
 
 // Lexicographic maximum of (K, -j) over the workgroup: within each wave by
@@ -1576,11 +1607,20 @@ __device__ __forceinline__ void slot_sums(const Part* pw, int slot, int T, const
     S = 0;
     N = 0;
     U = 0;
-    for (int k = 0; k < nt; ++k) {
-        const Part q = pw[(long long)slot * T + tiles[k]];
-        S += q.S;
-        N += q.N;
-        U += q.U;
+    // eight tiles' loads in flight (one after another they are a chain of
+    // nt memory latencies)
+    constexpr int G = 8;
+    for (int k = 0; k < nt; k += G) {
+        Part q[G];
+#pragma unroll
+        for (int j = 0; j < G; ++j) q[j] = pw[(long long)slot * T + tiles[min(k + j, nt - 1)]];
+#pragma unroll
+        for (int j = 0; j < G; ++j)
+            if (k + j < nt) {
+                S += q[j].S;
+                N += q[j].N;
+                U += q[j].U;
+            }
     }
 }
 
@@ -1644,7 +1684,7 @@ __device__ void emit_node_items(int w, const int* tiles, int nt, int base, const
 // bounded by its nearest exactly bounded ancestor's bound instead.
 __device__ void emit_hyps(const Search& sp, const WinParam& p, int w, int T, const int* tiles, int nt, int most,
                           const Sel* sl, int n_sel, int q_rem, int n_kids, float kinc, Hyp* hy, int* act,
-                          Item* items, int qcap, Queue* qf, int* s_wave, bool groups) {
+                          Item* items, int qcap, Queue* qf, ScanLds* sc, int& turn, bool groups) {
     const int F = sp.F, HS = sp.HS;
     const bool cert = sp.cert && sp.max_nodes == 0 && q_rem + 2 * n_kids <= F && q_rem + 2 * n_kids <= sp.CAP;
     // a node's children take the certificate when it is expected to clear
@@ -1675,7 +1715,7 @@ __device__ void emit_hyps(const Search& sp, const WinParam& p, int w, int T, con
             s_nb[i] = b;
         }
         int tot;
-        block_scan(in ? 1 : 0, s_wave, tot);
+        block_rank(in, sc, turn, tot);
         nodes += tot;
     }
     int na = 0;  // active slots so far
@@ -1704,7 +1744,7 @@ __device__ void emit_hyps(const Search& sp, const WinParam& p, int w, int T, con
         const int node = h < F ? h : (h - F) >> 1;
         const bool alone = hp.kind != HYP_NONE && !(nodes && s_na[node] < INFINITY);
         int tot;
-        const int r = block_scan(alone ? 1 : 0, s_wave, tot);
+        const int r = block_rank(alone, sc, turn, tot);
         if (alone) act[na + r] = h;
         na += tot;
     }
@@ -1749,7 +1789,7 @@ __device__ void emit_hyps(const Search& sp, const WinParam& p, int w, int T, con
 // Tiles of window w that hold events; s_nt[0]: how many, s_nt[1]: the events
 // of the fullest.
 __device__ __forceinline__ void nonempty_tiles(int w, int T, const long long* seg_off, int* tiles, int* s_nt,
-                                               int* s_wave) {
+                                               ScanLds* sc, int& turn) {
     const int t = threadIdx.x;
     int ne = 0, size = 0;
     if (t < T) {
@@ -1759,7 +1799,7 @@ __device__ __forceinline__ void nonempty_tiles(int w, int T, const long long* se
     }
     if (threadIdx.x == 0) s_nt[1] = 0;
     int tot;
-    const int r = block_scan(ne, s_wave, tot);
+    const int r = block_rank(ne != 0, sc, turn, tot);
     if (ne) {
         tiles[r] = t;
         atomicMax(&s_nt[1], size);
@@ -1776,7 +1816,9 @@ __global__ __launch_bounds__(NTF) void k_init(Search sp, const WinParam* __restr
     const int w = blockIdx.x;
     const unsigned top = 1u << sp.L;
     Sel* sl = sel + (long long)w * sp.F;
-    __shared__ int s_nsel, s_nt[2], s_wave[NWF];
+    __shared__ int s_nsel, s_nt[2];
+    __shared__ ScanLds s_scan;
+    int turn = 0;
     __shared__ int s_tiles[kMaxTiles];
     if (chk.wstat) {
         const int bad = chk.wstat[w] ? chk.wstat[w]
@@ -1831,9 +1873,9 @@ __global__ __launch_bounds__(NTF) void k_init(Search sp, const WinParam* __restr
         s_nsel = n_sel;
     }
     __syncthreads();
-    nonempty_tiles(w, T, seg_off, s_tiles, s_nt, s_wave);
+    nonempty_tiles(w, T, seg_off, s_tiles, s_nt, &s_scan, turn);
     emit_hyps(sp, wp[w], w, T, s_tiles, s_nt[0], s_nt[1], sl, s_nsel, 0, 1, -1.0f, hyps + (long long)w * sp.HS,
-              act + (long long)w * sp.HS, items, qcap, q, s_wave, false);
+              act + (long long)w * sp.HS, items, qcap, q, &s_scan, turn, false);
 }
 
 hipError_t launch_init(hipStream_t s, const Search& sp, const WinParam* wp, const float* seeds, int B,
@@ -1857,10 +1899,10 @@ __device__ __forceinline__ float child_cert(unsigned long long U, long long N) {
 
 // Append the children whose keep flag is set to the queue (array order),
 // noting an overflow of the capacity.
-__device__ __forceinline__ void queue_append(Node* fr, int& n, int CAP, bool keep, const Node& nd, int* s_wave,
-                                             int& overflow) {
+__device__ __forceinline__ void queue_append(Node* fr, int& n, int CAP, bool keep, const Node& nd, ScanLds* sc,
+                                             int& turn, int& overflow) {
     int tot;
-    const int r = block_scan(keep ? 1 : 0, s_wave, tot);
+    const int r = block_rank(keep, sc, turn, tot);
     if (keep && n + r < CAP) fr[n + r] = nd;
     if (n + tot > CAP) overflow = 1;
     n = min(n + tot, CAP);
@@ -1892,7 +1934,9 @@ __global__ __launch_bounds__(NTF) void k_frontier(
     __shared__ long long s_hi[NTF];
     __shared__ unsigned long long s_lo[NTF];
     __shared__ unsigned s_j[NTF];
-    __shared__ int s_wave[NWF], s_tiles[kMaxTiles], s_nt[2];
+    __shared__ int s_tiles[kMaxTiles], s_nt[2];
+    __shared__ ScanLds s_scan;
+    int turn = 0;
     __shared__ int s_hist[130];
     __shared__ int s_bstar, s_quota, s_stop, s_take, s_anycert, s_ubmax;
     __shared__ unsigned long long s_pix;
@@ -1908,7 +1952,7 @@ __global__ __launch_bounds__(NTF) void k_frontier(
     Hyp* hy = hyps + (long long)w * HS;
     int* ac = act + (long long)w * HS;
     const Part* pw = part + (long long)w * HS * T;
-    nonempty_tiles(w, T, seg_off, s_tiles, s_nt, s_wave);
+    nonempty_tiles(w, T, seg_off, s_tiles, s_nt, &s_scan, turn);
     const int nt = s_nt[0];
     i128 Kinc = mk128(s.Kinc_hi, s.Kinc_lo);
     unsigned jinc = s.j_inc;
@@ -1995,10 +2039,10 @@ __global__ __launch_bounds__(NTF) void k_frontier(
                     if (!keep) atomicAdd((unsigned long long*)&s_pruned, 1ull);
                 }
             }
-            queue_append(fr, n, CAP, keep, nd, s_wave, overflow);
+            queue_append(fr, n, CAP, keep, nd, &s_scan, turn, overflow);
             // the children to bound exactly between the phases
             int tot;
-            const int r = block_scan(rep ? 1 : 0, s_wave, tot);
+            const int r = block_rank(rep, &s_scan, turn, tot);
             if (rep) {
                 hy[F + c].kind = HYP_INTERVAL;  // same end rates
                 ac[nrep + r] = F + c;
@@ -2086,7 +2130,7 @@ __global__ __launch_bounds__(NTF) void k_frontier(
     // improvable nodes in larger classes, n_keep = all of them
     const int hb = tid < 130 ? s_hist[129 - tid] : 0;
     int n_keep = 0;
-    const int before = block_scan(hb, s_wave, n_keep);
+    const int before = block_scan(hb, &s_scan, turn, n_keep);
     if (tid == 0) {
         s.bound_evals += s_nbound;
         s.event_hyp += s_nbound * p.n_events;
@@ -2181,16 +2225,16 @@ __global__ __launch_bounds__(NTF) void k_frontier(
             }
         }
         int tot_c;
-        const int rc = block_scan(cand, s_wave, tot_c);
+        const int rc = block_rank(cand != 0, &s_scan, turn, tot_c);
         const int take = big || (cand && inb + rc < s_quota);
         if (cand && !take) keep = 1;
         inb += tot_c;
         const unsigned jb = nd.jb & ~kNodeCert;
         const int kids = take && jb - nd.ja >= 4;
         int tot_k, tot_t, tot_d;
-        const int rk = block_scan(keep, s_wave, tot_k);
-        const int rt = block_scan(take, s_wave, tot_t);
-        block_scan(kids, s_wave, tot_d);
+        const int rk = block_rank(keep != 0, &s_scan, turn, tot_k);
+        const int rt = block_rank(take != 0, &s_scan, turn, tot_t);
+        block_rank(kids != 0, &s_scan, turn, tot_d);
         if (keep) fr[out + rk] = nd;
         if (take) {
             Sel x;
@@ -2218,7 +2262,7 @@ __global__ __launch_bounds__(NTF) void k_frontier(
     __syncthreads();
     if (s.steps >= sp.max_steps) return;  // cut short: nothing more is evaluated
     emit_hyps(sp, p, w, T, s_tiles, nt, s_nt[1], sl, nsel, out, nkids, (float)i128_to_double(Kinc), hyps + (long long)w * HS,
-              act + (long long)w * HS, items, qcap, qf, s_wave, true);
+              act + (long long)w * HS, items, qcap, qf, &s_scan, turn, true);
 }
 
 // Grid range still alive in each active window: the queued nodes and those
