@@ -68,7 +68,6 @@ struct HostBuf {
     T* as() const { return static_cast<T*>(p); }
 };
 
-constexpr int kChunk = 4096;          // events per prep workgroup
 constexpr int kDefaultF = 96;         // nodes expanded together (measured: 64 to 192 within 3%; 96 best)
 constexpr int kDefaultCap = 16384;    // queued nodes per window
 constexpr int kMaxSteps = 1 << 20;    // hard stop of the step loop
@@ -349,10 +348,11 @@ static double key_to_double(long long hi, unsigned long long lo) {
 static int run_prep(ecmd_ctx* c, const Geometry& g, const Inputs& in, int B, float d_lo, float d_hi,
                     int* nblk_out, long long* copies_out = nullptr) {
     const int T = g.T;
+    const int chunk = prep_chunk(c->h_off[B] - c->h_off[0]);
     std::vector<int> blk(B + 1, 0);
     for (int w = 0; w < B; ++w) {
         long long n = c->h_off[w + 1] - c->h_off[w];
-        blk[w + 1] = blk[w] + (int)((n + kChunk - 1) / kChunk);
+        blk[w + 1] = blk[w] + (int)((n + chunk - 1) / chunk);
     }
     const int nblk = blk[B];
     HIPCHK(c, c->wp.ensure(sizeof(WinParam) * std::max(B, 1)));
@@ -372,7 +372,7 @@ static int run_prep(ecmd_ctx* c, const Geometry& g, const Inputs& in, int B, flo
     HIPCHK(c, launch_winparam(c->stream, g, in.tau, in.off, B, d_lo, d_hi, c->wp.as<WinParam>()));
     // count + scan (scatter needs the total to size the event store)
     HIPCHK(c, launch_prep(c->stream, 0, g, in.x, in.y, in.t, in.pol, in.off, c->wp.as<WinParam>(), B, c->blk.as<int>(),
-                          nblk, kChunk, c->cnt_own.as<int>(), c->seg_off.as<long long>(), c->seg_own.as<int>(),
+                          nblk, chunk, c->cnt_own.as<int>(), c->seg_off.as<long long>(), c->seg_own.as<int>(),
                           c->cursor.as<unsigned long long>(), nullptr, c->err_flag.as<int>(), -1));
     HIPCHK(c, hipMemcpyAsync(c->pinned.p, c->seg_off.as<long long>() + (size_t)B * T, sizeof(long long),
                              hipMemcpyDeviceToHost, c->stream));
@@ -389,7 +389,7 @@ static int run_prep(ecmd_ctx* c, const Geometry& g, const Inputs& in, int B, flo
     // the end of a segment
     HIPCHK(c, c->ev.ensure(sizeof(float4) * (size_t)(total + kEvalPad)));
     HIPCHK(c, launch_prep(c->stream, 1, g, in.x, in.y, in.t, in.pol, in.off, c->wp.as<WinParam>(), B, c->blk.as<int>(),
-                          nblk, kChunk, nullptr, nullptr, nullptr, c->cursor.as<unsigned long long>(),
+                          nblk, chunk, nullptr, nullptr, nullptr, c->cursor.as<unsigned long long>(),
                           c->ev.as<float4>(), nullptr, -1));
     *nblk_out = nblk;
     if (copies_out) *copies_out = total;
@@ -404,15 +404,16 @@ static int run_prep(ecmd_ctx* c, const Geometry& g, const Inputs& in, int B, flo
 // would not fit the store; run_search checks the total afterwards.
 static hipError_t enqueue_rebin(ecmd_ctx* c, const Geometry& g, const Inputs& in, int B, int nblk) {
     const size_t nctr = prep_counters(B, g.T);
+    const int chunk = prep_chunk(c->h_off[B] - c->h_off[0]);
     hipError_t e = hipMemsetAsync(c->cnt_own.p, 0, sizeof(int) * nctr, c->stream);
     if (e != hipSuccess) return e;
     e = launch_prep(c->stream, 0, g, in.x, in.y, in.t, in.pol, in.off, c->wp.as<WinParam>(), B, c->blk.as<int>(), nblk,
-                    kChunk, c->cnt_own.as<int>(), c->seg_off.as<long long>(), c->seg_own.as<int>(),
+                    chunk, c->cnt_own.as<int>(), c->seg_off.as<long long>(), c->seg_own.as<int>(),
                     c->cursor.as<unsigned long long>(), nullptr, c->err_flag.as<int>(), -1);
     if (e != hipSuccess) return e;
     const long long cap = (long long)(c->ev.cap / sizeof(float4)) - kEvalPad;
     return launch_prep(c->stream, 1, g, in.x, in.y, in.t, in.pol, in.off, c->wp.as<WinParam>(), B, c->blk.as<int>(),
-                       nblk, kChunk, nullptr, c->seg_off.as<long long>(), nullptr, c->cursor.as<unsigned long long>(),
+                       nblk, chunk, nullptr, c->seg_off.as<long long>(), nullptr, c->cursor.as<unsigned long long>(),
                        c->ev.as<float4>(), nullptr, cap);
 }
 
@@ -806,6 +807,7 @@ struct PlanShape {
     ecmd_plan_limits lim{};
     Geometry g{};
     Search sp{};       // G is set per launch
+    int chunk = 0;     // events per prep workgroup
     int nblk_max = 0;  // prep workgroups of the largest launch
     int qcap = 0;
     size_t lds = 0;
@@ -919,7 +921,8 @@ static int plan_shape(ecmd_ctx* c, const ecmd_sensor* sensor, const ecmd_search*
     sp.B = 1;
     sp.gslots = 0;
     const int Bm = L2.max_windows;
-    sh.nblk_max = (int)((L2.max_events + kChunk - 1) / kChunk) + Bm;
+    sh.chunk = prep_chunk(L2.max_events);
+    sh.nblk_max = (int)((L2.max_events + sh.chunk - 1) / sh.chunk) + Bm;
     sh.qcap = ((Bm + kXcd - 1) / kXcd) * sp.HS * g.T;
     sh.lds = eval_lds_bytes(g.ring_px);
     sh.nt = nt;
@@ -940,11 +943,11 @@ static hipError_t plan_prep(const PlanShape& sh, void* const* b, hipStream_t s, 
     hipError_t e = launch_fill_u32(s, (unsigned*)b[PB_CNT], (long long)prep_counters(B, g.T), 0u);
     if (e != hipSuccess) return e;
     e = launch_prep(s, 0, g, x, y, t, pol, off, (const WinParam*)b[PB_WP], B, (const int*)b[PB_BLK], sh.nblk_max,
-                    kChunk, (int*)b[PB_CNT], (long long*)b[PB_SEG_OFF], (int*)b[PB_SEG_OWN],
+                    sh.chunk, (int*)b[PB_CNT], (long long*)b[PB_SEG_OFF], (int*)b[PB_SEG_OWN],
                     (unsigned long long*)b[PB_CURSOR], nullptr, (int*)b[PB_WERR], -1);
     if (e != hipSuccess) return e;
     return launch_prep(s, 1, g, x, y, t, pol, off, (const WinParam*)b[PB_WP], B, (const int*)b[PB_BLK], sh.nblk_max,
-                       kChunk, nullptr, (long long*)b[PB_SEG_OFF], nullptr, (unsigned long long*)b[PB_CURSOR],
+                       sh.chunk, nullptr, (long long*)b[PB_SEG_OFF], nullptr, (unsigned long long*)b[PB_CURSOR],
                        (float4*)b[PB_EV], nullptr, sh.lim.max_records);
 }
 
@@ -971,7 +974,7 @@ static int plan_enqueue(ecmd_ctx* c, const PlanShape& sh, void* const* b, const 
     Queue* q = (Queue*)b[PB_QUEUES];
     Part* part = (Part*)b[PB_PART];
     long long* seg_off = (long long*)b[PB_SEG_OFF];
-    HIPCHK(c, launch_plan_check(s, off, tau, B, sp.d_hi, g.W, g.H, sh.lim.max_events, kChunk, (int*)b[PB_WSTAT],
+    HIPCHK(c, launch_plan_check(s, off, tau, B, sp.d_hi, g.W, g.H, sh.lim.max_events, sh.chunk, (int*)b[PB_WSTAT],
                                 (int*)b[PB_WERR], (int*)b[PB_BLK], q, (int*)b[PB_NACTIVE]));
     HIPCHK(c, launch_winparam(s, g, tau, off, B, sp.d_lo, sp.d_hi, wp));
     HIPCHK(c, plan_prep(sh, b, s, x, y, t_rel, pol, off, B));

@@ -184,6 +184,8 @@ hipError_t launch_winparam(hipStream_t s, const Geometry& g, const float* tau, c
 // Counters of the prep (per window and tile: owned events by walk class,
 // guests by bin and walk class).
 size_t prep_counters(int B, int T);
+// Events per prep workgroup where a call has up to max_events.
+int prep_chunk(long long max_events);
 // Ints of seg_own: per window and tile, the owned events, then the end of
 // each guest bin, counted from the segment's start.
 size_t seg_own_words(int B, int T);

@@ -255,38 +255,9 @@ __device__ __forceinline__ void load_cuts(const Geometry& g, PrepCuts& c) {
     for (int k = threadIdx.x; k <= g.nty; k += blockDim.x) c.row[k] = (float)g.rowcut[k];
 }
 
-// First segment of event i's image: the polarity-aware contrast keeps one
+// First segment of an event's image: the polarity-aware contrast keeps one
 // event image per polarity (p > 0: the second), each tiled alike.
-__device__ __forceinline__ int seg_base(const Geometry& g, const signed char* pol, long long i) {
-    return (pol && pol[i] > 0) ? g.nsp : 0;
-}
-
-constexpr int kPrepThreads = 256;
-
-// Counter of every copy of a prepared event (segment base sb), in the
-// same order for the counting and the scattering passes.  The event's own
-// copy (the one N_low and the certificates read) goes to the tile it
-// starts in, at the low end of the binning range: the corner of its tile
-// rectangle it moves away from.  Every other tile is a guest, reached at
-// higher rates only.
-template <class F>
-__device__ __forceinline__ void for_each_copy(const Geometry& g, const WinParam& p, const PrepCuts& c, int sb,
-                                              float x, float y, float ax, float ay, int tx0, int tx1, int ty0,
-                                              int ty1, int cls, F&& f) {
-    const int ox = ax < 0.0f ? tx1 : tx0, oy = ay < 0.0f ? ty1 : ty0;
-    for (int ty = ty0; ty <= ty1; ++ty) {
-        const int by = cuts_short(p, y, ay, c.row[ay < 0.0f ? ty + 1 : ty]);
-        for (int tx = tx0; tx <= tx1; ++tx) {
-            const int t = sb + ty * g.ntx + tx;
-            if (ty == oy && tx == ox) {
-                f(ctr_own(t, cls));
-            } else {
-                const int bx = cuts_short(p, x, ax, c.col[ax < 0.0f ? tx + 1 : tx]);
-                f(ctr_guest(t, max(bx, by), cls));
-            }
-        }
-    }
-}
+__device__ __forceinline__ int seg_base(const Geometry& g, int pol) { return pol > 0 ? g.nsp : 0; }
 
 // Per-event prep: validity, (ax, ay), reachable tiles and walk class.
 struct PrepEv {
@@ -294,6 +265,31 @@ struct PrepEv {
     float x, y, ax, ay;
     int tx0, tx1, ty0, ty1, cls;
 };
+
+// Counter of a prepared event's own copy (the one N_low and the certificates
+// read; segment base sb): it goes to the tile the event starts in, at the low
+// end of the binning range, the corner of its tile rectangle it moves away
+// from.  Every other tile is a guest, reached at higher rates only.
+__device__ __forceinline__ int own_copy(const Geometry& g, int sb, const PrepEv& e) {
+    return ctr_own(sb + (e.ay < 0.0f ? e.ty1 : e.ty0) * g.ntx + (e.ax < 0.0f ? e.tx1 : e.tx0), e.cls);
+}
+
+// Counters of its guest copies, in the same order for the counting and the
+// scattering passes.
+template <class F>
+__device__ __forceinline__ void for_each_guest(const Geometry& g, const WinParam& p, const PrepCuts& c, int sb,
+                                               const PrepEv& e, F&& f) {
+    if (e.tx0 == e.tx1 && e.ty0 == e.ty1) return;
+    const int ox = e.ax < 0.0f ? e.tx1 : e.tx0, oy = e.ay < 0.0f ? e.ty1 : e.ty0;
+    for (int ty = e.ty0; ty <= e.ty1; ++ty) {
+        const int by = cuts_short(p, e.y, e.ay, c.row[e.ay < 0.0f ? ty + 1 : ty]);
+        for (int tx = e.tx0; tx <= e.tx1; ++tx) {
+            if (ty == oy && tx == ox) continue;
+            const int bx = cuts_short(p, e.x, e.ax, c.col[e.ax < 0.0f ? tx + 1 : tx]);
+            f(ctr_guest(sb + ty * g.ntx + tx, max(bx, by), e.cls));
+        }
+    }
+}
 
 __device__ __forceinline__ PrepEv prep_event(const Geometry& g, const WinParam& p, float xv, float yv, float tv) {
     PrepEv e;
@@ -310,67 +306,142 @@ __device__ __forceinline__ PrepEv prep_event(const Geometry& g, const WinParam& 
     return e;
 }
 
-__global__ __launch_bounds__(kPrepThreads) void k_prep_count(
+// Prep workgroups: kPrepPer events per thread, held in registers between the
+// counting and the writing.  1024 threads share the chunk's zeroing of the
+// counters and its cursor atomics (up to kMaxTiles * kTC of each); with fewer
+// events there are too few such chunks to fill the CUs, and 256 threads are
+// faster (count / scatter: 20M events in 24 tiles 141 / 214 us with 1024
+// threads, 165 / 289 with 256; 2M in 8 tiles 24 / 34.8 and 21.6 / 31.0; one
+// window of 10k 6.2 / 6.8 with 256, 20 / 34 with chunks of 4096).  Eight
+// events per thread: 137 / 306 us for the 20M.
+constexpr int kPrepPer = 4, kPrepMany = 1024, kPrepSome = 256;
+constexpr long long kPrepFew = 1 << 22;
+
+// A thread's PER events of a chunk, all loads in flight; past the chunk's n
+// events the last one again.
+template <int PER>
+struct PrepIn {
+    float x[PER], y[PER], t[PER];
+    int p[PER];
+    template <int NT>
+    __device__ __forceinline__ void load(const float* xs, const float* ys, const float* ts, const signed char* ps,
+                                         long long beg, int n) {
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            const long long i = beg + min(j * NT + (int)threadIdx.x, n - 1);
+            x[j] = xs[i];
+            y[j] = ys[i];
+            t[j] = ts[i];
+            p[j] = ps ? ps[i] : 0;
+        }
+    }
+};
+
+// Bound by instructions (202 VALU per 64 events, three quarters of the issue
+// slots): the tile bands and, for the wave's events with guests, their bins.
+template <int NT, int PER>
+__global__ __launch_bounds__(NT) void k_prep_count(
     Geometry g, const float* __restrict__ x, const float* __restrict__ y, const float* __restrict__ t_rel,
     const signed char* __restrict__ pol, const long long* __restrict__ offsets, const WinParam* __restrict__ wp, int B,
-    const int* __restrict__ blk_start, int chunk, int* __restrict__ cnt, int* __restrict__ err_flag) {
+    const int* __restrict__ blk_start, int* __restrict__ cnt, int* __restrict__ err_flag) {
     extern __shared__ int s_cnt[];  // g.T * kTC counters
     __shared__ PrepCuts s_cuts;
-    if ((int)blockIdx.x >= blk_start[B]) return;  // a grid sized for the largest batch
+    const int blk = blockIdx.x;
+    if (blk >= blk_start[B]) return;  // a grid sized for the largest batch
     const int nc = g.T * kTC;
-    for (int k = threadIdx.x; k < nc; k += blockDim.x) s_cnt[k] = 0;
+    for (int k = threadIdx.x; k < nc; k += NT) s_cnt[k] = 0;
     load_cuts(g, s_cuts);
     __syncthreads();
-    const int w = window_of_block(blk_start, B, blockIdx.x);
-    const int c = blockIdx.x - blk_start[w];
-    const long long beg = offsets[w] + (long long)c * chunk;
-    const long long end = min(beg + chunk, offsets[w + 1]);
+    const int w = window_of_block(blk_start, B, blk);
+    const long long beg = offsets[w] + (long long)(blk - blk_start[w]) * (NT * PER);
+    const int n = (int)min((long long)(NT * PER), offsets[w + 1] - beg);  // >= 1
     const WinParam p = wp[w];
-    for (long long i = beg + threadIdx.x; i < end; i += blockDim.x) {
-        const PrepEv e = prep_event(g, p, x[i], y[i], t_rel[i]);
+    PrepIn<PER> in;
+    in.template load<NT>(x, y, t_rel, pol, beg, n);
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        const int i = j * NT + (int)threadIdx.x;
+        if (i >= n) break;
+        const PrepEv e = prep_event(g, p, in.x[j], in.y[j], in.t[j]);
         if (!e.valid) atomicOr(&err_flag[w], 1);
         if (!e.ok) continue;
-        for_each_copy(g, p, s_cuts, seg_base(g, pol, i), e.x, e.y, e.ax, e.ay, e.tx0, e.tx1, e.ty0, e.ty1, e.cls,
-                      [&](int k) { atomicAdd(&s_cnt[k], 1); });
+        const int sb = seg_base(g, in.p[j]);
+        atomicAdd(&s_cnt[own_copy(g, sb, e)], 1);
+        for_each_guest(g, p, s_cuts, sb, e, [&](int k) { atomicAdd(&s_cnt[k], 1); });
     }
     __syncthreads();
-    for (int k = threadIdx.x; k < nc; k += blockDim.x)
+    for (int k = threadIdx.x; k < nc; k += NT)
         if (s_cnt[k]) atomicAdd(&cnt[(long long)w * nc + k], s_cnt[k]);
 }
 
 // Exclusive scan of the counters of every (window, tile, owned/guest bin,
-// class) in that order (one workgroup: a prefix sum inside each wave, the
-// wave totals through LDS, 1024 counters per round); then the segment of
-// (w, t) starts at its first counter, its owned events end where its first
-// guest bin begins, and guest bin m ends where bin m + 1 (or the next
-// segment) begins.
+// class) in that order (one workgroup); then the segment of (w, t) starts at
+// its first counter, its owned events end where its first guest bin begins,
+// and guest bin m ends where bin m + 1 (or the next segment) begins.  The
+// rounds are a chain of load, scan and barrier, so each takes kScanPer int4
+// per thread, in rows of 64 neighbouring ones, and loads the next round's
+// before it scans: 64 windows of 24 tiles (73728 counters) take 41 us
+// (a CU's bandwidth), one counter per thread and round took 127.
+constexpr int kScanPer = 4;
+static_assert(kTC % 4 == 0, "the counters are read four at a time");
 __global__ __launch_bounds__(1024) void k_prep_scan(int B, int T, const int* __restrict__ cnt,
                                                     long long* __restrict__ seg_off, int* __restrict__ seg_own,
                                                     unsigned long long* __restrict__ cursor) {
-    __shared__ long long s_wave[16];
-    __shared__ long long s_carry;
-    const long long n = (long long)B * T * kTC;
+    __shared__ long long s_wave[2][16];
+    const long long n4 = (long long)B * T * kTC / 4, n = 4 * n4;
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    if (threadIdx.x == 0) s_carry = 0;
-    for (long long base = 0; base < n; base += 1024) {
-        const long long k = base + threadIdx.x;
-        const long long v = k < n ? cnt[k] : 0;
-        long long incl = v;
+    const int4* const c4 = reinterpret_cast<const int4*>(cnt);
+    const long long first = wv * 64 * kScanPer + lane;
+    int4 c[kScanPer], cn[kScanPer];
+#pragma unroll
+    for (int j = 0; j < kScanPer; ++j) cn[j] = first + 64 * j < n4 ? c4[first + 64 * j] : make_int4(0, 0, 0, 0);
+    long long total = 0;
+    int turn = 0;
+    for (long long base = 0; base < n4; base += 1024 * kScanPer, turn ^= 1) {
+        const long long k = base + first;
+        long long v[kScanPer];  // inclusive sums of the row's lanes
+#pragma unroll
+        for (int j = 0; j < kScanPer; ++j) {
+            c[j] = cn[j];
+            const long long kn = k + 1024 * kScanPer + 64 * j;
+            cn[j] = kn < n4 ? c4[kn] : make_int4(0, 0, 0, 0);
+            v[j] = (long long)c[j].x + c[j].y + c[j].z + c[j].w;
+        }
 #pragma unroll
         for (int o = 1; o < 64; o <<= 1) {
-            const long long a = __shfl_up(incl, o, 64);
-            if (lane >= o) incl += a;
+#pragma unroll
+            for (int j = 0; j < kScanPer; ++j) {
+                const long long a = __shfl_up(v[j], o, 64);
+                if (lane >= o) v[j] += a;
+            }
         }
-        if (lane == 63) s_wave[wv] = incl;
-        __syncthreads();  // the wave totals and the last round's carry are visible
-        long long pre = s_carry;
-        for (int j = 0; j < wv; ++j) pre += s_wave[j];
-        if (k < n) cursor[k] = (unsigned long long)(pre + incl - v);
-        __syncthreads();  // every read of s_wave and s_carry is done
-        if (threadIdx.x == 1023) s_carry = pre + incl;
+        long long row[kScanPer], wave = 0;  // before each row of the wave
+#pragma unroll
+        for (int j = 0; j < kScanPer; ++j) {
+            row[j] = wave;
+            wave += __shfl(v[j], 63, 64);
+        }
+        // two rows: the one written here was last read before the barrier
+        // of the round between
+        if (lane == 0) s_wave[turn][wv] = wave;
+        __syncthreads();
+        long long pre = total;
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            const long long a = s_wave[turn][j];
+            if (j < wv) pre += a;
+            total += a;
+        }
+#pragma unroll
+        for (int j = 0; j < kScanPer; ++j) {
+            if (k + 64 * j >= n4) break;
+            ulonglong2* const q = reinterpret_cast<ulonglong2*>(cursor + 4 * (k + 64 * j));
+            const long long r3 = pre + row[j] + v[j] - c[j].w, r2 = r3 - c[j].z, r1 = r2 - c[j].y;
+            q[0] = make_ulonglong2(r1 - c[j].x, r1);
+            q[1] = make_ulonglong2(r2, r3);
+        }
     }
-    __syncthreads();  // the total and every cursor are visible
-    const long long total = s_carry;
+    __syncthreads();  // every cursor is visible
     const auto start = [&](long long k) { return k < n ? (long long)cursor[k] : total; };
     for (int st = threadIdx.x; st < B * T; st += 1024) {
         const long long c0 = (long long)st * kTC;
@@ -383,72 +454,101 @@ __global__ __launch_bounds__(1024) void k_prep_scan(int B, int T, const int* __r
     if (threadIdx.x == 0) seg_off[(long long)B * T] = total;
 }
 
-__global__ __launch_bounds__(kPrepThreads) void k_prep_scatter(
+// The same events again; an owned record's rank in its run is what the
+// counting atomic returned, and the events stay in registers, so nothing is
+// read or worked out a third time (20M events in 24 tiles: 434 -> 214 us, 80M:
+// 2160 -> 1010).  Only the few guests are counted and then ranked.
+template <int NT, int PER>
+__global__ __launch_bounds__(NT) void k_prep_scatter(
     Geometry g, const float* __restrict__ x, const float* __restrict__ y, const float* __restrict__ t_rel,
     const signed char* __restrict__ pol, const long long* __restrict__ offsets, const WinParam* __restrict__ wp, int B,
-    const int* __restrict__ blk_start, int chunk, unsigned long long* __restrict__ cursor,
-    const long long* __restrict__ total, long long cap, float4* __restrict__ ev) {
+    const int* __restrict__ blk_start, unsigned long long* __restrict__ cursor, const long long* __restrict__ total,
+    long long cap, float4* __restrict__ ev) {
     extern __shared__ unsigned long long s_prep[];  // g.T * kTC bases, then as many counts
     const int nc = g.T * kTC;
     unsigned long long* const s_base = s_prep;
     int* const s_cnt = reinterpret_cast<int*>(s_prep + nc);
     __shared__ PrepCuts s_cuts;
-    if ((int)blockIdx.x >= blk_start[B]) return;
+    const int blk = blockIdx.x;
+    if (blk >= blk_start[B]) return;  // a grid sized for the largest batch
     if (total && *total > cap) return;  // the records would not fit the store: nothing is written
     load_cuts(g, s_cuts);
-    for (int k = threadIdx.x; k < nc; k += blockDim.x) s_cnt[k] = 0;
+    for (int k = threadIdx.x; k < nc; k += NT) s_cnt[k] = 0;
     __syncthreads();
-    const int w = window_of_block(blk_start, B, blockIdx.x);
-    const int c = blockIdx.x - blk_start[w];
-    const long long beg = offsets[w] + (long long)c * chunk;
-    const long long end = min(beg + chunk, offsets[w + 1]);
+    const int w = window_of_block(blk_start, B, blk);
+    const long long beg = offsets[w] + (long long)(blk - blk_start[w]) * (NT * PER);
+    const int n = (int)min((long long)(NT * PER), offsets[w + 1] - beg);  // >= 1
     const WinParam p = wp[w];
-    for (long long i = beg + threadIdx.x; i < end; i += blockDim.x) {
-        const PrepEv e = prep_event(g, p, x[i], y[i], t_rel[i]);
-        if (!e.ok) continue;
-        for_each_copy(g, p, s_cuts, seg_base(g, pol, i), e.x, e.y, e.ax, e.ay, e.tx0, e.tx1, e.ty0, e.ty1, e.cls,
-                      [&](int k) { atomicAdd(&s_cnt[k], 1); });
+    PrepIn<PER> in;
+    in.template load<NT>(x, y, t_rel, pol, beg, n);
+    PrepEv e[PER];
+    int sb[PER], rank[PER];
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        const int i = j * NT + (int)threadIdx.x;
+        e[j] = prep_event(g, p, in.x[j], in.y[j], in.t[j]);
+        e[j].ok = e[j].ok && i < n;
+        if (!e[j].ok) continue;
+        sb[j] = seg_base(g, in.p[j]);
+        rank[j] = atomicAdd(&s_cnt[own_copy(g, sb[j], e[j])], 1);
+        for_each_guest(g, p, s_cuts, sb[j], e[j], [&](int k) { atomicAdd(&s_cnt[k], 1); });
     }
     __syncthreads();
-    for (int k = threadIdx.x; k < nc; k += blockDim.x) {
-        const int n = s_cnt[k];
-        s_base[k] = n ? atomicAdd(&cursor[(long long)w * nc + k], (unsigned long long)n) : 0ull;
+    // the owned events have their ranks; the guests are counted again
+    for (int k = threadIdx.x; k < nc; k += NT) {
+        const int m = s_cnt[k];
+        s_base[k] = m ? atomicAdd(&cursor[(long long)w * nc + k], (unsigned long long)m) : 0ull;
         s_cnt[k] = 0;
     }
     __syncthreads();
-    for (long long i = beg + threadIdx.x; i < end; i += blockDim.x) {
-        const PrepEv e = prep_event(g, p, x[i], y[i], t_rel[i]);
-        if (!e.ok) continue;
-        const float4 v = make_float4(e.x, e.y, e.ax, e.ay);
-        for_each_copy(g, p, s_cuts, seg_base(g, pol, i), e.x, e.y, e.ax, e.ay, e.tx0, e.tx1, e.ty0, e.ty1, e.cls,
-                      [&](int k) {
-                          const int r = atomicAdd(&s_cnt[k], 1);
-                          ev[s_base[k] + (unsigned long long)r] = v;
-                      });
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        if (!e[j].ok) continue;
+        const float4 v = make_float4(e[j].x, e[j].y, e[j].ax, e[j].ay);
+        ev[s_base[own_copy(g, sb[j], e[j])] + (unsigned long long)rank[j]] = v;
+        for_each_guest(g, p, s_cuts, sb[j], e[j], [&](int k) {
+            const int r = atomicAdd(&s_cnt[k], 1);
+            ev[s_base[k] + (unsigned long long)r] = v;
+        });
     }
 }
 
+// Events per prep workgroup.
+int prep_chunk(long long max_events) { return (max_events < kPrepFew ? kPrepSome : kPrepMany) * kPrepPer; }
+
 size_t prep_counters(int B, int T) { return (size_t)B * T * kTC; }
 size_t seg_own_words(int B, int T) { return (size_t)B * T * (kGuestBins + 1); }
+
+template <int NT, int PER>
+static void prep_pass(hipStream_t s, int phase, const Geometry& g, const float* x, const float* y, const float* t_rel,
+                      const signed char* pol, const long long* offsets, const WinParam* wp, int B,
+                      const int* blk_start, int nblk, int* cnt, long long* seg_off, unsigned long long* cursor,
+                      float4* ev, int* err_flag, long long cap) {
+    if (phase == 0)
+        k_prep_count<NT, PER><<<nblk, NT, sizeof(int) * g.T * kTC, s>>>(g, x, y, t_rel, pol, offsets, wp, B, blk_start,
+                                                                        cnt, err_flag);
+    else
+        k_prep_scatter<NT, PER><<<nblk, NT, (sizeof(unsigned long long) + sizeof(int)) * g.T * kTC, s>>>(
+            g, x, y, t_rel, pol, offsets, wp, B, blk_start, cursor,
+            cap >= 0 ? seg_off + (long long)B * g.T : nullptr, cap, ev);
+}
 
 hipError_t launch_prep(hipStream_t s, int phase, const Geometry& g, const float* x, const float* y,
                        const float* t_rel, const signed char* pol, const long long* offsets, const WinParam* wp, int B,
                        const int* blk_start, int nblk, int chunk, int* cnt, long long* seg_off, int* seg_own,
                        unsigned long long* cursor, float4* ev, int* err_flag, long long cap) {
-    if (phase == 0) {
-        if (nblk > 0) {
-            k_prep_count<<<nblk, kPrepThreads, sizeof(int) * g.T * kTC, s>>>(g, x, y, t_rel, pol, offsets, wp, B,
-                                                                             blk_start, chunk, cnt, err_flag);
-            hipError_t e = hipGetLastError();
-            if (e != hipSuccess) return e;
-        }
-        k_prep_scan<<<1, 1024, 0, s>>>(B, g.T, cnt, seg_off, seg_own, cursor);
-        return hipGetLastError();
-    }
     if (nblk > 0) {
-        k_prep_scatter<<<nblk, kPrepThreads, (sizeof(unsigned long long) + sizeof(int)) * g.T * kTC, s>>>(
-            g, x, y, t_rel, pol, offsets, wp, B, blk_start, chunk, cursor,
-            cap >= 0 ? seg_off + (long long)B * g.T : nullptr, cap, ev);
+        if (chunk == kPrepSome * kPrepPer)
+            prep_pass<kPrepSome, kPrepPer>(s, phase, g, x, y, t_rel, pol, offsets, wp, B, blk_start, nblk, cnt, seg_off, cursor, ev,
+                              err_flag, cap);
+        else
+            prep_pass<kPrepMany, kPrepPer>(s, phase, g, x, y, t_rel, pol, offsets, wp, B, blk_start, nblk, cnt, seg_off,
+                                      cursor, ev, err_flag, cap);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    if (phase == 0) {
+        k_prep_scan<<<1, 1024, 0, s>>>(B, g.T, cnt, seg_off, seg_own, cursor);
         return hipGetLastError();
     }
     return hipSuccess;
