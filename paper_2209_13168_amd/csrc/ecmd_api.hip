@@ -90,7 +90,8 @@ struct ecmd_ctx {
     size_t nodes_lds = 0;  // LDS bytes and workgroups of the node groups' kernel on the same tiles
     int nodes_nb = 0;      // (0: its sums do not fit beside the counters)
     // staging of host inputs
-    DevBuf sx, sy, st, soff, stau, sseed, spol;
+    DevBuf sx, sy, st, soff, sseed, spol;
+    DevBuf head;  // small inputs of a synchronous call (Head)
     // prep
     DevBuf wp, blk, cnt_own, cnt_guest, seg_off, seg_own, cursor, ev, err_flag;
     // search
@@ -237,58 +238,58 @@ static int grid_depth(float d_lo, float d_hi, float eps) {
 // the one-cell border, fit the budget max_px.
 // npol = 1, or 2 for the polarity-aware contrast (one tiled image per
 // polarity); segments = tiles x npol stay within kMaxTiles.
+// Runs on every call: widths are worked out, cuts are only made for the plan
+// taken (making them for each of the 1024 splits tried took 150 us).
 static bool plan_geometry(int W, int H, float cx, float cy, int max_px, int npol, Geometry& g) {
     memset(&g, 0, sizeof g);
     g.W = W;
     g.H = H;
     g.cx = cx;
     g.cy = cy;
-    std::vector<int> bx = {0}, by = {0};
-    if (cx == floorf(cx) && cx > 0.0f && cx < (float)W) bx.push_back((int)cx);
-    if (cy == floorf(cy) && cy > 0.0f && cy < (float)H) by.push_back((int)cy);
-    bx.push_back(W);
-    by.push_back(H);
-    auto split = [](const std::vector<int>& base, int k) {
-        std::vector<int> cut;
-        for (size_t b = 0; b + 1 < base.size(); ++b) {
-            int a = base[b], e = base[b + 1];
-            for (int i = 0; i < k; ++i) cut.push_back(a + (int)((long long)(e - a) * i / k));
-        }
-        cut.push_back(base.back());
-        return cut;
-    };
-    auto max_band = [](const std::vector<int>& cut) {
+    int bx[3] = {0}, by[3] = {0}, nbx = 0, nby = 0;  // the bands between the FOE lines
+    if (cx == floorf(cx) && cx > 0.0f && cx < (float)W) bx[++nbx] = (int)cx;
+    if (cy == floorf(cy) && cy > 0.0f && cy < (float)H) by[++nby] = (int)cy;
+    bx[++nbx] = W;
+    by[++nby] = H;
+    // the widest part when every band is cut into k even ones
+    auto widest = [](const int* base, int nb, int k) {
         int m = 0;
-        for (size_t i = 0; i + 1 < cut.size(); ++i) m = std::max(m, cut[i + 1] - cut[i]);
+        for (int b = 0; b < nb; ++b) m = std::max(m, (base[b + 1] - base[b] + k - 1) / k);
         return m;
     };
-    int best = -1;
-    std::vector<int> bc, br;
+    int best = -1, bkx = 0, bky = 0;
     for (int kx = 1; kx <= 32; ++kx) {
+        const int mx = widest(bx, nbx, kx);
         for (int ky = 1; ky <= 32; ++ky) {
-            std::vector<int> c = split(bx, kx), r = split(by, ky);
-            int ntx = (int)c.size() - 1, nty = (int)r.size() - 1;
-            if (ntx * nty * npol > kMaxTiles) continue;
+            const int n = nbx * kx * nby * ky;
+            if (n * npol > kMaxTiles) break;
+            const int my = widest(by, nby, ky);
             // counters of the largest tile, with its one-cell border
-            if ((long long)(max_band(c) + 2) * (max_band(r) + 2) > max_px) continue;
+            if ((long long)(mx + 2) * (my + 2) > max_px) continue;
             // fewest tiles, then the squarest
-            int score = ntx * nty * 1000 + std::abs(max_band(c) - max_band(r)) % 1000;
+            const int score = n * 1000 + std::abs(mx - my) % 1000;
             if (best < 0 || score < best) {
                 best = score;
-                bc = c;
-                br = r;
+                bkx = kx;
+                bky = ky;
             }
         }
     }
     if (best < 0) return false;
-    g.ntx = (int)bc.size() - 1;
-    g.nty = (int)br.size() - 1;
+    auto split = [](const int* base, int nb, int k, int* cut) {
+        int n = 0;
+        for (int b = 0; b < nb; ++b)
+            for (int i = 0; i < k; ++i) cut[n++] = base[b] + (int)((long long)(base[b + 1] - base[b]) * i / k);
+        cut[n] = base[nb];
+        return n;
+    };
+    g.ntx = split(bx, nbx, bkx, g.colcut);
+    g.nty = split(by, nby, bky, g.rowcut);
     g.nsp = g.ntx * g.nty;
     g.T = g.nsp * npol;
-    for (int i = 0; i <= g.ntx; ++i) g.colcut[i] = bc[i];
-    for (int i = 0; i <= g.nty; ++i) g.rowcut[i] = br[i];
-    g.max_tile_px = max_band(bc) * max_band(br);
-    g.ring_px = (max_band(bc) + 2) * (max_band(br) + 2);
+    const int mx = widest(bx, nbx, bkx), my = widest(by, nby, bky);
+    g.max_tile_px = mx * my;
+    g.ring_px = (mx + 2) * (my + 2);
     return true;
 }
 
@@ -319,8 +320,33 @@ static int check_search(ecmd_ctx* c, const ecmd_search* s, int* L) {
 struct Inputs {
     const float *x = nullptr, *y = nullptr, *t = nullptr, *seeds = nullptr, *tau = nullptr;
     const long long* off = nullptr;
+    const int* blk = nullptr;  // first prep workgroup of every window (set by run_prep)
     const signed char* pol = nullptr;  // polarities (device), or NULL: one event image
+    const float* hseeds = nullptr;     // seeds in host memory (then `seeds` is set by run_prep)
 };
+
+// Small inputs of a synchronous call of B windows as they lie in the pinned
+// staging and in c->head: offsets, window lengths, seeds and first prep
+// workgroups.  The pinned buffer begins with the reports and ends with the
+// windows' states.
+struct Head {
+    size_t off, tau, seed, blk, bytes;
+    explicit Head(int B) {
+        off = 0;
+        tau = off + 8 * ((size_t)B + 1);
+        seed = tau + 4 * (size_t)B;
+        blk = seed + 4 * (size_t)B;
+        bytes = (blk + 4 * ((size_t)B + 1) + 15) / 16 * 16;
+    }
+};
+
+constexpr size_t kStaged = 64;  // bytes of the reports: one per poll slot, the prep's
+static Report* report(ecmd_ctx* c, int k) { return c->pinned.as<Report>() + k; }
+static char* staged(ecmd_ctx* c) { return c->pinned.as<char>() + kStaged; }
+static WinState* states(ecmd_ctx* c, int B) { return (WinState*)(staged(c) + Head(B).bytes); }
+static hipError_t pin(ecmd_ctx* c, int B) {
+    return c->pinned.ensure(kStaged + Head(B).bytes + sizeof(WinState) * B);
+}
 
 static int stage(ecmd_ctx* c, DevBuf& buf, const void* src, size_t bytes, uint32_t flags,
                  const void** out) {
@@ -341,58 +367,64 @@ static double key_to_double(long long hi, unsigned long long lo) {
 
 // --------------------------------------------------------------- pipeline
 
-// Prep of B windows: window params, event binning.  Needs h_off (host copy
-// of the offsets) and h_tau.  rebin: keep the window params already on the
-// device (binning ranges narrowed to the live search).  copies_out: event
-// records written, guest copies included.
-static int run_prep(ecmd_ctx* c, const Geometry& g, const Inputs& in, int B, float d_lo, float d_hi,
+// Prep of B windows: window params, event binning.  Needs the host copies
+// h_off and h_tau of offsets and window lengths; where `in` has no device
+// pointers of those (or of the seeds), they are staged from the host's.  With
+// `clear` the search's counters are cleared too.  copies_out: event records
+// written, guest copies included.  (The wait for their number costs little:
+// room for every copy that 10k events could have, and the checks read after
+// the first rounds are enqueued, took 510 us a search instead of 517, and a
+// contrast curve of 100k events 145 instead of 139.)
+static int run_prep(ecmd_ctx* c, const Geometry& g, Inputs& in, int B, float d_lo, float d_hi, bool clear,
                     int* nblk_out, long long* copies_out = nullptr) {
     const int T = g.T;
+    const Head hd(B);
     const int chunk = prep_chunk(c->h_off[B] - c->h_off[0]);
-    std::vector<int> blk(B + 1, 0);
+    HIPCHK(c, pin(c, B));
+    HIPCHK(c, c->head.ensure(hd.bytes));
+    char *const stg = staged(c), *const dev = c->head.as<char>();
+    int* const blk = (int*)(stg + hd.blk);
+    blk[0] = 0;
     for (int w = 0; w < B; ++w) {
         long long n = c->h_off[w + 1] - c->h_off[w];
         blk[w + 1] = blk[w] + (int)((n + chunk - 1) / chunk);
     }
     const int nblk = blk[B];
+    memcpy(stg + hd.off, c->h_off.data(), 8 * ((size_t)B + 1));
+    memcpy(stg + hd.tau, c->h_tau.data(), 4 * (size_t)B);
+    if (in.hseeds) memcpy(stg + hd.seed, in.hseeds, 4 * (size_t)B);
+    if (!in.off) in.off = (const long long*)(dev + hd.off);
+    if (!in.tau) in.tau = (const float*)(dev + hd.tau);
+    if (in.hseeds) in.seeds = (const float*)(dev + hd.seed);
+    in.blk = (const int*)(dev + hd.blk);
     HIPCHK(c, c->wp.ensure(sizeof(WinParam) * std::max(B, 1)));
-    HIPCHK(c, c->blk.ensure(sizeof(int) * (B + 1)));
-    // staging of blk (B + 1 ints) and, later, of the total and B error flags
-    HIPCHK(c, c->pinned.ensure(sizeof(int) * B + 72));
-    memcpy(c->pinned.p, blk.data(), sizeof(int) * (B + 1));
-    HIPCHK(c, hipMemcpyAsync(c->blk.p, c->pinned.p, sizeof(int) * (B + 1), hipMemcpyHostToDevice, c->stream));
     const size_t nctr = prep_counters(B, T);
     HIPCHK(c, c->cnt_own.ensure(sizeof(int) * nctr));
     HIPCHK(c, c->seg_off.ensure(sizeof(long long) * (B * T + 1)));
     HIPCHK(c, c->seg_own.ensure(sizeof(int) * seg_own_words(B, T)));
     HIPCHK(c, c->cursor.ensure(sizeof(unsigned long long) * nctr));
     HIPCHK(c, c->err_flag.ensure(sizeof(int) * B));
-    HIPCHK(c, hipMemsetAsync(c->cnt_own.p, 0, sizeof(int) * nctr, c->stream));
-    HIPCHK(c, hipMemsetAsync(c->err_flag.p, 0, sizeof(int) * B, c->stream));
+    HIPCHK(c, launch_begin(c->stream, (const unsigned*)stg, c->head.as<unsigned>(), (int)(hd.bytes / 4),
+                           c->cnt_own.as<int>(), (long long)nctr, c->err_flag.as<int>(), B,
+                           clear ? c->queues.as<Queue>() : nullptr, clear ? c->n_active.as<int>() : nullptr));
     HIPCHK(c, launch_winparam(c->stream, g, in.tau, in.off, B, d_lo, d_hi, c->wp.as<WinParam>()));
-    // count + scan (scatter needs the total to size the event store)
-    HIPCHK(c, launch_prep(c->stream, 0, g, in.x, in.y, in.t, in.pol, in.off, c->wp.as<WinParam>(), B, c->blk.as<int>(),
+    HIPCHK(c, launch_prep(c->stream, 0, g, in.x, in.y, in.t, in.pol, in.off, c->wp.as<WinParam>(), B, in.blk,
                           nblk, chunk, c->cnt_own.as<int>(), c->seg_off.as<long long>(), c->seg_own.as<int>(),
                           c->cursor.as<unsigned long long>(), nullptr, c->err_flag.as<int>(), -1));
-    HIPCHK(c, hipMemcpyAsync(c->pinned.p, c->seg_off.as<long long>() + (size_t)B * T, sizeof(long long),
-                             hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(c, hipMemcpyAsync((char*)c->pinned.p + 8, c->err_flag.p, sizeof(int) * B, hipMemcpyDeviceToHost,
-                             c->stream));
+    const long long* const records = c->seg_off.as<long long>() + (size_t)B * T;
+    HIPCHK(c, launch_report(c->stream, B, records, nullptr, c->err_flag.as<int>(), nullptr, 0, report(c, 2), nullptr));
     HIPCHK(c, hipStreamSynchronize(c->stream));
-    const long long total = *(long long*)c->pinned.p;
-    const int* errf = (const int*)((char*)c->pinned.p + 8);
-    for (int w = 0; w < B; ++w)
-        if (errf[w])
-            return fail(c, ECMD_EINVAL, "window %d: an event has a non-finite coordinate or t_rel outside [0, tau]",
-                        w);
+    const Report& r = *report(c, 2);
+    if (r.bad < B)
+        return fail(c, ECMD_EINVAL, "window %d: an event has a non-finite coordinate or t_rel outside [0, tau]", r.bad);
     // padding: the evaluation kernel prefetches up to kEvalPad records past
     // the end of a segment
-    HIPCHK(c, c->ev.ensure(sizeof(float4) * (size_t)(total + kEvalPad)));
-    HIPCHK(c, launch_prep(c->stream, 1, g, in.x, in.y, in.t, in.pol, in.off, c->wp.as<WinParam>(), B, c->blk.as<int>(),
-                          nblk, chunk, nullptr, nullptr, nullptr, c->cursor.as<unsigned long long>(),
-                          c->ev.as<float4>(), nullptr, -1));
+    HIPCHK(c, c->ev.ensure(sizeof(float4) * (size_t)(r.records + kEvalPad)));
+    HIPCHK(c, launch_prep(c->stream, 1, g, in.x, in.y, in.t, in.pol, in.off, c->wp.as<WinParam>(), B, in.blk, nblk,
+                          chunk, nullptr, nullptr, nullptr, c->cursor.as<unsigned long long>(), c->ev.as<float4>(),
+                          nullptr, -1));
     *nblk_out = nblk;
-    if (copies_out) *copies_out = total;
+    if (copies_out) *copies_out = r.records;
     return ECMD_OK;
 }
 
@@ -407,12 +439,12 @@ static hipError_t enqueue_rebin(ecmd_ctx* c, const Geometry& g, const Inputs& in
     const int chunk = prep_chunk(c->h_off[B] - c->h_off[0]);
     hipError_t e = hipMemsetAsync(c->cnt_own.p, 0, sizeof(int) * nctr, c->stream);
     if (e != hipSuccess) return e;
-    e = launch_prep(c->stream, 0, g, in.x, in.y, in.t, in.pol, in.off, c->wp.as<WinParam>(), B, c->blk.as<int>(), nblk,
+    e = launch_prep(c->stream, 0, g, in.x, in.y, in.t, in.pol, in.off, c->wp.as<WinParam>(), B, in.blk, nblk,
                     chunk, c->cnt_own.as<int>(), c->seg_off.as<long long>(), c->seg_own.as<int>(),
                     c->cursor.as<unsigned long long>(), nullptr, c->err_flag.as<int>(), -1);
     if (e != hipSuccess) return e;
     const long long cap = (long long)(c->ev.cap / sizeof(float4)) - kEvalPad;
-    return launch_prep(c->stream, 1, g, in.x, in.y, in.t, in.pol, in.off, c->wp.as<WinParam>(), B, c->blk.as<int>(),
+    return launch_prep(c->stream, 1, g, in.x, in.y, in.t, in.pol, in.off, c->wp.as<WinParam>(), B, in.blk,
                        nblk, chunk, nullptr, c->seg_off.as<long long>(), nullptr, c->cursor.as<unsigned long long>(),
                        c->ev.as<float4>(), nullptr, cap);
 }
@@ -525,7 +557,7 @@ static void set_nodes(Search& sp, int B, int T, int nb, int nt, int mcap) {
 }
 
 // Whole batched search on staged inputs; fills out[0..B).
-static int run_search(ecmd_ctx* c, const ecmd_sensor* sensor, const Inputs& in, int B,
+static int run_search(ecmd_ctx* c, const ecmd_sensor* sensor, Inputs& in, int B,
                       const ecmd_search* search, int L, ecmd_result* out) {
     const int W = sensor->width, H = sensor->height;
     const int npol = in.pol ? 2 : 1;
@@ -535,10 +567,12 @@ static int run_search(ecmd_ctx* c, const ecmd_sensor* sensor, const Inputs& in, 
     if (!choose_tiling(c->max_lds, c->tune, W, H, sensor->foe_x, sensor->foe_y, npol, g, nt, budget))
         return fail(c, ECMD_EINVAL, "sensor %dx%d needs more than %d tiles", W, H, kMaxTiles / npol);
     Timers tm(c);
+    HIPCHK(c, c->queues.ensure(sizeof(Queue) * kQueues));
+    HIPCHK(c, c->n_active.ensure(sizeof(int)));
     int nblk = 0;
     long long copies = 0;
     tm.begin();
-    int rc = run_prep(c, g, in, B, search->d_lo, search->d_hi, &nblk, &copies);
+    int rc = run_prep(c, g, in, B, search->d_lo, search->d_hi, true, &nblk, &copies);
     if (rc) return rc;
     tm.end(2);
     tm.cut();
@@ -572,11 +606,7 @@ static int run_search(ecmd_ctx* c, const ecmd_sensor* sensor, const Inputs& in, 
     HIPCHK(c, c->act.ensure(sizeof(int) * (size_t)B * sp.HS));
     const int qcap = ((B + kXcd - 1) / kXcd) * sp.HS * T;  // windows w = r (mod kXcd) share queue r
     HIPCHK(c, c->items.ensure(sizeof(Item) * (size_t)kXcd * qcap));
-    HIPCHK(c, c->queues.ensure(sizeof(Queue) * kQueues));
     HIPCHK(c, c->part.ensure(sizeof(Part) * (size_t)B * sp.HS * T));
-    HIPCHK(c, c->n_active.ensure(sizeof(int)));
-    HIPCHK(c, hipMemsetAsync(c->queues.p, 0, sizeof(Queue) * kQueues, c->stream));
-    HIPCHK(c, hipMemsetAsync(c->n_active.p, 0, sizeof(int), c->stream));
     Queue* q = c->queues.as<Queue>();
     HIPCHK(c, launch_init(c->stream, sp, c->wp.as<WinParam>(), in.seeds, B, c->state.as<WinState>(),
                           c->sel.as<Sel>(), c->hyps.as<Hyp>(), c->act.as<int>(), c->items.as<Item>(), qcap, &q[0],
@@ -640,30 +670,27 @@ static int run_search(ecmd_ctx* c, const ecmd_sensor* sensor, const Inputs& in, 
             c->gkey = key;
         }
     }
-    // Blocks of four rounds.  After each block the host copies the count of
-    // finished windows (and the event records) to pinned memory, but waits
-    // for block b's copy only once block b + 1 is enqueued, so the device
-    // never idles on the host; the block after the last is empty work.
-    HIPCHK(c, c->pinned.ensure(64));
-    char* const poll = (char*)c->pinned.p;  // two slots: [n_active int][pad][records int64]
+    // Blocks of two rounds, each with a report (the finished windows and the
+    // event records) written to pinned memory.  The host waits for block b's
+    // report only once block b + 1 is enqueued, so the device never idles on
+    // the host; the block after the last is empty work.  (Blocks of four with
+    // copies for the counts, the states and the small inputs, and the tiling
+    // planned slowly: 732 us for one 128 x 128 window, 510 with this.)
+    const long long* const records = c->seg_off.as<long long>() + (size_t)B * T;
+    WinState* const hs = states(c, B);
     hipEvent_t pev[2] = {pool_event(c), pool_event(c)};
     if (!pev[0] || !pev[1]) return fail(c, ECMD_EDEVICE, "hipEventCreate failed");
     auto enqueue_block = [&](int b) -> hipError_t {
         hipError_t e;
-        for (int k = 0; k < 4; ++k) {
-            if (graph) {  // two rounds a launch
-                if (k % 2 == 0 && (e = hipGraphLaunch(c->gexec, c->stream)) != hipSuccess) return e;
-            } else if ((e = run_round(k, true)) != hipSuccess) {
-                return e;
-            }
+        if (graph) {
+            if ((e = hipGraphLaunch(c->gexec, c->stream)) != hipSuccess) return e;
+        } else {
+            if ((e = run_round(0, true)) != hipSuccess || (e = run_round(1, true)) != hipSuccess) return e;
+            tm.cut();
         }
-        if (!graph) tm.cut();
-        char* slot = poll + 16 * (b & 1);
-        if ((e = hipMemcpyAsync(slot, c->n_active.p, sizeof(int), hipMemcpyDeviceToHost, c->stream)) != hipSuccess)
-            return e;
-        if ((e = hipMemcpyAsync(slot + 8, c->seg_off.as<long long>() + (size_t)B * T, sizeof(long long),
-                                hipMemcpyDeviceToHost, c->stream)) != hipSuccess)
-            return e;
+        e = launch_report(c->stream, B, records, c->n_active.as<int>(), nullptr, c->state.as<WinState>(), 0,
+                          report(c, b & 1), hs);
+        if (e != hipSuccess) return e;
         return hipEventRecord(pev[b & 1], c->stream);
     };
     int blocks = 0;
@@ -671,10 +698,10 @@ static int run_search(ecmd_ctx* c, const ecmd_sensor* sensor, const Inputs& in, 
     for (;;) {
         // Events copied to several tiles (guests) are binned by the whole
         // search range; once the frontier has narrowed, bin again with each
-        // window's live range (after blocks 1 .. kMaxRebins, while the last
-        // binning known here copied more than 1% of the events) to drop
-        // copies no longer needed.
-        if (rebins < kMaxRebins && copies > n_events + n_events / 100) {
+        // window's live range (after 4 * k rounds, k = 1 .. kMaxRebins, while
+        // the last binning known here copied more than 1% of the events) to
+        // drop copies no longer needed.
+        if (blocks % 2 == 0 && rebins < kMaxRebins && copies > n_events + n_events / 100) {
             tm.begin();
             HIPCHK(c, launch_live_range(c->stream, sp, c->state.as<WinState>(), c->front.as<Node>(),
                                         c->sel.as<Sel>(), c->wp.as<WinParam>(), B));
@@ -683,22 +710,20 @@ static int run_search(ecmd_ctx* c, const ecmd_sensor* sensor, const Inputs& in, 
             tm.cut();
             ++rebins;
         }
-        const bool more = blocks * 4 < 2 * kMaxSteps;  // a step takes two rounds at most
+        const bool more = blocks < kMaxSteps;  // a step takes two rounds, a block, at most
         if (more) HIPCHK(c, enqueue_block(blocks++));
-        const int done = more ? blocks - 2 : blocks - 1;  // the block whose copy is awaited
+        const int done = more ? blocks - 2 : blocks - 1;  // the block whose report is awaited
         HIPCHK(c, hipEventSynchronize(pev[done & 1]));
-        const char* slot = poll + 16 * (done & 1);
-        active = B + *(const int*)slot;  // n_active counts finished windows down from zero
-        copies = *(const long long*)(slot + 8);
+        active = B + report(c, done & 1)->finished;  // finished windows count down from zero
+        copies = report(c, done & 1)->records;
         if (active == 0 || !more) break;
     }
-    std::vector<WinState> hs(B);
-    HIPCHK(c, hipMemcpyAsync(hs.data(), c->state.p, sizeof(WinState) * B, hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(c, hipMemcpyAsync(poll, c->seg_off.as<long long>() + (size_t)B * T, sizeof(long long),
-                             hipMemcpyDeviceToHost, c->stream));
+    if (active != 0)
+        HIPCHK(c, launch_report(c->stream, B, records, c->n_active.as<int>(), nullptr, c->state.as<WinState>(), 1,
+                                report(c, (blocks - 1) & 1), hs));
     HIPCHK(c, hipStreamSynchronize(c->stream));
     tm.collect();
-    if (*(const long long*)poll > (long long)(c->ev.cap / sizeof(float4)) - kEvalPad)
+    if (report(c, (blocks - 1) & 1)->records > (long long)(c->ev.cap / sizeof(float4)) - kEvalPad)
         return fail(c, ECMD_EDEVICE, "re-binned events exceed the event store");
     int first_status = ECMD_OK;
     for (int w = 0; w < B; ++w) {
@@ -752,10 +777,13 @@ static int batched_impl(ecmd_ctx* c, const ecmd_sensor* sensor, const float* x, 
     c->h_off.assign(B + 1, 0);
     c->h_tau.assign(B, 0.0f);
     if (flags & ECMD_DEVICE_PTR) {
-        HIPCHK(c, hipMemcpyAsync(c->h_off.data(), offsets, sizeof(long long) * (B + 1), hipMemcpyDeviceToHost,
-                                 c->stream));
-        HIPCHK(c, hipMemcpyAsync(c->h_tau.data(), tau, sizeof(float) * B, hipMemcpyDeviceToHost, c->stream));
+        const Head hd(B);
+        HIPCHK(c, pin(c, B));
+        HIPCHK(c, launch_fetch(c->stream, (const unsigned*)offsets, (unsigned*)(staged(c) + hd.off), 2 * (B + 1),
+                               (const unsigned*)tau, (unsigned*)(staged(c) + hd.tau), B));
         HIPCHK(c, hipStreamSynchronize(c->stream));
+        memcpy(c->h_off.data(), staged(c) + hd.off, sizeof(long long) * (B + 1));
+        memcpy(c->h_tau.data(), staged(c) + hd.tau, sizeof(float) * B);
     } else {
         memcpy(c->h_off.data(), offsets, sizeof(long long) * (B + 1));
         memcpy(c->h_tau.data(), tau, sizeof(float) * B);
@@ -782,17 +810,16 @@ static int batched_impl(ecmd_ctx* c, const ecmd_sensor* sensor, const float* x, 
     in.y = (const float*)p;
     if ((rc = stage(c, c->st, t_rel, sizeof(float) * n_total, flags, &p))) return rc;
     in.t = (const float*)p;
-    if ((rc = stage(c, c->soff, offsets, sizeof(long long) * (B + 1), flags, &p))) return rc;
-    in.off = (const long long*)p;
-    if ((rc = stage(c, c->stau, tau, sizeof(float) * B, flags, &p))) return rc;
-    in.tau = (const float*)p;
+    if (flags & ECMD_DEVICE_PTR) {
+        in.off = (const long long*)offsets;
+        in.tau = tau;
+        in.seeds = d_seeds;
+    } else {
+        in.hseeds = d_seeds;
+    }
     if (pol) {
         if ((rc = stage(c, c->spol, pol, (size_t)n_total, flags, &p))) return rc;
         in.pol = (const signed char*)p;
-    }
-    if (d_seeds) {
-        if ((rc = stage(c, c->sseed, d_seeds, sizeof(float) * B, flags, &p))) return rc;
-        in.seeds = (const float*)p;
     }
     return run_search(c, sensor, in, B, search, L, out);
 }
@@ -1072,7 +1099,7 @@ void ecmd_ctx_destroy(ecmd_ctx* c) {
     if (!c) return;
     (void)hipSetDevice(c->device);
     (void)hipStreamSynchronize(c->stream);
-    DevBuf* bufs[] = {&c->sx, &c->sy, &c->st, &c->soff, &c->stau, &c->sseed, &c->spol, &c->wp, &c->blk, &c->cnt_own,
+    DevBuf* bufs[] = {&c->sx, &c->sy, &c->st, &c->soff, &c->sseed, &c->spol, &c->head, &c->wp, &c->blk, &c->cnt_own,
                       &c->cnt_guest, &c->seg_off, &c->seg_own, &c->cursor, &c->ev, &c->err_flag, &c->state,
                       &c->front, &c->sel, &c->hyps, &c->act, &c->items, &c->queues, &c->part, &c->n_active, &c->lists, &c->pix,
                       &c->img, &c->keep, &c->counts, &c->misc};
@@ -1474,15 +1501,7 @@ int ecmd_estimate_divergence(ecmd_ctx* c, const ecmd_sensor* sensor, const ecmd_
         in.y = dy;
         in.t = dt;
         if (has_pol) in.pol = c->spol.as<signed char>();
-        const void* p;
-        if ((rc = stage(c, c->soff, off, sizeof off, 0, &p))) return rc;
-        in.off = (const long long*)p;
-        if ((rc = stage(c, c->stau, &tau, sizeof tau, 0, &p))) return rc;
-        in.tau = (const float*)p;
-        if (d_seed) {
-            if ((rc = stage(c, c->sseed, &seed, sizeof seed, 0, &p))) return rc;
-            in.seeds = (const float*)p;
-        }
+        if (d_seed) in.hseeds = &seed;
         rc = run_search(c, sensor, in, 1, search, L, out);
     }
     return rc;
@@ -1548,15 +1567,10 @@ static int probe_impl(ecmd_ctx* c, const ecmd_sensor* sensor, const float* x, co
         if ((rc = stage(c, c->spol, pol, (size_t)n, flags, &p))) return rc;
         in.pol = (const signed char*)p;
     }
-    long long off[2] = {0, n};
-    if ((rc = stage(c, c->soff, off, sizeof off, 0, &p))) return rc;
-    in.off = (const long long*)p;
-    if ((rc = stage(c, c->stau, &tau, sizeof tau, 0, &p))) return rc;
-    in.tau = (const float*)p;
-    c->h_off.assign(off, off + 2);
+    c->h_off = {0, n};
     c->h_tau.assign(1, tau);
     int nblk = 0;
-    rc = run_prep(c, g, in, 1, d_lo, d_hi, &nblk);
+    rc = run_prep(c, g, in, 1, d_lo, d_hi, false, &nblk);
     if (rc) return rc;
     const void *pa, *pb = nullptr;
     if ((rc = stage(c, c->sseed, d_a, sizeof(float) * m, flags, &pa))) return rc;
@@ -1564,23 +1578,13 @@ static int probe_impl(ecmd_ctx* c, const ecmd_sensor* sensor, const float* x, co
         if ((rc = stage(c, c->misc, d_b, sizeof(float) * m, flags, &pb))) return rc;
     }
     HIPCHK(c, c->hyps.ensure(sizeof(Hyp) * m));
-    HIPCHK(c, launch_rates(c->stream, (const float*)pa, (const float*)pb, m, tau, c->hyps.as<Hyp>()));
-    // every hypothesis on every tile
-    std::vector<Item> items((size_t)m * T);
-    for (int h = 0; h < m; ++h)
-        for (int t = 0; t < T; ++t) items[(size_t)h * T + t] = Item{0, t, h, 1};
-    HIPCHK(c, c->items.ensure(sizeof(Item) * items.size()));
-    std::vector<int> ident(m);
-    for (int h = 0; h < m; ++h) ident[h] = h;
+    const size_t n_items = (size_t)m * T;  // every hypothesis on every tile
     HIPCHK(c, c->act.ensure(sizeof(int) * m));
-    HIPCHK(c, hipMemcpyAsync(c->act.p, ident.data(), sizeof(int) * m, hipMemcpyHostToDevice, c->stream));
-    HIPCHK(c, hipMemcpyAsync(c->items.p, items.data(), sizeof(Item) * items.size(), hipMemcpyHostToDevice,
-                             c->stream));
-    Queue hq[2 * kXcd] = {};
-    hq[0].n_items = (int)items.size();  // everything in queue 0; the other XCDs steal
-    HIPCHK(c, c->queues.ensure(sizeof hq));
-    HIPCHK(c, hipMemcpyAsync(c->queues.p, hq, sizeof hq, hipMemcpyHostToDevice, c->stream));
-    HIPCHK(c, c->part.ensure(sizeof(Part) * items.size()));
+    HIPCHK(c, c->items.ensure(sizeof(Item) * n_items));
+    HIPCHK(c, c->queues.ensure(sizeof(Queue) * kQueues));
+    HIPCHK(c, c->part.ensure(sizeof(Part) * n_items));
+    HIPCHK(c, launch_probe_items(c->stream, (const float*)pa, (const float*)pb, m, tau, T, c->hyps.as<Hyp>(),
+                                 c->act.as<int>(), c->items.as<Item>(), c->queues.as<Queue>()));
     unsigned* dimg = nullptr;
     if (img_out) {
         if (flags & ECMD_DEVICE_PTR) {
@@ -1596,33 +1600,23 @@ static int probe_impl(ecmd_ctx* c, const ecmd_sensor* sensor, const float* x, co
     Queue* q = c->queues.as<Queue>();
     HIPCHK(c, launch_eval(c->stream, g, nb, nt, lds, c->ev.as<float4>(), c->seg_off.as<long long>(),
                           c->seg_own.as<int>(), c->wp.as<WinParam>(), c->hyps.as<Hyp>(), c->act.as<int>(),
-                          c->items.as<Item>(), (int)items.size(), &q[0], &q[kXcd], c->part.as<Part>(), m, dimg));
-    std::vector<Part> parts(items.size());
-    std::vector<long long> seg(T + 1);
-    HIPCHK(c, hipMemcpyAsync(parts.data(), c->part.p, sizeof(Part) * parts.size(), hipMemcpyDeviceToHost,
-                             c->stream));
-    HIPCHK(c, hipMemcpyAsync(seg.data(), c->seg_off.p, sizeof(long long) * (T + 1), hipMemcpyDeviceToHost,
-                             c->stream));
-    if (img_out && !(flags & ECMD_DEVICE_PTR))
-        HIPCHK(c, hipMemcpyAsync(img_out, dimg, sizeof(unsigned) * (size_t)m * M, hipMemcpyDeviceToHost, c->stream));
+                          c->items.as<Item>(), (int)n_items, &q[0], &q[kXcd], c->part.as<Part>(), m, dimg));
+    unsigned long long* dS = (unsigned long long*)S;
+    long long* dN = (long long*)N;
+    if (!(flags & ECMD_DEVICE_PTR)) {
+        HIPCHK(c, c->counts.ensure(16 * (size_t)m));
+        dS = c->counts.as<unsigned long long>();
+        dN = (long long*)dS + m;
+    }
+    HIPCHK(c, launch_probe_sums(c->stream, m, T, c->seg_off.as<long long>(), c->part.as<Part>(), dS, dN));
+    if (!(flags & ECMD_DEVICE_PTR)) {
+        HIPCHK(c, hipMemcpyAsync(S, dS, sizeof(uint64_t) * m, hipMemcpyDeviceToHost, c->stream));
+        HIPCHK(c, hipMemcpyAsync(N, dN, sizeof(int64_t) * m, hipMemcpyDeviceToHost, c->stream));
+        if (img_out)
+            HIPCHK(c, hipMemcpyAsync(img_out, dimg, sizeof(unsigned) * (size_t)m * M, hipMemcpyDeviceToHost,
+                                     c->stream));
+    }
     HIPCHK(c, hipStreamSynchronize(c->stream));
-    std::vector<uint64_t> hS(m, 0);
-    std::vector<int64_t> hN(m, 0);
-    for (int h = 0; h < m; ++h) {
-        for (int t = 0; t < T; ++t) {
-            if (seg[t + 1] == seg[t]) continue;  // empty tile: not evaluated, contributes 0
-            hS[h] += parts[(size_t)h * T + t].S;
-            hN[h] += parts[(size_t)h * T + t].N;
-        }
-    }
-    if (flags & ECMD_DEVICE_PTR) {
-        HIPCHK(c, hipMemcpyAsync(S, hS.data(), sizeof(uint64_t) * m, hipMemcpyHostToDevice, c->stream));
-        HIPCHK(c, hipMemcpyAsync(N, hN.data(), sizeof(int64_t) * m, hipMemcpyHostToDevice, c->stream));
-        HIPCHK(c, hipStreamSynchronize(c->stream));
-    } else {
-        memcpy(S, hS.data(), sizeof(uint64_t) * m);
-        memcpy(N, hN.data(), sizeof(int64_t) * m);
-    }
     return ECMD_OK;
 }
 
@@ -1913,11 +1907,6 @@ int ecmd_estimate_stream(ecmd_ctx* c, const ecmd_sensor* sensor, const ecmd_even
     in.y = dy;
     in.t = trel;
     in.pol = dp;
-    const void* p;
-    if ((rc = stage(c, c->soff, rel.data(), sizeof(long long) * (K + 1), 0, &p))) return rc;
-    in.off = (const long long*)p;
-    if ((rc = stage(c, c->stau, taus.data(), sizeof(float) * K, 0, &p))) return rc;
-    in.tau = (const float*)p;
     return run_search(c, sensor, in, K, search, L, out);
 }
 

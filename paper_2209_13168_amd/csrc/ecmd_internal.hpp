@@ -183,6 +183,23 @@ hipError_t launch_winparam(hipStream_t s, const Geometry& g, const float* tau, c
                            int B, float d_lo, float d_hi, WinParam* wp);
 // Counters of the prep (per window and tile: owned events by walk class,
 // guests by bin and walk class).
+// Start of a synchronous call: n_head words of staged input (pinned host
+// memory) to the device, and what the call's kernels count in cleared: nctr
+// counters, B flags, kQueues queues and n_active (the last two may be NULL).
+hipError_t launch_begin(hipStream_t s, const unsigned* staged, unsigned* head, int n_head, int* cnt, long long nctr,
+                        int* err_flag, int B, Queue* q, int* n_active);
+// Two device arrays (of words) to pinned host memory.
+hipError_t launch_fetch(hipStream_t s, const unsigned* a, unsigned* ha, int na, const unsigned* b, unsigned* hb, int nb);
+// What a synchronous call waits for, in pinned host memory.
+struct Report {
+    long long records;  // event records, guest copies included
+    int finished;       // minus the finished windows
+    int bad;            // first window with an invalid event, or B
+};
+// Written from the device's counters, `bad` where err_flag is given; with st,
+// the windows' states too once every window has finished (or if `all`).
+hipError_t launch_report(hipStream_t s, int B, const long long* records, const int* n_active, const int* err_flag,
+                         const WinState* st, int all, Report* rep, WinState* hs);
 size_t prep_counters(int B, int T);
 // Events per prep workgroup where a call has up to max_events.
 int prep_chunk(long long max_events);
@@ -234,7 +251,14 @@ hipError_t launch_nodes(hipStream_t s, const Geometry& g, int nblocks, int nt, s
                         float4* lists, int mcap, hipEvent_t t0 = nullptr, hipEvent_t t1 = nullptr);
 size_t nodes_lds_bytes(int ring_px);
 hipError_t nodes_occupancy(int* blocks_per_cu, size_t lds_bytes, int nt);
-hipError_t launch_rates(hipStream_t s, const float* d_a, const float* d_b, int m, float tau, Hyp* hyps);
+// m hypotheses (points if d_b is NULL) of one window, each on all T tiles:
+// their rates, the identity as active list, one item per tile, queue 0 holding
+// them all (the other XCDs steal) and the 2 * kXcd - 1 others empty.
+hipError_t launch_probe_items(hipStream_t s, const float* d_a, const float* d_b, int m, float tau, int T, Hyp* hyps,
+                              int* act, Item* items, Queue* q);
+// Their sums over the tiles with events.
+hipError_t launch_probe_sums(hipStream_t s, int m, int T, const long long* seg_off, const Part* part,
+                             unsigned long long* S, long long* N);
 hipError_t launch_probe_pixels(hipStream_t s, const float* x, const float* y, const float* t_rel,
                                long long n, float tau, float d, int W, int H, float cx, float cy,
                                int* pix);

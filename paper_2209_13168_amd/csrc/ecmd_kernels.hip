@@ -516,6 +516,76 @@ __global__ __launch_bounds__(NT) void k_prep_scatter(
 // Events per prep workgroup.
 int prep_chunk(long long max_events) { return (max_events < kPrepFew ? kPrepSome : kPrepMany) * kPrepPer; }
 
+__global__ void k_begin(const unsigned* __restrict__ staged, unsigned* __restrict__ head, int n_head,
+                        int* __restrict__ cnt, long long nctr, int* __restrict__ err_flag, int B,
+                        Queue* __restrict__ q, int* __restrict__ n_active) {
+    const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n_head) head[i] = staged[i];
+    if (i < nctr) cnt[i] = 0;
+    if (i < B) err_flag[i] = 0;
+    if (q && i < kQueues) {
+        q[i].n_items = 0;
+        q[i].next = 0;
+    }
+    if (n_active && i == 0) *n_active = 0;
+}
+
+hipError_t launch_begin(hipStream_t s, const unsigned* staged, unsigned* head, int n_head, int* cnt, long long nctr,
+                        int* err_flag, int B, Queue* q, int* n_active) {
+    const long long n = std::max(std::max((long long)n_head, nctr), (long long)std::max(B, kQueues));
+    k_begin<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(staged, head, n_head, cnt, nctr, err_flag, B, q, n_active);
+    return hipGetLastError();
+}
+
+__global__ void k_fetch(const unsigned* __restrict__ a, unsigned* __restrict__ ha, int na,
+                        const unsigned* __restrict__ b, unsigned* __restrict__ hb, int nb) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < na) ha[i] = a[i];
+    if (i < nb) hb[i] = b[i];
+}
+
+hipError_t launch_fetch(hipStream_t s, const unsigned* a, unsigned* ha, int na, const unsigned* b, unsigned* hb,
+                        int nb) {
+    k_fetch<<<(std::max(na, nb) + 255) / 256, 256, 0, s>>>(a, ha, na, b, hb, nb);
+    return hipGetLastError();
+}
+
+// 64 windows' states per workgroup
+__global__ __launch_bounds__(256) void k_report(int B, const long long* __restrict__ records,
+                                                const int* __restrict__ n_active, const int* __restrict__ err_flag,
+                                                const WinState* __restrict__ st, int all, Report* __restrict__ rep,
+                                                WinState* __restrict__ hs) {
+    __shared__ int s_bad;
+    const int finished = n_active ? *n_active : 0;
+    if (blockIdx.x == 0) {
+        if (threadIdx.x == 0) s_bad = B;
+        __syncthreads();
+        if (err_flag)
+            for (int w = threadIdx.x; w < B; w += 256)
+                if (err_flag[w]) atomicMin(&s_bad, w);
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            rep->records = *records;
+            rep->finished = finished;
+            rep->bad = s_bad;
+        }
+    }
+    if (st && (all || finished + B == 0)) {
+        static_assert(sizeof(WinState) % 8 == 0, "copied in 8-byte words");
+        constexpr long long words = sizeof(WinState) / 8;
+        const unsigned long long* const src = reinterpret_cast<const unsigned long long*>(st);
+        unsigned long long* const dst = reinterpret_cast<unsigned long long*>(hs);
+        const long long end = min((long long)B, 64ll * (blockIdx.x + 1)) * words;
+        for (long long k = 64ll * blockIdx.x * words + threadIdx.x; k < end; k += 256) dst[k] = src[k];
+    }
+}
+
+hipError_t launch_report(hipStream_t s, int B, const long long* records, const int* n_active, const int* err_flag,
+                         const WinState* st, int all, Report* rep, WinState* hs) {
+    k_report<<<st ? (B + 63) / 64 : 1, 256, 0, s>>>(B, records, n_active, err_flag, st, all, rep, hs);
+    return hipGetLastError();
+}
+
 size_t prep_counters(int B, int T) { return (size_t)B * T * kTC; }
 size_t seg_own_words(int B, int T) { return (size_t)B * T * (kGuestBins + 1); }
 
@@ -2567,21 +2637,51 @@ hipError_t launch_plan_results(hipStream_t s, const Search& sp, int B, const Win
 
 // ------------------------------------------------------------ probes
 
-__global__ void k_rates(const float* __restrict__ d_a, const float* __restrict__ d_b, int m, float tau,
-                        Hyp* __restrict__ hyps) {
-    int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= m) return;
-    Hyp h;
-    h.ra = rate_of(d_a[k], tau);
-    h.rb = d_b ? rate_of(d_b[k], tau) : h.ra;
-    h.kind = d_b ? HYP_INTERVAL : HYP_POINT;
-    h.pad = 0;
-    hyps[k] = h;
+__global__ void k_probe_items(const float* __restrict__ d_a, const float* __restrict__ d_b, int m, float tau, int T,
+                              Hyp* __restrict__ hyps, int* __restrict__ act, Item* __restrict__ items,
+                              Queue* __restrict__ q) {
+    const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x, n = (long long)m * T;
+    if (i < 2 * kXcd) {
+        q[i].n_items = i == 0 ? (int)n : 0;
+        q[i].next = 0;
+    }
+    if (i < m) {
+        Hyp h;
+        h.ra = rate_of(d_a[i], tau);
+        h.rb = d_b ? rate_of(d_b[i], tau) : h.ra;
+        h.kind = d_b ? HYP_INTERVAL : HYP_POINT;
+        h.pad = 0;
+        hyps[i] = h;
+        act[i] = (int)i;
+    }
+    if (i < n) items[i] = Item{0, (int)(i % T), (int)(i / T), 1};
 }
 
-hipError_t launch_rates(hipStream_t s, const float* d_a, const float* d_b, int m, float tau, Hyp* hyps) {
-    if (m <= 0) return hipSuccess;
-    k_rates<<<(m + 255) / 256, 256, 0, s>>>(d_a, d_b, m, tau, hyps);
+hipError_t launch_probe_items(hipStream_t s, const float* d_a, const float* d_b, int m, float tau, int T, Hyp* hyps,
+                              int* act, Item* items, Queue* q) {
+    const long long n = std::max((long long)m * T, (long long)(2 * kXcd));
+    k_probe_items<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(d_a, d_b, m, tau, T, hyps, act, items, q);
+    return hipGetLastError();
+}
+
+__global__ void k_probe_sums(int m, int T, const long long* __restrict__ seg_off, const Part* __restrict__ part,
+                             unsigned long long* __restrict__ S, long long* __restrict__ N) {
+    const int h = blockIdx.x * blockDim.x + threadIdx.x;
+    if (h >= m) return;
+    unsigned long long a = 0, b = 0;
+    for (int t = 0; t < T; ++t) {
+        if (seg_off[t + 1] == seg_off[t]) continue;  // empty tile: not evaluated, contributes 0
+        const Part q = part[(long long)h * T + t];
+        a += q.S;
+        b += q.N;
+    }
+    S[h] = a;
+    N[h] = (long long)b;
+}
+
+hipError_t launch_probe_sums(hipStream_t s, int m, int T, const long long* seg_off, const Part* part,
+                             unsigned long long* S, long long* N) {
+    k_probe_sums<<<(m + 63) / 64, 64, 0, s>>>(m, T, seg_off, part, S, N);
     return hipGetLastError();
 }
 
