@@ -1099,37 +1099,6 @@ constexpr unsigned kStepIn0 = 1u << 25, kStepIn1 = 1u << 26;  // the pixels befo
 constexpr unsigned kStepNone = 31u << kStepRate;
 static_assert(3 * kMaxNodes <= 31, "rate index of a step");
 
-// The pixels of walk_tile's walk after its start, handed to `visit` (the end
-// comes last).
-template <class V>
-__device__ __forceinline__ void walk_pixels(int kx, int ky, int kxb, int kyb, const float4& ev, V&& visit) {
-    const bool px = kxb > kx, py = kyb > ky;
-    const int sx = px ? 1 : -1, sy = py ? 1 : -1;
-    if (kx != kxb && ky != kyb) {
-        const double xo = (double)ev.x - (double)px, yo = (double)ev.y - (double)py;
-        const double aax = fabs((double)ev.z), aay = fabs((double)ev.w);
-        const double thr = (aax + aay) * 0.00390625;
-        do {
-            const double ex = fabs((double)kx - xo) * aay;
-            const double ey = fabs((double)ky - yo) * aax;
-            const double e = ex - ey;
-            const bool lo = e < -thr, hi = e > thr;
-            if (!lo && !hi) {
-                visit(kx + sx, ky);
-                visit(kx, ky + sy);
-            }
-            kx += !hi ? sx : 0;
-            ky += !lo ? sy : 0;
-            visit(kx, ky);
-        } while (kx != kxb && ky != kyb);
-    }
-    while (kx != kxb || ky != kyb) {
-        kx += kx != kxb ? sx : 0;
-        ky += ky != kyb ? sy : 0;
-        visit(kx, ky);
-    }
-}
-
 __device__ __forceinline__ float lane_f(float v, int k) {
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), k));
 }
@@ -1300,9 +1269,9 @@ __global__ __launch_bounds__(NT, NT == 1024 ? 4 : 6) void k_nodes(
         // rates are one diagonal step, and what its walk visits on the way
         // (walk_tile's corner test) a step from a pixel to itself, which adds
         // to the one child's image only.  A list without room, or an event
-        // that moves further, leaves every wave to find its strip's changes
-        // from the segment's events again, at every rate (s_full: the groups
-        // are cut so narrow that ordinary windows meet neither).
+        // that moves further, leaves the images to be made one by one from the
+        // segment's events (s_full: the groups are cut so narrow that ordinary
+        // windows meet neither; windows whose events crowd on few points do).
         if (nl > mcap && lane == 0) *s_full = 1;
         for (int j0 = 0; j0 < min(nl, mcap); j0 += 64) {
             const bool ok = j0 + lane < nl;
@@ -1372,14 +1341,39 @@ __global__ __launch_bounds__(NT, NT == 1024 ? 4 : 6) void k_nodes(
             if (two) put(gx, gy, kxb, kyb, xfirst ? cy : cx);
         }
         __syncthreads();  // the image at ra and the lists are complete
-
-        {
-            const int sy0 = y0 + wave * sr, sh = min(sr, th - wave * sr);
-            const auto in_strip = [&](int kx, int ky) {
-                return (unsigned)(kx - x0) < (unsigned)tw && (unsigned)(ky - sy0) < (unsigned)sh;
-            };
-            const bool full = *s_full != 0;
-            const int ns = full ? 0 : s_cnt[wave];
+        const bool full = *s_full != 0;
+        uint4* const t4 = reinterpret_cast<uint4*>(tile);
+        const int n4 = (R.rw * (th + 2) + 3) >> 2;
+        if (full) {
+            for (int i = tid; i < n4; i += NT) t4[i] = make_uint4(0u, 0u, 0u, 0u);
+            R.vxhi = to_vgpr(R.xhi);
+            R.vyhi = to_vgpr(R.yhi);
+            __syncthreads();
+        }
+      // once over the last image of the group, or (full) over every image,
+      // 3k: node k's point image, 3k + 1 and 3k + 2: its children's.  (Every
+      // wave looking through all events for its strip's changes, phase by
+      // phase, kept the counters but took 35 ms for 16 windows of 1M events
+      // on 128 x 128 pixels; image by image 9.3, 200k events 4.5 and 1.9.)
+      for (int im = 0; im < (full ? 3 * m : 1); ++im) {
+        const int fk = im / 3, fside = im - 3 * fk;
+        if (full && fside && !__builtin_amdgcn_readlane(kids, fk)) continue;  // a leaf
+        if (full) {
+            const float lo = fside == 1 ? lane_f(na, fk) : lane_f(nc, fk);
+            const float hi = fside == 2 ? lane_f(nb, fk) : lane_f(nc, fk);
+            int nin = 0;  // events in the tile at the far end
+            for (unsigned j = tid; j < nseg; j += NT) {
+                const float4 e = at(j);
+                int kx, ky, hx, hy;
+                pix(e, lo, kx, ky);
+                pix(e, hi, hx, hy);
+                tile_add(org, R, kx, ky);
+                if (kx != hx || ky != hy) walk_tile(org, R, kx, ky, hx, hy, e.x, e.y, e.z, e.w);
+                nin += (unsigned)(hx - x0) < (unsigned)tw && (unsigned)(hy - y0) < (unsigned)th;
+            }
+            if (fside && nin) atomicAdd(s_dN, nin);
+        } else {
+            const int ns = s_cnt[wave];
             const unsigned* const steps = steps_of(wave);
             // four chunks of steps at a time, kept in registers when they are all
             constexpr int C = 4;
@@ -1403,13 +1397,6 @@ __global__ __launch_bounds__(NT, NT == 1024 ? 4 : 6) void k_nodes(
                     }
                 }
             };
-            // the segment's j-th event (with s_full), and whether it moves
-            const auto moving = [&](unsigned j, float4& e) {
-                int kx, ky, kxb, kyb;
-                e = at(j);
-                ends(e, kx, ky, kxb, kyb);
-                return kx != kxb || ky != kyb;
-            };
             const auto first = [&](unsigned v) { return tile + (v & 0xFFFFu); };
             const auto second = [&](unsigned v) {
                 const int dx = (int)(v << (30 - kStepX)) >> 30, dy = (int)(v << (30 - kStepY)) >> 30;
@@ -1419,45 +1406,13 @@ __global__ __launch_bounds__(NT, NT == 1024 ? 4 : 6) void k_nodes(
                 if (dS != 0) atomicAdd(s_dS + to_vgpr(ph), (unsigned long long)dS);
                 if (dH != 0) atomicAdd(s_dH + to_vgpr(ph), dH);
             };
-            // The extra pixels of an interval's image over the point image at
-            // c, found from the events: those of a walk between the rates c
-            // and o, less the pixel at c.  sgn = 1 adds them (phase ph of node
-            // k), -1 takes them away again, back to the point image.
-            const auto extras = [&](float c, float o, int sgn, int k, int ph) {
-                const bool fwd = o > c;
-                for (unsigned j = lane; j < nseg; j += 64) {
-                    float4 e;
-                    if (!moving(j, e)) continue;
-                    int cx, cy, ox, oy;
-                    pix(e, c, cx, cy);
-                    pix(e, o, ox, oy);
-                    if (ox == cx && oy == cy) continue;
-                    long long dS = 0;
-                    int dH = 0;
-                    const auto step = [&](int kx, int ky) {
-                        if (in_strip(kx, ky) && (kx != cx || ky != cy)) {
-                            dS += 2 * (long long)(int)atomicAdd(ring_at(org, R, kx, ky), (unsigned)sgn) + 1;
-                            dH += 1;
-                        }
-                    };
-                    if (!fwd) step(ox, oy);
-                    walk_pixels(fwd ? cx : ox, fwd ? cy : oy, fwd ? ox : cx, fwd ? oy : cy, e, step);
-                    if (sgn > 0) {
-                        account(ph, dS, dH);
-                        const int d = (int)in_strip(ox, oy) - (int)in_strip(cx, cy);
-                        if (fwd && d) atomicAdd(s_dN + to_vgpr(k), d);
-                    }
-                }
-            };
-            float c0 = ra, b0 = ra;  // centre and end of the image in the counters (at first: points at ra)
-            for (int k = 0; (full || ns > 0) && k < m; ++k) {
-                const float a = lane_f(na, k), c = lane_f(nc, k), b = lane_f(nb, k);
+            for (int k = 0; ns > 0 && k < m; ++k) {
+                const bool leaf = lane_f(na, k) == lane_f(nb, k);
 #pragma unroll 1
                 for (int st = 0; st < 4; ++st) {
                     // 0: the last second child's extra pixels go, the points
                     // move to the next centre; 1: first child's extra pixels;
                     // 2: they go; 3: second child's
-                    const float fc = st ? c : c0, fo = st == 0 ? b0 : st == 3 ? b : a;
                     if (st == 0) {
                         each_step(3 * k - 1, 1u, [&](unsigned v) {
                             if (v & kStepIn1) atomicSub(second(v), 1u);
@@ -1475,7 +1430,6 @@ __global__ __launch_bounds__(NT, NT == 1024 ? 4 : 6) void k_nodes(
                             if (st == 3 && d) atomicAdd(s_dN + to_vgpr(k), d);
                         });
                     }
-                    if (full && fc != fo) extras(fc, fo, st & 1 ? 1 : -1, k, st == 1 ? 3 * k + 1 : 3 * k + 2);
                     if (st == 0) {
                         each_step(3 * k - 1, 3u, [&](unsigned v) {
                             const bool in0 = v & kStepIn0, in1 = v & kStepIn1;
@@ -1485,32 +1439,11 @@ __global__ __launch_bounds__(NT, NT == 1024 ? 4 : 6) void k_nodes(
                             account(3 * k, (in1 ? 2 * (long long)(int)o1 + 1 : 0) - (in0 ? 2 * (long long)(int)o0 - 1 : 0),
                                     (int)in1 - (int)in0);
                         });
-                        for (unsigned j = lane; full && j < nseg; j += 64) {
-                            float4 e;
-                            if (!moving(j, e)) continue;
-                            int cx, cy, kx, ky;
-                            pix(e, c0, cx, cy);
-                            pix(e, c, kx, ky);
-                            if (cx == kx && cy == ky) continue;
-                            long long dS = 0;
-                            int dH = 0;
-                            if (in_strip(cx, cy)) {
-                                dS += 1 - 2 * (long long)(int)atomicSub(ring_at(org, R, cx, cy), 1u);
-                                dH -= 1;
-                            }
-                            if (in_strip(kx, ky)) {
-                                dS += 2 * (long long)(int)atomicAdd(ring_at(org, R, kx, ky), 1u) + 1;
-                                dH += 1;
-                            }
-                            account(3 * k, dS, dH);
-                        }
-                        c0 = c;
                     }
                     // the next part's changes stay behind this one's
                     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-                    if (a == b) break;  // a leaf
+                    if (leaf) break;
                 }
-                b0 = b;
             }
         }
         // The sums over the last image: the border's counters come off, then
@@ -1528,8 +1461,6 @@ __global__ __launch_bounds__(NT, NT == 1024 ? 4 : 6) void k_nodes(
             hits -= v;
         }
         __syncthreads();
-        uint4* const t4 = reinterpret_cast<uint4*>(tile);
-        const int n4 = (R.rw * (th + 2) + 3) >> 2;
         for (int i = tid; i < n4; i += NT) {
             const uint4 v = t4[i];
             t4[i] = make_uint4(0u, 0u, 0u, 0u);
@@ -1544,6 +1475,21 @@ __global__ __launch_bounds__(NT, NT == 1024 ? 4 : 6) void k_nodes(
             atomicAdd(&s_fin[1], hits);
         }
         __syncthreads();
+        if (full) {
+            if (tid == 0) {
+                const int i = __builtin_amdgcn_readlane(slot, fk);
+                Part pt;
+                pt.S = s_fin[0];
+                pt.U = s_fin[1];
+                pt.N = fside ? (long long)*s_dN : (long long)s_fin[1];
+                pt.pad = 0;
+                part[((long long)w * HS + (fside == 0 ? i : F + 2 * i + fside - 1)) * g.T + t] = pt;
+                s_fin[0] = s_fin[1] = 0ull;
+                *s_dN = 0;
+            }
+            __syncthreads();
+            continue;
+        }
         if (tid < 64) {
             // lane p: the image of phase p.  The last image's sums less its
             // extra pixels give the last centre's, less the moves after
@@ -1582,6 +1528,8 @@ __global__ __launch_bounds__(NT, NT == 1024 ? 4 : 6) void k_nodes(
             if (lane < kEvalWaves + 1) s_cnt[lane] = 0;  // and s_full
             if (lane < 2) s_fin[lane] = 0ull;
         }
+      }
+        if (full && tid < kEvalWaves + 1) s_cnt[tid] = 0;  // and s_full
     }
 }
 
