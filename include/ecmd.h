@@ -202,7 +202,8 @@ int ecmd_ctx_get_profile(ecmd_ctx *ctx, ecmd_profile *out, int reset);
  * tile, (w + 2)(h + 2) for a w x h tile with its one-pixel border (0 = what
  * the LDS holds; smaller values split the FOE quadrants further, trading
  * guest copies for occupancy).  tile_px and eval_threads both 0: the
- * default rule of ecmd_plan picks both.  graph: replay the step
+ * default rule picks both from the sensor and the call's events
+ * (ecmd_plan).  graph: replay the step
  * loop as a captured hipGraph (0 = plain launches).  group: hypotheses of
  * one window and tile evaluated per work item (0 = chosen at every step:
  * 1 while the step has fewer than ~48 items per CU, else 2). */
@@ -227,7 +228,8 @@ int ecmd_ctx_get_tuning(const ecmd_ctx *ctx, ecmd_tuning *out);
  * (0: the default rule, which takes the first of: tiles whose counters let
  * three 512-thread workgroups share a CU, then two — each only when it
  * cuts the image into at most 24 tiles — then one 1024-thread workgroup
- * with the whole LDS);
+ * with the whole LDS: the tiling of calls of 3.5 million events or more;
+ * smaller calls take the whole LDS and 1024 threads at once);
  * polarity != 0 plans the two images of the polarity-aware contrast. */
 typedef struct {
     int32_t L;

@@ -471,10 +471,19 @@ static int tile_budget(ecmd_ctx* c) { return tile_budget_for(c->max_lds); }
 // guest copy walks its whole path in every tile it is copied to, so many
 // cuts cost more than they save (256 windows of 1280x720, D up to 2: 2.22 s
 // of evaluation in 48 tiles against 1.92 s in 24 with 1024 threads).
+// Below kFewEvents events in the call the last of these is taken at once:
+// the items are then short, and what each costs besides its events (its
+// set-up and sums, per tile) and its threads' chain of walks weigh more than
+// hidden latency.  us a search, small tiles and whole LDS: 346x260, 8 windows
+// of 100k events 2810 and 1950, 16 of 200k 4600 and 4470, 32 of 200k 6590 and
+// 7120; 640x480, 16 of 50k 4510 and 3430, 16 of 200k 5910 and 5610, 32 of 200k
+// 9280 and 9670; 128x128 (4 tiles either way), 16 of 10k 1830 and 1080, 64 of
+// 50k 2620 and 2110.
 constexpr int kMaxSmallTiles = 24;
+constexpr long long kFewEvents = 3500000;
 
 static bool choose_tiling(size_t max_lds, const ecmd_tuning& tu, int W, int H, float cx, float cy, int npol,
-                          Geometry& g, int& nt, int& budget) {
+                          long long n_events, Geometry& g, int& nt, int& budget) {
     const int full = tile_budget_for(max_lds);
     if (tu.tile_px > 0 || tu.eval_threads > 0) {
         budget = tu.tile_px > 0 ? std::min(tu.tile_px, full) : full;
@@ -482,7 +491,7 @@ static bool choose_tiling(size_t max_lds, const ecmd_tuning& tu, int W, int H, f
         return plan_geometry(W, H, cx, cy, budget, npol, g);
     }
     const int divs[] = {3, 2}, nts[] = {512, 512};
-    for (int k = 0; k < 2; ++k) {
+    for (int k = 0; k < 2 && n_events >= kFewEvents; ++k) {
         budget = tile_budget_for(max_lds / divs[k]);
         nt = nts[k];
         if (plan_geometry(W, H, cx, cy, budget, npol, g) && g.nsp <= kMaxSmallTiles) return true;
@@ -539,17 +548,22 @@ static void set_groups(ecmd_ctx* c, int B, Search& sp, int T) {
 // Bytes of the node groups' lists for nb workgroups of nt threads.
 static size_t list_bytes(int nb, int nt, int cap) { return (size_t)nb * (nt / 64) * node_list_bytes(cap); }
 
-// Node groups of a search of B windows of T segments, on nb workgroups of nt
-// threads (0: none) with lists of mcap events per wave.  Below kMinSegments
-// segments most of the chip is idle with or without groups, and the launch
-// that they cost per round is not repaid (one 346x260 window of 100k events:
-// 1.45 ms without, 1.53 with; four: 2.38 and 2.21; one 640x480 window of 1M
-// events, 24 segments: 3.54 and 3.20).  The lists keep a third of their room
-// for windows whose events move more than the mean.
+// Node groups of a search of B windows of T segments and n_events events, on
+// nb workgroups of nt threads (0: none) with lists of mcap events per wave.
+// With fewer than kMinSegments segments most of the chip is idle with or
+// without groups, and unless there are kManyEvents events the launch that they
+// cost per round is not repaid.  us a search, without and with groups: one
+// 346x260 window (4 segments) of 100k events 871 and 944, of 200k 1126 and
+// 1214, of 1M 3350 and 2792; two of 200k 1606 and 1600, four of 100k 1588 and
+// 1412; one 640x480 window (12) of 50k 953 and 1008, of 300k 1589 and 1500,
+// two of 50k 1257 and 1196.  The lists keep a third of their room for windows
+// whose events move more than the mean.
 constexpr int kMinSegments = 24;
+constexpr long long kManyEvents = 300000;
 
-static void set_nodes(Search& sp, int B, int T, int nb, int nt, int mcap) {
-    sp.nmax = nb > 0 && mcap >= 64 && (long long)B * T >= kMinSegments ? kMaxNodes : 0;
+static void set_nodes(Search& sp, int B, int T, long long n_events, int nb, int nt, int mcap) {
+    const bool many = (long long)B * T >= kMinSegments || n_events >= kManyEvents;
+    sp.nmax = nb > 0 && mcap >= 64 && many ? kMaxNodes : 0;
     sp.nwave = nt / 64;
     sp.nlist = mcap * 3 / 8;
     sp.npad = 0;
@@ -562,9 +576,10 @@ static int run_search(ecmd_ctx* c, const ecmd_sensor* sensor, Inputs& in, int B,
     const int W = sensor->width, H = sensor->height;
     const int npol = in.pol ? 2 : 1;
     const long long M = (long long)W * H * npol;  // cells of the event image(s): the key is M*S - N^2
+    const long long n_events = c->h_off[B] - c->h_off[0];
     Geometry g;
     int nt = 0, budget = 0;
-    if (!choose_tiling(c->max_lds, c->tune, W, H, sensor->foe_x, sensor->foe_y, npol, g, nt, budget))
+    if (!choose_tiling(c->max_lds, c->tune, W, H, sensor->foe_x, sensor->foe_y, npol, n_events, g, nt, budget))
         return fail(c, ECMD_EINVAL, "sensor %dx%d needs more than %d tiles", W, H, kMaxTiles / npol);
     Timers tm(c);
     HIPCHK(c, c->queues.ensure(sizeof(Queue) * kQueues));
@@ -576,7 +591,6 @@ static int run_search(ecmd_ctx* c, const ecmd_sensor* sensor, Inputs& in, int B,
     if (rc) return rc;
     tm.end(2);
     tm.cut();
-    const long long n_events = c->h_off[B] - c->h_off[0];
     int rebins = 0;
 
     Search sp;
@@ -597,7 +611,7 @@ static int run_search(ecmd_ctx* c, const ecmd_sensor* sensor, Inputs& in, int B,
     const size_t lds = eval_lds_bytes(g.ring_px);
     int nb = 0;
     HIPCHK(c, eval_setup(c, g.ring_px, nt, &nb));
-    set_nodes(sp, B, T, c->nodes_nb, nt, kListCap);
+    set_nodes(sp, B, T, n_events, c->nodes_nb, nt, kListCap);
     if (sp.nmax > 0) HIPCHK(c, c->lists.ensure(list_bytes(c->nodes_nb, nt, kListCap)));
     HIPCHK(c, c->state.ensure(sizeof(WinState) * B));
     HIPCHK(c, c->front.ensure(sizeof(Node) * (size_t)B * sp.CAP));
@@ -914,7 +928,7 @@ static int plan_shape(ecmd_ctx* c, const ecmd_sensor* sensor, const ecmd_search*
     const int npol = lim->polarity ? 2 : 1;
     Geometry& g = sh.g;
     int nt = 0, budget = 0;
-    if (!choose_tiling(c->max_lds, c->tune, W, H, sensor->foe_x, sensor->foe_y, npol, g, nt, budget))
+    if (!choose_tiling(c->max_lds, c->tune, W, H, sensor->foe_x, sensor->foe_y, npol, lim->max_events, g, nt, budget))
         return fail(c, ECMD_EINVAL, "sensor %dx%d needs more than %d tiles", W, H, kMaxTiles / npol);
     ecmd_plan_limits L2 = *lim;
     // default: twice the grid depth and eight more (a level-synchronous
@@ -957,7 +971,7 @@ static int plan_shape(ecmd_ctx* c, const ecmd_sensor* sensor, const ecmd_search*
     sh.nodes_lds = c->nodes_lds;
     sh.nodes_nb = c->nodes_nb;
     sh.mcap = kListCap;
-    set_nodes(sp, Bm, g.T, sh.nodes_nb, nt, sh.mcap);
+    set_nodes(sp, Bm, g.T, L2.max_events, sh.nodes_nb, nt, sh.mcap);
     if (sp.nmax == 0) sh.mcap = 0;  // no launch forms groups
     return ECMD_OK;
 }
@@ -989,7 +1003,7 @@ static int plan_enqueue(ecmd_ctx* c, const PlanShape& sh, void* const* b, const 
     const int T = g.T;
     Search sp = sh.sp;
     set_groups(c, B, sp, T);
-    set_nodes(sp, B, T, sh.nodes_nb, sh.nt, sh.mcap);
+    set_nodes(sp, B, T, sh.lim.max_events, sh.nodes_nb, sh.nt, sh.mcap);
     const long long* off = (const long long*)offsets;
     const signed char* pol = (const signed char*)polarity;
     WinParam* wp = (WinParam*)b[PB_WP];
@@ -1137,7 +1151,7 @@ int ecmd_plan(const ecmd_sensor* sensor, const ecmd_search* search, int32_t pola
     Geometry g;
     int nt = 0, budget = 0;
     if (!choose_tiling(lds_bytes ? (size_t)lds_bytes : (size_t)160 * 1024, tu, sensor->width, sensor->height,
-                       sensor->foe_x, sensor->foe_y, npol, g, nt, budget))
+                       sensor->foe_x, sensor->foe_y, npol, LLONG_MAX, g, nt, budget))
         return ECMD_EINVAL;
     memset(out, 0, sizeof *out);
     out->L = L;
@@ -1552,7 +1566,7 @@ static int probe_impl(ecmd_ctx* c, const ecmd_sensor* sensor, const float* x, co
     const long long M = (long long)W * H * npol;  // image cells per hypothesis
     Geometry g;
     int nt = 0, budget = 0;
-    if (!choose_tiling(c->max_lds, c->tune, W, H, sensor->foe_x, sensor->foe_y, npol, g, nt, budget))
+    if (!choose_tiling(c->max_lds, c->tune, W, H, sensor->foe_x, sensor->foe_y, npol, n, g, nt, budget))
         return fail(c, ECMD_EINVAL, "sensor needs more than %d tiles", kMaxTiles / npol);
     const int T = g.T;
     Inputs in;
