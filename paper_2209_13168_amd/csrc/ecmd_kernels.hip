@@ -193,32 +193,6 @@ __device__ __forceinline__ int window_of_block(const int* blk_start, int B, int 
     return lo;
 }
 
-__device__ __forceinline__ int band_of(const int* cut, int n, int k) {
-    // the cuts increase: the band is the count of inner cuts at or below k
-    // (every lane runs the same loop, so the cuts are read as scalars)
-    int b = 0;
-    for (int j = 1; j < n; ++j) b += cut[j] <= k ? 1 : 0;
-    return b;
-}
-
-// Tile rectangle [tx0, tx1] x [ty0, ty1] reachable by an event over the
-// whole search range (the pixel box spanned by its root segment), or
-// false when that box misses the image.
-__device__ __forceinline__ bool event_tiles(const Geometry& g, float x, float y, float ax, float ay,
-                                            float r_lo, float r_hi, int& tx0, int& tx1, int& ty0,
-                                            int& ty1) {
-    float xa = fmaf(ax, r_lo, x), xb = fmaf(ax, r_hi, x);
-    float ya = fmaf(ay, r_lo, y), yb = fmaf(ay, r_hi, y);
-    int kx0 = flr_clamp(fminf(xa, xb), g.W), kx1 = flr_clamp(fmaxf(xa, xb), g.W);
-    int ky0 = flr_clamp(fminf(ya, yb), g.H), ky1 = flr_clamp(fmaxf(ya, yb), g.H);
-    if (kx1 < 0 || kx0 > g.W - 1 || ky1 < 0 || ky0 > g.H - 1) return false;
-    kx0 = max(kx0, 0); ky0 = max(ky0, 0);
-    kx1 = min(kx1, g.W - 1); ky1 = min(ky1, g.H - 1);
-    tx0 = band_of(g.colcut, g.ntx, kx0); tx1 = band_of(g.colcut, g.ntx, kx1);
-    ty0 = band_of(g.rowcut, g.nty, ky0); ty1 = band_of(g.rowcut, g.nty, ky1);
-    return true;
-}
-
 __device__ __forceinline__ int walk_class(float ax, float ay, float kscale) {
     int b = (int)((fabsf(ax) + fabsf(ay)) * kscale);
     return kNB - 1 - min(max(b, 0), kNB - 1);
@@ -291,26 +265,69 @@ __device__ __forceinline__ void for_each_guest(const Geometry& g, const WinParam
     }
 }
 
-__device__ __forceinline__ PrepEv prep_event(const Geometry& g, const WinParam& p, float xv, float yv, float tv) {
+// All but the tiles: tx0 .. ty1 are the pixels of the box that the event
+// spans over the whole search range (clamped to the image), and ok is false
+// when that box misses the image.
+__device__ __forceinline__ PrepEv prep_box(const Geometry& g, const WinParam& p, float xv, float yv, float tv) {
     PrepEv e;
     e.valid = isfinite(xv) && isfinite(yv) && tv >= 0.0f && tv <= p.tau;
     e.ok = false;
+    e.tx0 = e.tx1 = e.ty0 = e.ty1 = 0;
     if (!e.valid) return e;
     const float ux = xv - g.cx, uy = yv - g.cy, delta = p.tau - tv;
     e.x = xv;
     e.y = yv;
     e.ax = ux * delta;
     e.ay = uy * delta;
-    e.ok = event_tiles(g, xv, yv, e.ax, e.ay, p.r_lo, p.r_hi, e.tx0, e.tx1, e.ty0, e.ty1);
+    const float xa = fmaf(e.ax, p.r_lo, xv), xb = fmaf(e.ax, p.r_hi, xv);
+    const float ya = fmaf(e.ay, p.r_lo, yv), yb = fmaf(e.ay, p.r_hi, yv);
+    const int kx0 = flr_clamp(fminf(xa, xb), g.W), kx1 = flr_clamp(fmaxf(xa, xb), g.W);
+    const int ky0 = flr_clamp(fminf(ya, yb), g.H), ky1 = flr_clamp(fmaxf(ya, yb), g.H);
+    e.ok = !(kx1 < 0 || kx0 > g.W - 1 || ky1 < 0 || ky0 > g.H - 1);
+    e.tx0 = max(kx0, 0);
+    e.ty0 = max(ky0, 0);
+    e.tx1 = min(kx1, g.W - 1);
+    e.ty1 = min(ky1, g.H - 1);
     e.cls = walk_class(e.ax, e.ay, p.kscale);
     return e;
+}
+
+// The tiles of N prepared boxes.  The cuts increase: a band is the count of
+// inner cuts at or below the pixel, and each cut is read (as a scalar) once
+// for all the thread's events.
+template <int N>
+__device__ __forceinline__ void prep_tiles(const Geometry& g, PrepEv (&e)[N]) {
+    int x0[N] = {}, x1[N] = {}, y0[N] = {}, y1[N] = {};
+    for (int k = 1; k < g.ntx; ++k) {
+        const int c = g.colcut[k];
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+            x0[j] += c <= e[j].tx0 ? 1 : 0;
+            x1[j] += c <= e[j].tx1 ? 1 : 0;
+        }
+    }
+    for (int k = 1; k < g.nty; ++k) {
+        const int c = g.rowcut[k];
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+            y0[j] += c <= e[j].ty0 ? 1 : 0;
+            y1[j] += c <= e[j].ty1 ? 1 : 0;
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+        e[j].tx0 = x0[j];
+        e[j].tx1 = x1[j];
+        e[j].ty0 = y0[j];
+        e[j].ty1 = y1[j];
+    }
 }
 
 // Prep workgroups: kPrepPer events per thread, held in registers between the
 // counting and the writing.  1024 threads share the chunk's zeroing of the
 // counters and its cursor atomics (up to kMaxTiles * kTC of each); with fewer
 // events there are too few such chunks to fill the CUs, and 256 threads are
-// faster (count / scatter: 20M events in 24 tiles 141 / 214 us with 1024
+// faster (count / scatter, before prep_tiles: 20M events in 24 tiles 141 / 214 us with 1024
 // threads, 165 / 289 with 256; 2M in 8 tiles 24 / 34.8 and 21.6 / 31.0; one
 // window of 10k 6.2 / 6.8 with 256, 20 / 34 with chunks of 4096).  Eight
 // events per thread: 137 / 306 us for the 20M.
@@ -337,8 +354,10 @@ struct PrepIn {
     }
 };
 
-// Bound by instructions (202 VALU per 64 events, three quarters of the issue
-// slots): the tile bands and, for the wave's events with guests, their bins.
+// Bound by instructions: the boxes, the tile bands and, for the wave's events
+// with guests, their bins (20M events in 24 tiles: 141 us with the cuts read
+// and the bands counted event by event, 108 with each cut read once for the
+// thread's four; 80M: 641 and 484).
 template <int NT, int PER>
 __global__ __launch_bounds__(NT) void k_prep_count(
     Geometry g, const float* __restrict__ x, const float* __restrict__ y, const float* __restrict__ t_rel,
@@ -358,16 +377,18 @@ __global__ __launch_bounds__(NT) void k_prep_count(
     const WinParam p = wp[w];
     PrepIn<PER> in;
     in.template load<NT>(x, y, t_rel, pol, beg, n);
+    PrepEv e[PER];
+#pragma unroll
+    for (int j = 0; j < PER; ++j) e[j] = prep_box(g, p, in.x[j], in.y[j], in.t[j]);
+    prep_tiles(g, e);
 #pragma unroll
     for (int j = 0; j < PER; ++j) {
-        const int i = j * NT + (int)threadIdx.x;
-        if (i >= n) break;
-        const PrepEv e = prep_event(g, p, in.x[j], in.y[j], in.t[j]);
-        if (!e.valid) atomicOr(&err_flag[w], 1);
-        if (!e.ok) continue;
+        if (j * NT + (int)threadIdx.x >= n) break;
+        if (!e[j].valid) atomicOr(&err_flag[w], 1);
+        if (!e[j].ok) continue;
         const int sb = seg_base(g, in.p[j]);
-        atomicAdd(&s_cnt[own_copy(g, sb, e)], 1);
-        for_each_guest(g, p, s_cuts, sb, e, [&](int k) { atomicAdd(&s_cnt[k], 1); });
+        atomicAdd(&s_cnt[own_copy(g, sb, e[j])], 1);
+        for_each_guest(g, p, s_cuts, sb, e[j], [&](int k) { atomicAdd(&s_cnt[k], 1); });
     }
     __syncthreads();
     for (int k = threadIdx.x; k < nc; k += NT)
@@ -456,8 +477,8 @@ __global__ __launch_bounds__(1024) void k_prep_scan(int B, int T, const int* __r
 
 // The same events again; an owned record's rank in its run is what the
 // counting atomic returned, and the events stay in registers, so nothing is
-// read or worked out a third time (20M events in 24 tiles: 434 -> 214 us, 80M:
-// 2160 -> 1010).  Only the few guests are counted and then ranked.
+// read or worked out a third time (20M events in 24 tiles: 434 -> 195 us, 80M:
+// 2160 -> 977).  Only the few guests are counted and then ranked.
 template <int NT, int PER>
 __global__ __launch_bounds__(NT) void k_prep_scatter(
     Geometry g, const float* __restrict__ x, const float* __restrict__ y, const float* __restrict__ t_rel,
@@ -484,10 +505,11 @@ __global__ __launch_bounds__(NT) void k_prep_scatter(
     PrepEv e[PER];
     int sb[PER], rank[PER];
 #pragma unroll
+    for (int j = 0; j < PER; ++j) e[j] = prep_box(g, p, in.x[j], in.y[j], in.t[j]);
+    prep_tiles(g, e);
+#pragma unroll
     for (int j = 0; j < PER; ++j) {
-        const int i = j * NT + (int)threadIdx.x;
-        e[j] = prep_event(g, p, in.x[j], in.y[j], in.t[j]);
-        e[j].ok = e[j].ok && i < n;
+        e[j].ok = e[j].ok && j * NT + (int)threadIdx.x < n;
         if (!e[j].ok) continue;
         sb[j] = seg_base(g, in.p[j]);
         rank[j] = atomicAdd(&s_cnt[own_copy(g, sb[j], e[j])], 1);
