@@ -732,7 +732,7 @@ __device__ __forceinline__ void walk_tile(unsigned* org, const Ring& R, int kx, 
     if (kx != kxb && ky != kyb) {
         // the edges ahead are X = kx + px and Y = ky + py; with the origin
         // moved to (x - px, y - py) (exact in fp64), X - x = kx - xo exactly
-        const double xo = (double)xf - (double)px, yo = (double)yf - (double)py;
+        const double xo = (double)xf - (px ? 1.0 : 0.0), yo = (double)yf - (py ? 1.0 : 0.0);
         const double aax = fabs((double)axf), aay = fabs((double)ayf);
         const double thr = (aax + aay) * 0.00390625;
         // both coordinates still move: which edge does the ray meet first
