@@ -63,19 +63,19 @@ DEFAULT_F = 96
 # Bytes of one prepared event record read by the evaluation kernel (x, y, ax, ay as fp32).
 EVENT_RECORD_BYTES = 16
 
-# HBM traffic of the evaluation kernel per launch, from two rocprofv3 --pmc
-# passes (FETCH_SIZE, then WRITE_SIZE, KiB per dispatch, mean over the
-# dispatches) of `bench.py --steps 1 --warmup 0 --legs main --extra none
+# HBM traffic of one evaluation (k_eval and the node groups' k_nodes after it),
+# from two rocprofv3 --pmc passes (FETCH_SIZE, then WRITE_SIZE, KiB per
+# dispatch, mean over the dispatches) of `bench.py --steps 1 --warmup 0 --legs main --extra none
 # --no-cpu-baseline` on the default workload, each scaled by bytes/KiB that
 # the same counter reads for a plain copy of 1 GiB (`bench.py
 # --calibrate-copy`).  The figures hold only for the kernel sources and the
 # workload they were taken on; for anything else `traffic` is null.
 TRAFFIC = {
-    "sources_sha256": "fdc6d8b0e93706e4a3455bfc52efb26aef555c542fff6116ae86563e543558f0",
+    "sources_sha256": "1a5094da4d77875f6bf9f8793280ac0553da3cb628a9adf3c7e937dfc656ba16",
     "workload": {"config": "c5", "windows": 256, "frontier_batch": 96},
-    "fetch_kib": 5342178.8,
-    "write_kib": 7266.1,
-    "fetch_bytes_per_kib": 1073741824 / 524304.8,
+    "fetch_kib": 10573545.9,
+    "write_kib": 523037.0,
+    "fetch_bytes_per_kib": 1073741824 / 524306.0,
     "write_bytes_per_kib": 1073741824 / 1048576.0,
 }
 KERNEL_SOURCES = ("paper_2209_13168_amd/csrc/ecmd_kernels.hip", "paper_2209_13168_amd/csrc/ecmd_internal.hpp",
