@@ -71,11 +71,11 @@ EVENT_RECORD_BYTES = 16
 # --calibrate-copy`).  The figures hold only for the kernel sources and the
 # workload they were taken on; for anything else `traffic` is null.
 TRAFFIC = {
-    "sources_sha256": "1a5094da4d77875f6bf9f8793280ac0553da3cb628a9adf3c7e937dfc656ba16",
+    "sources_sha256": "f3cf985f77b17ea12b5b95d22ed3af0732749dbb4955162108fd2f6e8a5e0776",
     "workload": {"config": "c5", "windows": 256, "frontier_batch": 96},
-    "fetch_kib": 10573545.9,
-    "write_kib": 523037.0,
-    "fetch_bytes_per_kib": 1073741824 / 524306.0,
+    "fetch_kib": 10606754.2,
+    "write_kib": 522958.0,
+    "fetch_bytes_per_kib": 1073741824 / 524305.0,
     "write_bytes_per_kib": 1073741824 / 1048576.0,
 }
 KERNEL_SOURCES = ("paper_2209_13168_amd/csrc/ecmd_kernels.hip", "paper_2209_13168_amd/csrc/ecmd_internal.hpp",

@@ -933,7 +933,7 @@ static int plan_shape(ecmd_ctx* c, const ecmd_sensor* sensor, const ecmd_search*
         return fail(c, ECMD_EINVAL, "sensor %dx%d needs more than %d tiles", W, H, kMaxTiles / npol);
     ecmd_plan_limits L2 = *lim;
     // default: twice the grid depth and eight more (a level-synchronous
-    // search needs about L steps; finished steps still cost two launches)
+    // search needs about L steps; finished steps still cost their rounds' launches)
     if (L2.max_steps == 0) L2.max_steps = min(2 * L + 8, kMaxSteps);
     L2.max_steps = (L2.max_steps + 3) / 4 * 4;  // whole polling blocks of four steps
     // an event's tiles over any range lie in its FOE quadrant (no event
