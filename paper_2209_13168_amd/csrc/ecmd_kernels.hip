@@ -1644,6 +1644,13 @@ constexpr int NWF = NTF / 64;
 // windows of 346x260 and 64 of 640x480, per batch: 0.1 5.03 and 23.7 ms, 0.2
 // 5.01 and 23.6, 0.3 5.08 and 23.8 (7.29 and 40.3 without node groups).
 constexpr float kNodeShare = 0.2f;
+// A window of an image of at most kNodeSmall cells with more than kNodeDense
+// events per cell forms none: its walks are short, so plain evaluation is
+// cheap, and whole points of events cross pixel edges together and outgrow the
+// lists.  us a search, without and with groups: 128x128, 8 windows of 500k
+// events (30 per cell) 2816 and 3733, 16 of 1M (61) 6540 and 9270, 16 of 200k
+// (12) 2295 and 1863; 346x260 (89960 cells), 6 of 3M (33) 35960 and 21940.
+constexpr long long kNodeSmall = 40000, kNodeDense = 24;
 
 // Scratch of the workgroup's scans: each call alternates between two rows, so
 // a call needs one barrier (the row it writes was last read before the barrier
@@ -1844,8 +1851,9 @@ __device__ void emit_hyps(const Search& sp, const WinParam& p, int w, int T, con
     // the share of the events that a group may list
     const float share = fminf(kNodeShare, (float)sp.nlist / fmaxf(per, 1.0f));
     const float lam = p.kscale > 0.0f ? 0.25f * (float)kNB / p.kscale : 0.0f;
+    groups = groups && sp.nmax > 0 && (sp.M > kNodeSmall || p.n_events <= kNodeDense * sp.M);
     int nodes = 0;
-    for (int i0 = 0; groups && sp.nmax > 0 && i0 < n_sel; i0 += NTF) {
+    for (int i0 = 0; groups && i0 < n_sel; i0 += NTF) {
         const int i = i0 + threadIdx.x;
         bool in = false;
         if (i < n_sel) {

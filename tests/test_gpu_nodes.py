@@ -115,3 +115,24 @@ def test_lists_of_the_allocation_free_call(ctx):
                                      frontier_capacity=cap)
         torch.cuda.synchronize()
         assert ecmd.BatchPlan.results(out, 8) == want
+
+
+@pytest.mark.parametrize("n", [24 * 128 * 128, 24 * 128 * 128 + 1])
+def test_dense_small_windows(ctx, orc, n):
+    """Both sides of the line above which a small image's windows form no groups."""
+    from paper_2209_13168_amd import ecmd
+
+    wins = _placed(n, 9, (40, 90), (40, 90), (0.0, 0.4))[:2]
+    s = wins[0].spec
+    got = _run(ctx, wins)
+    saved = ctx.tuning()
+    try:
+        ctx.set_tuning(tile_px=6000, eval_threads=256)
+        assert _run(ctx, wins) == got
+    finally:
+        ctx.set_tuning(**saved)
+    S, N = ctx.probe_point(ecmd.sensor(s.width, s.height, s.foe), wins[0].x, wins[0].y, wins[0].t_rel, s.tau,
+                           np.array([got[0].d_hat], np.float32))[:2]
+    ev = orc.Events(wins[0].x, wins[0].y, wins[0].t_rel, np.float32(s.tau), s.width, s.height, s.foe)
+    So, No = orc.point(ev, float(got[0].d_hat))[:2]
+    assert (int(S[0]), int(N[0])) == (So, No) and got[0].K == s.width * s.height * So - No * No
