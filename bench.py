@@ -71,10 +71,10 @@ EVENT_RECORD_BYTES = 16
 # --calibrate-copy`).  The figures hold only for the kernel sources and the
 # workload they were taken on; for anything else `traffic` is null.
 TRAFFIC = {
-    "sources_sha256": "f3cf985f77b17ea12b5b95d22ed3af0732749dbb4955162108fd2f6e8a5e0776",
+    "sources_sha256": "501d5d03a02dfc6f3f95db98a43bf1b0f189c2ff8e016936a958391d42337323",
     "workload": {"config": "c5", "windows": 256, "frontier_batch": 96},
-    "fetch_kib": 10606754.2,
-    "write_kib": 522958.0,
+    "fetch_kib": 10605487.5,
+    "write_kib": 523470.4,
     "fetch_bytes_per_kib": 1073741824 / 524305.0,
     "write_bytes_per_kib": 1073741824 / 1048576.0,
 }
