@@ -1781,20 +1781,8 @@ static int preproc_impl(ecmd_ctx* c, int kind, const ecmd_sensor* in_s, const ec
         doff = c->soff.as<long long>();
         base = 0;
     }
-    // the windows' chunks
-    HIPCHK(c, c->pinned.ensure(sizeof(int) * (B + 1)));
-    int* const blk = (int*)c->pinned.p;
-    long long chunks = 0;
-    for (int w = 0; w <= B; ++w) {
-        if (chunks > INT_MAX) return fail(c, ECMD_EINVAL, "too many events");
-        blk[w] = (int)chunks;
-        if (w < B) chunks += (off[w + 1] - off[w] + kPreChunk - 1) / kPreChunk;
-    }
-    const int nblk = blk[B];
-    const size_t nb1 = std::max(nblk, 1);
-    HIPCHK(c, c->blk.ensure(sizeof(int) * (B + 1)));
-    HIPCHK(c, hipMemcpyAsync(c->blk.p, blk, sizeof(int) * (B + 1), hipMemcpyHostToDevice, c->stream));
-    const int* dblk = c->blk.as<int>();
+    const long long nblk = (n + kPreChunk - 1) / kPreChunk;
+    const size_t nb1 = std::max(nblk, 1ll);
     HIPCHK(c, c->keep.ensure(nb1 * (kPreChunk / 8)));
     HIPCHK(c, c->err_flag.ensure(sizeof(int) * nb1));
     HIPCHK(c, c->misc.ensure(sizeof(long long) * (nb1 + 1)));
@@ -1822,11 +1810,11 @@ static int preproc_impl(ecmd_ctx* c, int kind, const ecmd_sensor* in_s, const ec
             HIPCHK(c, c->counts.ensure(sizeof(unsigned) * M * nwin));
             HIPCHK(c, hipMemsetAsync(c->counts.p, 0, sizeof(unsigned) * M * nwin, c->stream));
         }
-        HIPCHK(c, launch_hot_keep(c->stream, dx, dy, doff, B, dblk, nblk, W, H, nb, cnt, cursor, list, hot,
+        HIPCHK(c, launch_hot_keep(c->stream, dx, dy, doff, B, nblk, W, H, nb, cnt, cursor, list, hot,
                                   c->counts.as<unsigned>(), (unsigned)max_count, words, blk_cnt));
     } else {
         const double th = floor((double)keep_frac * 16777216.0);
-        HIPCHK(c, launch_resample_keep(c->stream, doff, B, dblk, nblk, seed, (unsigned)th, words, blk_cnt));
+        HIPCHK(c, launch_resample_keep(c->stream, doff, B, nblk, seed, (unsigned)th, words, blk_cnt));
     }
     const float sx = kind == 1 ? (float)out_s->width / (float)W : 1.0f;
     const float sy = kind == 1 ? (float)out_s->height / (float)H : 1.0f;
@@ -1839,7 +1827,7 @@ static int preproc_impl(ecmd_ctx* c, int kind, const ecmd_sensor* in_s, const ec
         ot = oy + std::max(n, 1ll);
         ooff = (long long*)(ot + std::max(n, 1ll));
     }
-    HIPCHK(c, launch_compact(c->stream, dx, dy, dt, doff, B, dblk, nblk, words, blk_cnt, c->misc.as<long long>(), sx,
+    HIPCHK(c, launch_compact(c->stream, dx, dy, dt, doff, B, nblk, words, blk_cnt, c->misc.as<long long>(), sx,
                              sy, ox, oy, ot, ooff));
     if (!(flags & ECMD_DEVICE_PTR)) {
         std::vector<long long> ho(B + 1);

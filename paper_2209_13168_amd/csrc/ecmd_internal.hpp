@@ -277,25 +277,24 @@ hipError_t launch_select(hipStream_t s, const float* x, const float* y, const do
                          long long n, double t0, double t1, float* xo, float* yo, float* to, signed char* po,
                          int* blk_cnt, long long* total);
 
-// preprocessing (ecmd_preproc.hip): windows cut into chunks of kPreChunk
-// events (blk_start: their prefix per window, B + 1 entries; nblk chunks), a
-// keep bit per event (kPreChunk / 64 words a chunk) and the chunk's count
+// preprocessing (ecmd_preproc.hip): the batch's events cut into nblk chunks of
+// kPreChunk, a keep bit per event (kPreChunk / 64 words a chunk) and the chunk's count
 constexpr int kPreChunk = 8192;
 constexpr int kMaxBands = 256;
 // blk: nblk + 1 prefix sums
 hipError_t launch_compact(hipStream_t s, const float* x, const float* y, const float* t, const long long* offsets,
-                          int B, const int* blk_start, int nblk, const unsigned long long* words, const int* blk_cnt,
-                          long long* blk, float sx, float sy, float* xo, float* yo, float* to, long long* off_out);
-hipError_t launch_resample_keep(hipStream_t s, const long long* offsets, int B, const int* blk_start, int nblk,
+                          int B, long long nblk, const unsigned long long* words, const int* blk_cnt, long long* blk,
+                          float sx, float sy, float* xo, float* yo, float* to, long long* off_out);
+hipError_t launch_resample_keep(hipStream_t s, const long long* offsets, int B, long long nblk,
                                 unsigned long long seed, unsigned thresh24, unsigned long long* words, int* blk_cnt);
 // Pixel bands of the hot-pixel sort (0: too many, counters in memory).  With
 // nb bands: cnt (B nb, zero), cursor (B nb + 1), list (16 bits per event), hot
 // (a bit per pixel, whole 64-bit words per window); else counts (B W H, zero).
 int hot_bands(int W, int H);
 hipError_t launch_hot_keep(hipStream_t s, const float* x, const float* y, const long long* offsets, int B,
-                           const int* blk_start, int nblk, int W, int H, int nb, int* cnt, long long* cursor,
-                           uint16_t* list, unsigned long long* hot, unsigned* counts, unsigned max_count,
-                           unsigned long long* words, int* blk_cnt);
+                           long long nblk, int W, int H, int nb, int* cnt, long long* cursor, uint16_t* list,
+                           unsigned long long* hot, unsigned* counts, unsigned max_count, unsigned long long* words,
+                           int* blk_cnt);
 
 hipError_t launch_stream_bounds(hipStream_t s, const double* t, long long n, double t_start, double tau, int K,
                                 long long* offsets);

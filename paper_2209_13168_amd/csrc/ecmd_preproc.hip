@@ -8,14 +8,19 @@
 // window w (k counted from the window start) is kept iff the top 24 bits of
 // SplitMix64 at counter seed + (w * 2^32 + k + 1) * 0x9E3779B97F4A7C15 fall
 // below keep_frac * 2^24.
+#include <utility>
+
 #include "ecmd_internal.hpp"
 
 namespace ecmd {
 
 constexpr int kPreThreads = 1024;
-// Events of a workgroup: a chunk of one window (the host cuts every window
-// into chunks of kPreChunk; blk_start is their prefix).  Whether event e of a
-// chunk is kept is bit e % 64 of the chunk's word e / 64.
+// Events of a workgroup: a chunk of kPreChunk consecutive events of the batch,
+// whichever windows they lie in, so that the launches grow with the events and
+// not with the windows.  (A chunk per window: 65535 windows of 10 events
+// resampled in 1305 us, windows of 100 in 1312, against 228 and 340 with a
+// thread per event, and more windows than a grid holds workgroups refused.)
+// Whether event e of a chunk is kept is bit e % 64 of the chunk's word e / 64.
 constexpr int kPreIter = 8;
 constexpr int kPreWords = kPreThreads * kPreIter / 64;
 static_assert(kPreChunk == kPreThreads * kPreIter, "a chunk is a workgroup's events");
@@ -27,26 +32,34 @@ __device__ __forceinline__ unsigned long long splitmix64(unsigned long long s) {
     return z ^ (z >> 31);
 }
 
-// This workgroup's chunk: its window, the chunk's first event counted from
-// the window's start, and how many events it holds.
-struct Chunk {
-    int w, n;
-    long long first, base;  // base: the chunk's first event in the arrays
-};
-
-__device__ __forceinline__ Chunk chunk_of(const int* __restrict__ blk_start, int B,
-                                          const long long* __restrict__ offsets) {
-    int lo = 0, hi = B;  // the last window that starts at or before this chunk
+// The window of event i: the last w in [lo, hi) that starts at or before it.
+__device__ __forceinline__ int window_at(const long long* __restrict__ offsets, int lo, int hi, long long i) {
     while (hi - lo > 1) {
         const int mid = (lo + hi) >> 1;
-        if (blk_start[mid] <= (int)blockIdx.x) lo = mid; else hi = mid;
+        if (offsets[mid] <= i) lo = mid; else hi = mid;
     }
+    return lo;
+}
+
+// This workgroup's chunk: its first event in the arrays, how many it holds and
+// the windows of its first and last event (mostly the same one).
+struct Chunk {
+    int lo, hi, n;
+    long long base;
+};
+
+__device__ __forceinline__ Chunk chunk_of(const long long* __restrict__ offsets, int B) {
     Chunk c;
-    c.w = lo;
-    c.first = (long long)((int)blockIdx.x - blk_start[lo]) * kPreChunk;
-    c.base = offsets[lo] + c.first;
-    c.n = (int)min((long long)kPreChunk, offsets[lo + 1] - c.base);
+    c.base = offsets[0] + (long long)blockIdx.x * kPreChunk;
+    c.n = (int)min((long long)kPreChunk, offsets[B] - c.base);  // >= 1
+    c.lo = window_at(offsets, 0, B, c.base);
+    const long long last = c.base + c.n - 1;
+    c.hi = offsets[c.lo + 1] > last ? c.lo : window_at(offsets, c.lo + 1, B, last);
     return c;
+}
+
+__device__ __forceinline__ int window_of(const Chunk& c, const long long* __restrict__ offsets, int e) {
+    return c.lo == c.hi ? c.lo : window_at(offsets, c.lo, c.hi + 1, c.base + e);
 }
 
 // Pixel floor(y) W + floor(x), or -1 outside the sensor.
@@ -80,15 +93,23 @@ __device__ __forceinline__ void store_keep(const Chunk& c, unsigned long long* _
 
 // keep words of the resample: a counter-based draw per event
 __global__ __launch_bounds__(kPreThreads) void k_resample_keep(const long long* __restrict__ offsets, int B,
-                                                               const int* __restrict__ blk_start,
                                                                unsigned long long seed, unsigned thresh24,
                                                                unsigned long long* __restrict__ words,
                                                                int* __restrict__ blk_cnt) {
-    const Chunk c = chunk_of(blk_start, B, offsets);
-    store_keep(c, words, blk_cnt, [&](int e, int) {
-        const unsigned long long ctr = ((unsigned long long)c.w << 32) + (unsigned long long)(c.first + e) + 1ull;
+    const Chunk c = chunk_of(offsets, B);
+    const auto keep = [&](int w, long long k) {  // event k of window w
+        const unsigned long long ctr = ((unsigned long long)w << 32) + (unsigned long long)k + 1ull;
         return (unsigned)(splitmix64(seed + ctr * 0x9E3779B97F4A7C15ull) >> 40) < thresh24;
-    });
+    };
+    if (c.lo == c.hi) {
+        const long long first = c.base - offsets[c.lo];
+        store_keep(c, words, blk_cnt, [&](int e, int) { return keep(c.lo, first + e); });
+    } else {
+        store_keep(c, words, blk_cnt, [&](int e, int) {
+            const int w = window_of(c, offsets, e);
+            return keep(w, c.base + e - offsets[w]);
+        });
+    }
 }
 
 // ---------------------------------------------------------------- hot pixels
@@ -113,74 +134,117 @@ __device__ __forceinline__ void chunk_pixels(const Chunk& c, const float* __rest
     }
 }
 
+// A chunk's counters, one per band of each of its windows, lie together from
+// its first window's.  They are counted in LDS where at most kBandLds are;
+// with more (many small windows) each gets a few events only, and these go to
+// the counters in memory.
+constexpr int kBandLds = 2048;
+static_assert(kMaxBands <= kBandLds, "a window's bands");
+__device__ __forceinline__ long long chunk_bands(const Chunk& c, int nb) { return (long long)(c.hi - c.lo + 1) * nb; }
+
+// Counter of the band of this thread's event j, from the chunk's first one.
+__device__ __forceinline__ int band_at(const Chunk& c, const long long* __restrict__ offsets, int j, int nb, int pix) {
+    return (window_of(c, offsets, j * kPreThreads + (int)threadIdx.x) - c.lo) * nb + pix / kBandPx;
+}
+
 __global__ __launch_bounds__(kPreThreads) void k_band_count(const float* __restrict__ x, const float* __restrict__ y,
                                                             const long long* __restrict__ offsets, int B,
-                                                            const int* __restrict__ blk_start, int W, int H, int nb,
-                                                            int* __restrict__ cnt) {
-    __shared__ int s_cnt[kMaxBands];
-    const Chunk c = chunk_of(blk_start, B, offsets);
-    for (int k = threadIdx.x; k < nb; k += kPreThreads) s_cnt[k] = 0;
+                                                            int W, int H, int nb, int* __restrict__ cnt) {
+    __shared__ int s_cnt[kBandLds];
+    const Chunk c = chunk_of(offsets, B);
+    const long long nc = chunk_bands(c, nb);
+    int* const out = cnt + (long long)c.lo * nb;
     int pix[kPreIter];
     chunk_pixels(c, x, y, W, H, pix);
+    if (nc > kBandLds) {
+#pragma unroll
+        for (int j = 0; j < kPreIter; ++j)
+            if (pix[j] >= 0) atomicAdd(&out[band_at(c, offsets, j, nb, pix[j])], 1);
+        return;
+    }
+    for (int k = threadIdx.x; k < nc; k += kPreThreads) s_cnt[k] = 0;
     __syncthreads();
 #pragma unroll
     for (int j = 0; j < kPreIter; ++j)
-        if (pix[j] >= 0) atomicAdd(&s_cnt[pix[j] / kBandPx], 1);
+        if (pix[j] >= 0) atomicAdd(&s_cnt[band_at(c, offsets, j, nb, pix[j])], 1);
     __syncthreads();
-    for (int k = threadIdx.x; k < nb; k += kPreThreads)
-        if (s_cnt[k]) atomicAdd(&cnt[(long long)c.w * nb + k], s_cnt[k]);
+    for (int k = threadIdx.x; k < nc; k += kPreThreads)
+        if (s_cnt[k]) atomicAdd(&out[k], s_cnt[k]);
 }
 
 __global__ __launch_bounds__(kPreThreads) void k_band_scatter(const float* __restrict__ x, const float* __restrict__ y,
                                                               const long long* __restrict__ offsets, int B,
-                                                              const int* __restrict__ blk_start, int W, int H, int nb,
-                                                              long long* __restrict__ cursor,
+                                                              int W, int H, int nb, long long* __restrict__ cursor,
                                                               uint16_t* __restrict__ list) {
-    __shared__ int s_cnt[kMaxBands];
-    __shared__ long long s_base[kMaxBands];
-    const Chunk c = chunk_of(blk_start, B, offsets);
-    for (int k = threadIdx.x; k < nb; k += kPreThreads) s_cnt[k] = 0;
-    int pix[kPreIter], rank[kPreIter];
+    __shared__ int s_cnt[kBandLds];
+    __shared__ long long s_base[kBandLds];
+    const Chunk c = chunk_of(offsets, B);
+    const long long nc = chunk_bands(c, nb);
+    unsigned long long* const cur = (unsigned long long*)cursor + (long long)c.lo * nb;
+    int pix[kPreIter], at[kPreIter], rank[kPreIter];
     chunk_pixels(c, x, y, W, H, pix);
-    __syncthreads();
+    if (nc > kBandLds) {
 #pragma unroll
-    for (int j = 0; j < kPreIter; ++j)
-        if (pix[j] >= 0) rank[j] = atomicAdd(&s_cnt[pix[j] / kBandPx], 1);
-    __syncthreads();
-    for (int k = threadIdx.x; k < nb; k += kPreThreads)
-        if (s_cnt[k])
-            s_base[k] = (long long)atomicAdd((unsigned long long*)&cursor[(long long)c.w * nb + k],
-                                             (unsigned long long)s_cnt[k]);
-    __syncthreads();
-#pragma unroll
-    for (int j = 0; j < kPreIter; ++j)
-        if (pix[j] >= 0) list[s_base[pix[j] / kBandPx] + rank[j]] = (uint16_t)(pix[j] % kBandPx);
-}
-
-// One workgroup per band of a window: its pixel counts in LDS, then one bit
-// per pixel that holds more than max_count events.  (After the scatter a
-// band's cursor is its end, the one before it its start.)
-__global__ __launch_bounds__(kPreThreads) void k_band_hot(const long long* __restrict__ cursor,
-                                                          const uint16_t* __restrict__ list, int nb, int words_w,
-                                                          unsigned max_count, unsigned long long* __restrict__ hot) {
-    __shared__ __align__(16) unsigned s_cnt[kBandPx];
-    const long long k = blockIdx.x;
-    const int band = (int)(k % nb);
-    unsigned long long* const out = hot + k / nb * words_w + band * (kBandPx / 64);
-    const int nw = min(kBandPx / 64, words_w - band * (kBandPx / 64));
-    const long long beg = k ? cursor[k - 1] : 0, end = cursor[k];
-    if (end - beg <= (long long)max_count) {  // no pixel can hold more
-        for (int i = threadIdx.x; i < nw; i += kPreThreads) out[i] = 0ull;
+        for (int j = 0; j < kPreIter; ++j)
+            if (pix[j] >= 0)
+                list[atomicAdd(&cur[band_at(c, offsets, j, nb, pix[j])], 1ull)] = (uint16_t)(pix[j] % kBandPx);
         return;
     }
-    for (int i = threadIdx.x; i < kBandPx / 4; i += kPreThreads)
-        reinterpret_cast<uint4*>(s_cnt)[i] = make_uint4(0u, 0u, 0u, 0u);
+    for (int k = threadIdx.x; k < nc; k += kPreThreads) s_cnt[k] = 0;
     __syncthreads();
-    for (long long i = beg + threadIdx.x; i < end; i += kPreThreads) atomicAdd(&s_cnt[list[i]], 1u);
+#pragma unroll
+    for (int j = 0; j < kPreIter; ++j)
+        if (pix[j] >= 0) {
+            at[j] = band_at(c, offsets, j, nb, pix[j]);
+            rank[j] = atomicAdd(&s_cnt[at[j]], 1);
+        }
     __syncthreads();
-    for (int i = threadIdx.x >> 6; i < nw; i += kPreThreads / 64) {
-        const unsigned long long m = __ballot(s_cnt[i * 64 + (threadIdx.x & 63)] > max_count);
-        if ((threadIdx.x & 63) == 0) out[i] = m;
+    for (int k = threadIdx.x; k < nc; k += kPreThreads)
+        if (s_cnt[k]) s_base[k] = (long long)atomicAdd(&cur[k], (unsigned long long)s_cnt[k]);
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kPreIter; ++j)
+        if (pix[j] >= 0) list[s_base[at[j]] + rank[j]] = (uint16_t)(pix[j] % kBandPx);
+}
+
+// The pixel counts of a band of a window in LDS, then one bit per pixel that
+// holds more than max_count events.  (After the scatter a band's cursor is its
+// end, the one before it its start.)  A workgroup takes `per` bands: one, or
+// with many small windows kPreThreads / 64 or more, of which each wave looks at its
+// own and clears them where no pixel can hold more than max_count (65535 windows of
+// 6 bands: a workgroup for each would be launched to write 2 KB).
+__global__ __launch_bounds__(kPreThreads) void k_band_hot(const long long* __restrict__ cursor,
+                                                          const uint16_t* __restrict__ list, long long nbands, int per,
+                                                          int nb, int words_w, unsigned max_count,
+                                                          unsigned long long* __restrict__ hot) {
+    __shared__ __align__(16) unsigned s_cnt[kBandPx];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const long long k0 = (long long)blockIdx.x * per;
+    const auto words = [&](long long k) {  // a band's words, and how many
+        const int at = (int)(k % nb) * (kBandPx / 64);
+        return std::pair<unsigned long long*, int>(hot + k / nb * words_w + at, min(kBandPx / 64, words_w - at));
+    };
+    const auto first = [&](long long k) { return k ? cursor[k - 1] : 0ll; };
+    for (int i = per == 1 ? 0 : wave; i < per && k0 + i < nbands; i += kPreThreads / 64) {
+        const long long k = k0 + i;
+        if (cursor[k] - first(k) > (long long)max_count) continue;
+        const auto [out, nw] = words(k);  // no pixel can hold more
+        for (int q = per == 1 ? threadIdx.x : lane; q < nw; q += per == 1 ? kPreThreads : 64) out[q] = 0ull;
+    }
+    for (int i = 0; i < per && k0 + i < nbands; ++i) {
+        const long long k = k0 + i, beg = first(k), end = cursor[k];
+        if (end - beg <= (long long)max_count) continue;
+        __syncthreads();  // the band before has been read
+        for (int q = threadIdx.x; q < kBandPx / 4; q += kPreThreads)
+            reinterpret_cast<uint4*>(s_cnt)[q] = make_uint4(0u, 0u, 0u, 0u);
+        __syncthreads();
+        for (long long q = beg + threadIdx.x; q < end; q += kPreThreads) atomicAdd(&s_cnt[list[q]], 1u);
+        __syncthreads();
+        const auto [out, nw] = words(k);
+        for (int q = wave; q < nw; q += kPreThreads / 64) {
+            const unsigned long long m = __ballot(s_cnt[q * 64 + lane] > max_count);
+            if (lane == 0) out[q] = m;
+        }
     }
 }
 
@@ -188,34 +252,36 @@ __global__ __launch_bounds__(kPreThreads) void k_band_hot(const long long* __res
 // the sort takes.
 __global__ __launch_bounds__(kPreThreads) void k_pixel_counts(const float* __restrict__ x, const float* __restrict__ y,
                                                               const long long* __restrict__ offsets, int B,
-                                                              const int* __restrict__ blk_start, int W, int H,
-                                                              unsigned* __restrict__ counts) {
-    const Chunk c = chunk_of(blk_start, B, offsets);
+                                                              int W, int H, unsigned* __restrict__ counts) {
+    const Chunk c = chunk_of(offsets, B);
     int pix[kPreIter];
     chunk_pixels(c, x, y, W, H, pix);
 #pragma unroll
     for (int j = 0; j < kPreIter; ++j)
-        if (pix[j] >= 0) atomicAdd(&counts[(long long)c.w * W * H + pix[j]], 1u);
+        if (pix[j] >= 0)
+            atomicAdd(&counts[(long long)window_of(c, offsets, j * kPreThreads + (int)threadIdx.x) * W * H + pix[j]], 1u);
 }
 
 // Keep words of the hot-pixel filter, from the bitmap or from the counters.
 __global__ __launch_bounds__(kPreThreads) void k_hot_keep(const float* __restrict__ x, const float* __restrict__ y,
                                                           const long long* __restrict__ offsets, int B,
-                                                          const int* __restrict__ blk_start, int W, int H, int words_w,
+                                                          int W, int H, int words_w,
                                                           const unsigned long long* __restrict__ hot,
                                                           const unsigned* __restrict__ counts, unsigned max_count,
                                                           unsigned long long* __restrict__ words,
                                                           int* __restrict__ blk_cnt) {
-    const Chunk c = chunk_of(blk_start, B, offsets);
+    const Chunk c = chunk_of(offsets, B);
     int pix[kPreIter];
     chunk_pixels(c, x, y, W, H, pix);
     bool hot_px[kPreIter];
 #pragma unroll
     for (int j = 0; j < kPreIter; ++j) {
         hot_px[j] = false;
-        if (pix[j] >= 0)
-            hot_px[j] = hot ? (hot[(long long)c.w * words_w + (pix[j] >> 6)] >> (pix[j] & 63)) & 1ull
-                            : counts[(long long)c.w * W * H + pix[j]] > max_count;
+        if (pix[j] >= 0) {
+            const long long w = window_of(c, offsets, j * kPreThreads + (int)threadIdx.x);
+            hot_px[j] = hot ? (hot[w * words_w + (pix[j] >> 6)] >> (pix[j] & 63)) & 1ull
+                            : counts[w * W * H + pix[j]] > max_count;
+        }
     }
     store_keep(c, words, blk_cnt, [&](int, int j) { return !hot_px[j]; });
 }
@@ -223,40 +289,58 @@ __global__ __launch_bounds__(kPreThreads) void k_hot_keep(const float* __restric
 // ---------------------------------------------------------------- compaction
 
 // Exclusive prefix sums of n counts and their total (out[n]): one workgroup,
-// a run of consecutive counts per thread.
+// four counts a thread and round, the next round's loaded before the scan.
 __global__ __launch_bounds__(1024) void k_scan(const int* __restrict__ in, long long n, long long* __restrict__ out) {
-    __shared__ long long s_wave[16];
+    __shared__ long long s_wave[2][16];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const long long per = (n + 1023) / 1024;
-    const long long a = min(n, per * threadIdx.x), b = min(n, a + per);
-    long long v = 0;
-    for (long long k = a; k < b; ++k) v += in[k];
-    long long incl = v;
+    const auto load = [&](long long k) {
+        if (k + 4 <= n) return *reinterpret_cast<const int4*>(in + k);
+        return make_int4(k < n ? in[k] : 0, k + 1 < n ? in[k + 1] : 0, k + 2 < n ? in[k + 2] : 0, 0);
+    };
+    long long total = 0;
+    int turn = 0;
+    int4 next = load(4 * threadIdx.x);
+    for (long long base = 0; base < n; base += 4096, turn ^= 1) {
+        const long long k = base + 4 * threadIdx.x;
+        const int4 c = next;
+        next = load(k + 4096);
+        const long long v = (long long)c.x + c.y + c.z + c.w;
+        long long incl = v;
 #pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const long long u = __shfl_up(incl, o, 64);
-        if (lane >= o) incl += u;
+        for (int o = 1; o < 64; o <<= 1) {
+            const long long u = __shfl_up(incl, o, 64);
+            if (lane >= o) incl += u;
+        }
+        // two rows: the one written here was last read before the barrier of
+        // the round between
+        if (lane == 63) s_wave[turn][wave] = incl;
+        __syncthreads();
+        long long run = total + incl - v;
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            const long long a = s_wave[turn][j];
+            if (j < wave) run += a;
+            total += a;
+        }
+        const int part[4] = {c.x, c.y, c.z, c.w};
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            if (k + j < n) out[k + j] = run;
+            run += part[j];
+        }
     }
-    if (lane == 63) s_wave[wave] = incl;
-    __syncthreads();
-    long long run = incl - v;
-    for (int k = 0; k < wave; ++k) run += s_wave[k];
-    for (long long k = a; k < b; ++k) {
-        out[k] = run;
-        run += in[k];
-    }
-    if (threadIdx.x == 1023) out[n] = run;  // its run ends at n
+    if (threadIdx.x == 0) out[n] = total;
 }
 
-// The kept events in order, and the windows' new offsets (a window starts
-// with its first chunk).
+// The kept events in order.
 __global__ __launch_bounds__(kPreThreads) void k_keep_scatter(
     const float* __restrict__ x, const float* __restrict__ y, const float* __restrict__ t,
-    const long long* __restrict__ offsets, int B, const int* __restrict__ blk_start,
-    const unsigned long long* __restrict__ words, const long long* __restrict__ blk, float sx, float sy,
+    const long long* __restrict__ offsets, int B, const unsigned long long* __restrict__ words,
+    const long long* __restrict__ blk, float sx, float sy,
     float* __restrict__ xo, float* __restrict__ yo, float* __restrict__ to) {
     __shared__ int s_pre[kPreWords];
-    const Chunk c = chunk_of(blk_start, B, offsets);
+    const long long first = offsets[0] + (long long)blockIdx.x * kPreChunk;
+    const int n = (int)min((long long)kPreChunk, offsets[B] - first);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const unsigned long long* const mine = words + (long long)blockIdx.x * kPreWords;
     if (threadIdx.x < 64) {  // one wave: kept events before each word, two words a lane
@@ -276,9 +360,9 @@ __global__ __launch_bounds__(kPreThreads) void k_keep_scatter(
     for (int j = 0; j < kPreIter; ++j) {
         const int e = j * kPreThreads + (int)threadIdx.x, wd = j * (kPreThreads / 64) + wave;
         const unsigned long long m = mine[wd];
-        if (e < c.n && (m >> lane & 1ull)) {
+        if (e < n && (m >> lane & 1ull)) {
             const long long d = base + s_pre[wd] + __popcll(m & ((1ull << lane) - 1ull));
-            const long long i = c.base + e;
+            const long long i = first + e;
             xo[d] = x[i] * sx;
             yo[d] = y[i] * sy;
             to[d] = t[i];
@@ -287,31 +371,49 @@ __global__ __launch_bounds__(kPreThreads) void k_keep_scatter(
 }
 static_assert(kPreWords == 128, "two words of a chunk per lane of the scanning wave");
 
-__global__ void k_keep_offsets(const int* __restrict__ blk_start, int B, const long long* __restrict__ blk,
-                               long long* __restrict__ off_out) {
-    const int w = blockIdx.x * blockDim.x + threadIdx.x;
-    if (w <= B) off_out[w] = blk[blk_start[w]];
+// The windows' new offsets: the kept events before each window's first, by
+// kOffLanes lanes a window (a chain of a lane's loads takes 12 us, this 4).
+constexpr int kOffLanes = 16;
+__global__ __launch_bounds__(256) void k_keep_offsets(const long long* __restrict__ offsets, int B,
+                                                      const unsigned long long* __restrict__ words,
+                                                      const long long* __restrict__ blk,
+                                                      long long* __restrict__ off_out) {
+    const long long w = ((long long)blockIdx.x * 256 + threadIdx.x) / kOffLanes;
+    const int part = threadIdx.x % kOffLanes;
+    if (w > B) return;
+    const long long i = offsets[w] - offsets[0], b = i / kPreChunk;
+    const int e = (int)(i % kPreChunk);  // 0 where there is no chunk b
+    const unsigned long long* const mine = words + b * kPreWords;
+    int v = 0;
+#pragma unroll
+    for (int j = 0; j < kPreWords / kOffLanes; ++j) {
+        const int k = j * kOffLanes + part, n = e - k * 64;  // bits of word k that lie before
+        if (n > 0) v += __popcll(mine[k] & (n < 64 ? (1ull << n) - 1ull : ~0ull));
+    }
+#pragma unroll
+    for (int o = kOffLanes / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, kOffLanes);
+    if (part == 0) off_out[w] = blk[b] + v;
 }
 
 hipError_t launch_compact(hipStream_t s, const float* x, const float* y, const float* t, const long long* offsets,
-                          int B, const int* blk_start, int nblk, const unsigned long long* words, const int* blk_cnt,
+                          int B, long long nblk, const unsigned long long* words, const int* blk_cnt,
                           long long* blk, float sx, float sy, float* xo, float* yo, float* to, long long* off_out) {
     k_scan<<<1, 1024, 0, s>>>(blk_cnt, nblk, blk);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (nblk > 0) {
-        k_keep_scatter<<<nblk, kPreThreads, 0, s>>>(x, y, t, offsets, B, blk_start, words, blk, sx, sy, xo, yo, to);
+        k_keep_scatter<<<(unsigned)nblk, kPreThreads, 0, s>>>(x, y, t, offsets, B, words, blk, sx, sy, xo, yo, to);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    k_keep_offsets<<<(B + 1 + 255) / 256, 256, 0, s>>>(blk_start, B, blk, off_out);
+    k_keep_offsets<<<(unsigned)((((long long)B + 1) * kOffLanes + 255) / 256), 256, 0, s>>>(offsets, B, words, blk, off_out);
     return hipGetLastError();
 }
 
-hipError_t launch_resample_keep(hipStream_t s, const long long* offsets, int B, const int* blk_start, int nblk,
+hipError_t launch_resample_keep(hipStream_t s, const long long* offsets, int B, long long nblk,
                                 unsigned long long seed, unsigned thresh24, unsigned long long* words, int* blk_cnt) {
     if (nblk <= 0) return hipSuccess;
-    k_resample_keep<<<nblk, kPreThreads, 0, s>>>(offsets, B, blk_start, seed, thresh24, words, blk_cnt);
+    k_resample_keep<<<(unsigned)nblk, kPreThreads, 0, s>>>(offsets, B, seed, thresh24, words, blk_cnt);
     return hipGetLastError();
 }
 
@@ -320,26 +422,31 @@ int hot_bands(int W, int H) {
     return nb <= kMaxBands ? (int)nb : 0;
 }
 
+constexpr long long kManyBands = 16384;  // 64 workgroups of k_band_hot per CU
+
 hipError_t launch_hot_keep(hipStream_t s, const float* x, const float* y, const long long* offsets, int B,
-                           const int* blk_start, int nblk, int W, int H, int nb, int* cnt, long long* cursor,
+                           long long nblk, int W, int H, int nb, int* cnt, long long* cursor,
                            uint16_t* list, unsigned long long* hot, unsigned* counts, unsigned max_count,
                            unsigned long long* words, int* blk_cnt) {
     if (nblk <= 0) return hipSuccess;
     const int words_w = (int)(((long long)W * H + 63) / 64);
     hipError_t e;
     if (nb > 0) {
-        k_band_count<<<nblk, kPreThreads, 0, s>>>(x, y, offsets, B, blk_start, W, H, nb, cnt);
+        k_band_count<<<(unsigned)nblk, kPreThreads, 0, s>>>(x, y, offsets, B, W, H, nb, cnt);
         if ((e = hipGetLastError()) != hipSuccess) return e;
         k_scan<<<1, 1024, 0, s>>>(cnt, (long long)B * nb, cursor);
         if ((e = hipGetLastError()) != hipSuccess) return e;
-        k_band_scatter<<<nblk, kPreThreads, 0, s>>>(x, y, offsets, B, blk_start, W, H, nb, cursor, list);
+        k_band_scatter<<<(unsigned)nblk, kPreThreads, 0, s>>>(x, y, offsets, B, W, H, nb, cursor, list);
         if ((e = hipGetLastError()) != hipSuccess) return e;
-        k_band_hot<<<(unsigned)(B * nb), kPreThreads, 0, s>>>(cursor, list, nb, words_w, max_count, hot);
+        const long long nbands = (long long)B * nb;
+        const int per = nbands > kManyBands ? kPreThreads / 64 * (int)(1 + (nbands >> 25)) : 1;  // at most 2^21 workgroups
+        k_band_hot<<<(unsigned)((nbands + per - 1) / per), kPreThreads, 0, s>>>(cursor, list, nbands, per, nb, words_w,
+                                                                               max_count, hot);
     } else {
-        k_pixel_counts<<<nblk, kPreThreads, 0, s>>>(x, y, offsets, B, blk_start, W, H, counts);
+        k_pixel_counts<<<(unsigned)nblk, kPreThreads, 0, s>>>(x, y, offsets, B, W, H, counts);
     }
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    k_hot_keep<<<nblk, kPreThreads, 0, s>>>(x, y, offsets, B, blk_start, W, H, words_w, nb > 0 ? hot : nullptr, counts,
+    k_hot_keep<<<(unsigned)nblk, kPreThreads, 0, s>>>(x, y, offsets, B, W, H, words_w, nb > 0 ? hot : nullptr, counts,
                                             max_count, words, blk_cnt);
     return hipGetLastError();
 }
