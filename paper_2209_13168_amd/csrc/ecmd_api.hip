@@ -1698,10 +1698,11 @@ int ecmd_downsample(ecmd_ctx* c, const ecmd_sensor* sensor, const float* x, cons
         memcpy(off.data(), offsets, sizeof(long long) * (B + 1));
     }
     std::vector<int> blk(B + 1, 0);
+    const int chunk = down_chunk(off[B] - off[0], B);
     for (int w = 0; w < B; ++w) {
         long long n = off[w + 1] - off[w];
         if (n < 0 || off[0] < 0) return fail(c, ECMD_EINVAL, "offsets must be non-decreasing and >= 0");
-        blk[w + 1] = blk[w] + (int)((n + kDownChunk - 1) / kDownChunk);
+        blk[w + 1] = blk[w] + (int)((n + chunk - 1) / chunk);
     }
     const long long n_total = off[B];
     if (n_total > 0 && (!x || !y)) return fail(c, ECMD_EINVAL, "NULL event arrays");
@@ -1719,7 +1720,7 @@ int ecmd_downsample(ecmd_ctx* c, const ecmd_sensor* sensor, const float* x, cons
         dout = c->img.as<uint16_t>();
     }
     HIPCHK(c, launch_downsample(c->stream, (const float*)px, (const float*)py, (const long long*)po, B,
-                                sensor->width, sensor->height, c->blk.as<int>(), blk[B], kDownChunk,
+                                sensor->width, sensor->height, c->blk.as<int>(), blk[B], chunk,
                                 c->counts.as<unsigned>(), dout));
     if (!(flags & ECMD_DEVICE_PTR))
         HIPCHK(c, hipMemcpyAsync(out, dout, sizeof(uint16_t) * (size_t)B * 4096, hipMemcpyDeviceToHost, c->stream));

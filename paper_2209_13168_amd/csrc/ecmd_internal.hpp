@@ -262,7 +262,8 @@ hipError_t launch_probe_sums(hipStream_t s, int m, int T, const long long* seg_o
 hipError_t launch_probe_pixels(hipStream_t s, const float* x, const float* y, const float* t_rel,
                                long long n, float tau, float d, int W, int H, float cx, float cy,
                                int* pix);
-constexpr int kDownChunk = 32768;  // events per workgroup of launch_downsample (its `chunk`)
+// Events per workgroup of launch_downsample (its `chunk`) for B windows of n_events in all.
+int down_chunk(long long n_events, int B);
 hipError_t launch_downsample(hipStream_t s, const float* x, const float* y, const long long* offsets,
                              int B, int W, int H, const int* blk_start, int nblk, int chunk,
                              unsigned* counts, uint16_t* out);

@@ -2775,9 +2775,20 @@ __device__ __forceinline__ uint16_t bf16_rne(float v) {
 
 constexpr int kGrid = 64;
 
-// A workgroup's chunk is large (kDownChunk events): it clears and adds up to
-// 4096 counters however few events it bins (64 windows, 20M events: chunks of
-// 4096 events 81 us, of 32768 48 us).
+// A workgroup clears and adds up to 4096 counters however few events it bins,
+// so with many events its chunk is large; with few it is smaller, or the chip
+// stays empty; and for windows that hardly fill a workgroup's counters one of
+// 256 threads is started sooner.  us a call with 256 threads and 4096 events,
+// 1024 and 8192, 1024 and 32768: one window of 100k events 57.1, 56.0, 62.3, of
+// 500k 58.7, 55.5, 62.0; 16 of 300k 73.1, 66.3, 68.5; 64 of 100k 78.7, 69.6,
+// 71.3; 16 of 1M 104, 84, 77; 64 of 400k 133, 102, 96; 512 of 5000 73.0, 66.2,
+// 66.0; 4096 of 1000 122, 130, 129; 4096 of 100 98, 111, 111.
+constexpr int kDownSmall = 4096, kDownMid = 8192, kDownLarge = 32768;
+constexpr long long kDownMany = 8000000, kDownPerWindow = 2048;
+int down_chunk(long long n_events, int B) {
+    return n_events < kDownPerWindow * B ? kDownSmall : n_events < kDownMany ? kDownMid : kDownLarge;
+}
+
 __global__ __launch_bounds__(1024) void k_downsample_count(const float* __restrict__ x,
                                                           const float* __restrict__ y,
                                                           const long long* __restrict__ offsets, int B,
@@ -2817,7 +2828,7 @@ hipError_t launch_downsample(hipStream_t s, const float* x, const float* y, cons
                              uint16_t* out) {
     if (B <= 0) return hipSuccess;
     if (nblk > 0) {
-        k_downsample_count<<<nblk, 1024, 0, s>>>(x, y, offsets, B, W, H, blk_start, chunk, counts);
+        k_downsample_count<<<nblk, chunk == kDownSmall ? 256 : 1024, 0, s>>>(x, y, offsets, B, W, H, blk_start, chunk, counts);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
