@@ -479,26 +479,58 @@ static int tile_budget(ecmd_ctx* c) { return tile_budget_for(c->max_lds); }
 // 7120; 640x480, 16 of 50k 4510 and 3430, 16 of 200k 5910 and 5610, 32 of 200k
 // 9280 and 9670; 128x128 (4 tiles either way), 16 of 10k 1830 and 1080, 64 of
 // 50k 2620 and 2110.
+// Where such a call leaves most of the chip empty because it has few items, the
+// tiles of the larger calls are taken all the same if they are several times as
+// many: a search whose windows hold kLargeWindow events on the mean and would
+// get three times the tiles (whole LDS and small tiles: 640x480, one window of
+// 500k events 1688 and 1676, of 700k 2085 and 1904, of 3M 6293 and 5727, three
+// of 1.1M 3723 and 3565; but one of 1M with seven of 100k 3275 and 3730, and
+// 346x260 with twice the tiles, one of 3M 6807 and 7068), and a probe of few
+// intervals (1M events, 346x260 in 4 and 8 tiles: 1 interval 1604 and 1417, 16
+// 361 and 358, 20 335 and 379; 640x480 in 8 and 24: 1 1933 and 1311, 16 360 and
+// 344, 20 330 and 339; 200k events, 8 intervals 180 and 182).
 constexpr int kMaxSmallTiles = 24;
 constexpr long long kFewEvents = 3500000;
+constexpr long long kLargeWindow = 600000;
+constexpr long long kLargeProbe = 300000;
+constexpr int kProbeItems = 64;
+
+// What a call brings, for its tiling.
+struct Load {
+    long long n_events;
+    int windows;
+    int intervals;  // of a probe (0: points, or a search)
+};
 
 static bool choose_tiling(size_t max_lds, const ecmd_tuning& tu, int W, int H, float cx, float cy, int npol,
-                          long long n_events, Geometry& g, int& nt, int& budget) {
+                          const Load& load, Geometry& g, int& nt, int& budget) {
     const int full = tile_budget_for(max_lds);
     if (tu.tile_px > 0 || tu.eval_threads > 0) {
         budget = tu.tile_px > 0 ? std::min(tu.tile_px, full) : full;
         nt = tu.eval_threads > 0 ? tu.eval_threads : 1024;
         return plan_geometry(W, H, cx, cy, budget, npol, g);
     }
-    const int divs[] = {3, 2}, nts[] = {512, 512};
-    for (int k = 0; k < 2 && n_events >= kFewEvents; ++k) {
-        budget = tile_budget_for(max_lds / divs[k]);
-        nt = nts[k];
-        if (plan_geometry(W, H, cx, cy, budget, npol, g) && g.nsp <= kMaxSmallTiles) return true;
-    }
-    budget = full;
-    nt = 1024;
-    return plan_geometry(W, H, cx, cy, budget, npol, g);
+    const auto whole = [&] {
+        budget = full;
+        nt = 1024;
+        return plan_geometry(W, H, cx, cy, full, npol, g);
+    };
+    const auto small = [&] {
+        const int divs[] = {3, 2};
+        for (int div : divs) {
+            budget = tile_budget_for(max_lds / div);
+            nt = 512;
+            if (plan_geometry(W, H, cx, cy, budget, npol, g) && g.nsp <= kMaxSmallTiles) return true;
+        }
+        return false;
+    };
+    if (load.n_events >= kFewEvents) return small() || whole();
+    if (!whole()) return false;
+    const bool probe = load.intervals > 0;
+    if (load.n_events < (probe ? kLargeProbe : kLargeWindow * load.windows)) return true;
+    const long long T = g.T;
+    if (small() && (probe ? load.intervals * T <= kProbeItems * (g.T / T - 1) : g.T >= 3 * T)) return true;
+    return whole();
 }
 
 // Persistent workgroup count of the evaluation kernel for `lds` bytes of
@@ -579,7 +611,8 @@ static int run_search(ecmd_ctx* c, const ecmd_sensor* sensor, Inputs& in, int B,
     const long long n_events = c->h_off[B] - c->h_off[0];
     Geometry g;
     int nt = 0, budget = 0;
-    if (!choose_tiling(c->max_lds, c->tune, W, H, sensor->foe_x, sensor->foe_y, npol, n_events, g, nt, budget))
+    if (!choose_tiling(c->max_lds, c->tune, W, H, sensor->foe_x, sensor->foe_y, npol, Load{n_events, B, 0}, g, nt,
+                       budget))
         return fail(c, ECMD_EINVAL, "sensor %dx%d needs more than %d tiles", W, H, kMaxTiles / npol);
     Timers tm(c);
     HIPCHK(c, c->queues.ensure(sizeof(Queue) * kQueues));
@@ -929,7 +962,8 @@ static int plan_shape(ecmd_ctx* c, const ecmd_sensor* sensor, const ecmd_search*
     const int npol = lim->polarity ? 2 : 1;
     Geometry& g = sh.g;
     int nt = 0, budget = 0;
-    if (!choose_tiling(c->max_lds, c->tune, W, H, sensor->foe_x, sensor->foe_y, npol, lim->max_events, g, nt, budget))
+    if (!choose_tiling(c->max_lds, c->tune, W, H, sensor->foe_x, sensor->foe_y, npol,
+                       Load{lim->max_events, lim->max_windows, 0}, g, nt, budget))
         return fail(c, ECMD_EINVAL, "sensor %dx%d needs more than %d tiles", W, H, kMaxTiles / npol);
     ecmd_plan_limits L2 = *lim;
     // default: twice the grid depth and eight more (a level-synchronous
@@ -1153,7 +1187,7 @@ int ecmd_plan(const ecmd_sensor* sensor, const ecmd_search* search, int32_t pola
     Geometry g;
     int nt = 0, budget = 0;
     if (!choose_tiling(lds_bytes ? (size_t)lds_bytes : (size_t)160 * 1024, tu, sensor->width, sensor->height,
-                       sensor->foe_x, sensor->foe_y, npol, LLONG_MAX, g, nt, budget))
+                       sensor->foe_x, sensor->foe_y, npol, Load{LLONG_MAX, 1, 0}, g, nt, budget))
         return ECMD_EINVAL;
     memset(out, 0, sizeof *out);
     out->L = L;
@@ -1568,7 +1602,8 @@ static int probe_impl(ecmd_ctx* c, const ecmd_sensor* sensor, const float* x, co
     const long long M = (long long)W * H * npol;  // image cells per hypothesis
     Geometry g;
     int nt = 0, budget = 0;
-    if (!choose_tiling(c->max_lds, c->tune, W, H, sensor->foe_x, sensor->foe_y, npol, n, g, nt, budget))
+    if (!choose_tiling(c->max_lds, c->tune, W, H, sensor->foe_x, sensor->foe_y, npol, Load{n, 1, d_b ? m : 0}, g, nt,
+                       budget))
         return fail(c, ECMD_EINVAL, "sensor needs more than %d tiles", kMaxTiles / npol);
     const int T = g.T;
     Inputs in;
