@@ -326,11 +326,11 @@ int ecmd_estimate_stream(ecmd_ctx *ctx, const ecmd_sensor *sensor, const ecmd_ev
  *   max_steps:   frontier steps per launch, rounded up to a multiple of 4
  *                (0 = 2L + 8 for the grid depth L, e.g. 44 for L = 18; a
  *                search of F nodes per step usually needs about L steps);
- *                each costs two rounds of an evaluation (one kernel, two
- *                where node groups are formed) and the frontier (a window
- *                without failed certificates takes a step per round), whose
- *                kernels return at once
- *                when every window has finished;
+ *                each costs two rounds of an evaluation and the frontier (a
+ *                window without failed certificates takes a step per round),
+ *                whose kernels return at once when every window has finished;
+ *                the first L + 8 rounds take one kernel more where node groups
+ *                are formed;
  *   max_events:  events of a launch over all windows, 1 .. 2^40;
  *   max_records: binned event records, guest copies included (0 = the worst
  *                case: max_events times the tiles of one FOE quadrant);

@@ -1026,6 +1026,15 @@ static hipError_t plan_prep(const PlanShape& sh, void* const* b, hipStream_t s, 
                        (float4*)b[PB_EV], nullptr, sh.lim.max_records);
 }
 
+// A plan's rounds are enqueued whether or not a search needs them, and an empty
+// launch costs 3.5 us, so groups are formed in the first L + kNodeRounds rounds:
+// a search takes L steps at most where it expands a level of the grid at a time
+// (13 steps at L = 14, 17 at L = 18), and a few rounds more where certificates
+// fail.  us a launch, 8 windows of 346x260 and 100k events, eps 1e-4, 200 steps:
+// groups in every round 4179, in the first 16, 24, 36 2973, 3025, 3050; 36 steps:
+// 1239 and 1140, 1156, 1178.
+constexpr int kNodeRounds = 8;
+
 // Enqueues a whole batched search of B windows on the context's stream with
 // the plan buffers b (device checks, prep, a fixed number of steps, results).
 static int plan_enqueue(ecmd_ctx* c, const PlanShape& sh, void* const* b, const float* x, const float* y,
@@ -1057,15 +1066,18 @@ static int plan_enqueue(ecmd_ctx* c, const PlanShape& sh, void* const* b, const 
                           InitCheck{(const int*)b[PB_WSTAT], (const int*)b[PB_WERR], (long long)sh.lim.max_records}));
     // rounds as in the synchronous call; a step takes two at most
     const int rounds = 2 * sh.lim.max_steps;
+    // the launch of the node groups, in the first rounds only
+    const int node_rounds = sp.nmax > 0 ? std::min(rounds, sp.L + kNodeRounds) : 0;
     for (int r = 0; r < rounds; ++r) {
         const int parity = r & 1;
         HIPCHK(c, launch_eval(s, g, sh.nb, sh.nt, sh.lds, (const float4*)b[PB_EV], seg_off, (const int*)b[PB_SEG_OWN],
                               wp, hyps, act, items, sh.qcap, &q[parity * kXcd], &q[(1 - parity) * kXcd], part, sp.HS,
                               nullptr));
-        if (sp.nmax > 0)
+        if (r < node_rounds)
             HIPCHK(c, launch_nodes(s, g, sh.nodes_nb, sh.nt, sh.nodes_lds, (const float4*)b[PB_EV], seg_off,
                                    (const int*)b[PB_SEG_OWN], wp, hyps, act, items, sh.qcap, &q[(2 + parity) * kXcd],
                                    &q[(3 - parity) * kXcd], part, sp.HS, (float4*)b[PB_LISTS], sh.mcap));
+        if (r + 1 == node_rounds) sp.nmax = 0;  // from here on no groups are formed
         HIPCHK(c, launch_frontier(s, sp, wp, B, T, seg_off, st, (Node*)b[PB_FRONT], sel, hyps, act, part, items,
                                   sh.qcap, &q[(1 - parity) * kXcd], (int*)b[PB_NACTIVE]));
         // bin again with the live ranges, at the synchronous call's polling
