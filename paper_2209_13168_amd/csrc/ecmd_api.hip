@@ -962,19 +962,27 @@ static int plan_shape(ecmd_ctx* c, const ecmd_sensor* sensor, const ecmd_search*
     const int npol = lim->polarity ? 2 : 1;
     Geometry& g = sh.g;
     int nt = 0, budget = 0;
-    if (!choose_tiling(c->max_lds, c->tune, W, H, sensor->foe_x, sensor->foe_y, npol,
-                       Load{lim->max_events, lim->max_windows, 0}, g, nt, budget))
-        return fail(c, ECMD_EINVAL, "sensor %dx%d needs more than %d tiles", W, H, kMaxTiles / npol);
+    const auto tiling = [&](long long n_events) {
+        return choose_tiling(c->max_lds, c->tune, W, H, sensor->foe_x, sensor->foe_y, npol,
+                             Load{n_events, lim->max_windows, 0}, g, nt, budget);
+    };
+    // an event's tiles over any range lie in its FOE quadrant (no event
+    // crosses an FOE line), so it has at most that many copies
+    const bool xcut = sensor->foe_x == floorf(sensor->foe_x) && sensor->foe_x > 0.0f && sensor->foe_x < (float)W;
+    const bool ycut = sensor->foe_y == floorf(sensor->foe_y) && sensor->foe_y > 0.0f && sensor->foe_y < (float)H;
+    const auto copies = [&] { return (long long)(xcut ? g.ntx / 2 : g.ntx) * (ycut ? g.nty / 2 : g.nty); };
+    bool fits = tiling(lim->max_events);
+    // a caller's own limit of records was met on the tiles of a large call,
+    // and other cuts cross other events: it keeps them, unless the limit
+    // holds every copy anyway
+    if (fits && lim->max_records > 0 && lim->max_records / copies() < lim->max_events) fits = tiling(LLONG_MAX);
+    if (!fits) return fail(c, ECMD_EINVAL, "sensor %dx%d needs more than %d tiles", W, H, kMaxTiles / npol);
     ecmd_plan_limits L2 = *lim;
     // default: twice the grid depth and eight more (a level-synchronous
     // search needs about L steps; finished steps still cost their rounds' launches)
     if (L2.max_steps == 0) L2.max_steps = min(2 * L + 8, kMaxSteps);
     L2.max_steps = (L2.max_steps + 3) / 4 * 4;  // whole polling blocks of four steps
-    // an event's tiles over any range lie in its FOE quadrant (no event
-    // crosses an FOE line), so it has at most that many copies
-    const bool xcut = sensor->foe_x == floorf(sensor->foe_x) && sensor->foe_x > 0.0f && sensor->foe_x < (float)W;
-    const bool ycut = sensor->foe_y == floorf(sensor->foe_y) && sensor->foe_y > 0.0f && sensor->foe_y < (float)H;
-    const long long per = (long long)(xcut ? g.ntx / 2 : g.ntx) * (ycut ? g.nty / 2 : g.nty);
+    const long long per = copies();
     if (L2.max_records == 0) L2.max_records = L2.max_events * per;
     sh.guests = per > 1;
     sh.lim = L2;
