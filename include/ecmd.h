@@ -167,8 +167,11 @@ typedef struct {
 
 /* Create a context on HIP device `device`, ordering work on `hip_stream`
  * (a hipStream_t; NULL = a blocking stream of default priority that the
- * context creates and owns).  The context owns all device scratch;
- * ecmd_ctx_destroy frees it, together with the device memory of every
+ * context creates and owns).  The context owns all device scratch, 128 to
+ * 192 MiB of it (32 KiB per wave the device holds at once) for the lists of
+ * the searches' node groups: shorter ones, or none and no groups, where
+ * memory runs out, and given back when another buffer of the context needs
+ * it.  ecmd_ctx_destroy frees the scratch, together with the device memory of every
  * network still alive on it (those handles then accept only
  * ecmd_cnn_destroy; every other call on them returns ECMD_EINVAL). */
 int ecmd_ctx_create(ecmd_ctx **out, int device, void *hip_stream);
@@ -349,7 +352,9 @@ typedef struct ecmd_batch_plan ecmd_batch_plan;
 
 /* Allocate a plan on the context for `sensor` and `search` (both copied;
  * the context's tuning at this call applies).  `limits` is read, and its
- * zero fields are replaced by the values used.  The plan's device memory is
+ * zero fields are replaced by the values used.  A plan whose launches may
+ * form node groups has lists for them of its own, as long as the context's
+ * (ecmd_ctx_create).  The plan's device memory is
  * freed by ecmd_plan_destroy, or with the context: the handle then accepts
  * only ecmd_plan_destroy. */
 int ecmd_plan_create(ecmd_ctx *ctx, const ecmd_sensor *sensor, const ecmd_search *search,

@@ -218,6 +218,21 @@ static int fail(ecmd_ctx* c, int code, const char* fmt, ...) {
 
 // ---------------------------------------------------------------- helpers
 
+// At least `bytes` in a buffer.  The lists of the node groups are 128 to 192
+// MiB that a search can do without, so they are given back first where memory
+// runs out (they hold nothing between calls).
+static hipError_t need(ecmd_ctx* c, DevBuf& b, size_t bytes) {
+    hipError_t e = b.ensure(bytes);
+    if (e != hipSuccess) (void)hipGetLastError();  // reported by the return value
+    if (e == hipErrorOutOfMemory && c->lists.p) {
+        (void)hipStreamSynchronize(c->stream);
+        c->lists.release();
+        e = b.ensure(bytes);
+        if (e != hipSuccess) (void)hipGetLastError();
+    }
+    return e;
+}
+
 // Grid point j of depth L (fp64 then fp32; identical to the device's).
 static float host_grid_d(float d_lo, float d_hi, int L, unsigned j) {
     double span = (double)d_hi - (double)d_lo;
@@ -354,7 +369,7 @@ static int stage(ecmd_ctx* c, DevBuf& buf, const void* src, size_t bytes, uint32
         *out = src;
         return ECMD_OK;
     }
-    HIPCHK(c, buf.ensure(bytes));
+    HIPCHK(c, need(c, buf, bytes));
     if (bytes) HIPCHK(c, hipMemcpyAsync(buf.p, src, bytes, hipMemcpyHostToDevice, c->stream));
     *out = buf.p;
     return ECMD_OK;
@@ -381,7 +396,7 @@ static int run_prep(ecmd_ctx* c, const Geometry& g, Inputs& in, int B, float d_l
     const Head hd(B);
     const int chunk = prep_chunk(c->h_off[B] - c->h_off[0]);
     HIPCHK(c, pin(c, B));
-    HIPCHK(c, c->head.ensure(hd.bytes));
+    HIPCHK(c, need(c, c->head, hd.bytes));
     char *const stg = staged(c), *const dev = c->head.as<char>();
     int* const blk = (int*)(stg + hd.blk);
     blk[0] = 0;
@@ -397,13 +412,13 @@ static int run_prep(ecmd_ctx* c, const Geometry& g, Inputs& in, int B, float d_l
     if (!in.tau) in.tau = (const float*)(dev + hd.tau);
     if (in.hseeds) in.seeds = (const float*)(dev + hd.seed);
     in.blk = (const int*)(dev + hd.blk);
-    HIPCHK(c, c->wp.ensure(sizeof(WinParam) * std::max(B, 1)));
+    HIPCHK(c, need(c, c->wp, sizeof(WinParam) * std::max(B, 1)));
     const size_t nctr = prep_counters(B, T);
-    HIPCHK(c, c->cnt_own.ensure(sizeof(int) * nctr));
-    HIPCHK(c, c->seg_off.ensure(sizeof(long long) * (B * T + 1)));
-    HIPCHK(c, c->seg_own.ensure(sizeof(int) * seg_own_words(B, T)));
-    HIPCHK(c, c->cursor.ensure(sizeof(unsigned long long) * nctr));
-    HIPCHK(c, c->err_flag.ensure(sizeof(int) * B));
+    HIPCHK(c, need(c, c->cnt_own, sizeof(int) * nctr));
+    HIPCHK(c, need(c, c->seg_off, sizeof(long long) * (B * T + 1)));
+    HIPCHK(c, need(c, c->seg_own, sizeof(int) * seg_own_words(B, T)));
+    HIPCHK(c, need(c, c->cursor, sizeof(unsigned long long) * nctr));
+    HIPCHK(c, need(c, c->err_flag, sizeof(int) * B));
     HIPCHK(c, launch_begin(c->stream, (const unsigned*)stg, c->head.as<unsigned>(), (int)(hd.bytes / 4),
                            c->cnt_own.as<int>(), (long long)nctr, c->err_flag.as<int>(), B,
                            clear ? c->queues.as<Queue>() : nullptr, clear ? c->n_active.as<int>() : nullptr));
@@ -419,7 +434,7 @@ static int run_prep(ecmd_ctx* c, const Geometry& g, Inputs& in, int B, float d_l
         return fail(c, ECMD_EINVAL, "window %d: an event has a non-finite coordinate or t_rel outside [0, tau]", r.bad);
     // padding: the evaluation kernel prefetches up to kEvalPad records past
     // the end of a segment
-    HIPCHK(c, c->ev.ensure(sizeof(float4) * (size_t)(r.records + kEvalPad)));
+    HIPCHK(c, need(c, c->ev, sizeof(float4) * (size_t)(r.records + kEvalPad)));
     HIPCHK(c, launch_prep(c->stream, 1, g, in.x, in.y, in.t, in.pol, in.off, c->wp.as<WinParam>(), B, in.blk, nblk,
                           chunk, nullptr, nullptr, nullptr, c->cursor.as<unsigned long long>(), c->ev.as<float4>(),
                           nullptr, -1));
@@ -580,6 +595,20 @@ static void set_groups(ecmd_ctx* c, int B, Search& sp, int T) {
 // Bytes of the node groups' lists for nb workgroups of nt threads.
 static size_t list_bytes(int nb, int nt, int cap) { return (size_t)nb * (nt / 64) * node_list_bytes(cap); }
 
+// Lists for nb workgroups of nt threads, as long as memory allows: events per
+// wave (cap), halved until they fit, 0 where not even those of 64 events do
+// (then no groups are formed).
+static hipError_t fit_lists(DevBuf& lists, int nb, int nt, int& cap) {
+    for (cap = kListCap; cap >= 64; cap /= 2) {
+        const hipError_t e = lists.ensure(list_bytes(nb, nt, cap));
+        if (e == hipSuccess) return e;
+        (void)hipGetLastError();  // reported by the return value
+        if (e != hipErrorOutOfMemory) return e;
+    }
+    cap = 0;
+    return hipSuccess;
+}
+
 // Node groups of a search of B windows of T segments and n_events events, on
 // nb workgroups of nt threads (0: none) with lists of mcap events per wave.
 // With fewer than kMinSegments segments most of the chip is idle with or
@@ -615,8 +644,8 @@ static int run_search(ecmd_ctx* c, const ecmd_sensor* sensor, Inputs& in, int B,
                        budget))
         return fail(c, ECMD_EINVAL, "sensor %dx%d needs more than %d tiles", W, H, kMaxTiles / npol);
     Timers tm(c);
-    HIPCHK(c, c->queues.ensure(sizeof(Queue) * kQueues));
-    HIPCHK(c, c->n_active.ensure(sizeof(int)));
+    HIPCHK(c, need(c, c->queues, sizeof(Queue) * kQueues));
+    HIPCHK(c, need(c, c->n_active, sizeof(int)));
     int nblk = 0;
     long long copies = 0;
     tm.begin();
@@ -644,16 +673,20 @@ static int run_search(ecmd_ctx* c, const ecmd_sensor* sensor, Inputs& in, int B,
     const size_t lds = eval_lds_bytes(g.ring_px);
     int nb = 0;
     HIPCHK(c, eval_setup(c, g.ring_px, nt, &nb));
-    set_nodes(sp, B, T, n_events, c->nodes_nb, nt, kListCap);
-    if (sp.nmax > 0) HIPCHK(c, c->lists.ensure(list_bytes(c->nodes_nb, nt, kListCap)));
-    HIPCHK(c, c->state.ensure(sizeof(WinState) * B));
-    HIPCHK(c, c->front.ensure(sizeof(Node) * (size_t)B * sp.CAP));
-    HIPCHK(c, c->sel.ensure(sizeof(Sel) * (size_t)B * sp.F));
-    HIPCHK(c, c->hyps.ensure(sizeof(Hyp) * (size_t)B * sp.HS));
-    HIPCHK(c, c->act.ensure(sizeof(int) * (size_t)B * sp.HS));
+    HIPCHK(c, need(c, c->state, sizeof(WinState) * B));
+    HIPCHK(c, need(c, c->front, sizeof(Node) * (size_t)B * sp.CAP));
+    HIPCHK(c, need(c, c->sel, sizeof(Sel) * (size_t)B * sp.F));
+    HIPCHK(c, need(c, c->hyps, sizeof(Hyp) * (size_t)B * sp.HS));
+    HIPCHK(c, need(c, c->act, sizeof(int) * (size_t)B * sp.HS));
     const int qcap = ((B + kXcd - 1) / kXcd) * sp.HS * T;  // windows w = r (mod kXcd) share queue r
-    HIPCHK(c, c->items.ensure(sizeof(Item) * (size_t)kXcd * qcap));
-    HIPCHK(c, c->part.ensure(sizeof(Part) * (size_t)B * sp.HS * T));
+    HIPCHK(c, need(c, c->items, sizeof(Item) * (size_t)kXcd * qcap));
+    HIPCHK(c, need(c, c->part, sizeof(Part) * (size_t)B * sp.HS * T));
+    int mcap = kListCap;
+    set_nodes(sp, B, T, n_events, c->nodes_nb, nt, mcap);
+    if (sp.nmax > 0) {  // after every buffer that the search cannot do without
+        HIPCHK(c, fit_lists(c->lists, c->nodes_nb, nt, mcap));
+        set_nodes(sp, B, T, n_events, c->nodes_nb, nt, mcap);
+    }
     Queue* q = c->queues.as<Queue>();
     HIPCHK(c, launch_init(c->stream, sp, c->wp.as<WinParam>(), in.seeds, B, c->state.as<WinState>(),
                           c->sel.as<Sel>(), c->hyps.as<Hyp>(), c->act.as<int>(), c->items.as<Item>(), qcap, &q[0],
@@ -677,7 +710,7 @@ static int run_search(ecmd_ctx* c, const ecmd_sensor* sensor, Inputs& in, int B,
             e = launch_nodes(c->stream, g, c->nodes_nb, nt, c->nodes_lds, c->ev.as<float4>(),
                              c->seg_off.as<long long>(), c->seg_own.as<int>(), c->wp.as<WinParam>(),
                              c->hyps.as<Hyp>(), c->act.as<int>(), c->items.as<Item>(), qcap, &q[(2 + parity) * kXcd],
-                             &q[(3 - parity) * kXcd], c->part.as<Part>(), sp.HS, c->lists.as<float4>(), kListCap, a, b);
+                             &q[(3 - parity) * kXcd], c->part.as<Part>(), sp.HS, c->lists.as<float4>(), mcap, a, b);
             if (e != hipSuccess) return e;
         }
         if (timed) tm.pair(1, a, b);
@@ -899,7 +932,8 @@ enum PlanBuf {
     PB_HYPS, PB_ACT, PB_ITEMS, PB_QUEUES, PB_PART, PB_NACTIVE, PB_LISTS, PB_COUNT
 };
 
-// Bytes of each device buffer for the shape's limits.
+// Bytes of each device buffer but the lists (as long as there is room for) for
+// the shape's limits.
 static void plan_sizes(const PlanShape& sh, size_t* bytes) {
     const int Bm = sh.lim.max_windows, T = sh.g.T;
     const Search& sp = sh.sp;
@@ -922,7 +956,6 @@ static void plan_sizes(const PlanShape& sh, size_t* bytes) {
     bytes[PB_QUEUES] = sizeof(Queue) * kQueues;
     bytes[PB_PART] = sizeof(Part) * (size_t)Bm * sp.HS * T;
     bytes[PB_NACTIVE] = sizeof(int);
-    bytes[PB_LISTS] = list_bytes(sh.nodes_nb, sh.nt, sh.mcap);
 }
 
 // Device buffers of batched searches up to fixed limits; a launch only
@@ -1230,9 +1263,9 @@ int ecmd_measure_peaks(ecmd_ctx* c, int64_t hbm_bytes, double* lds_atomics_per_s
     if (bytes < (1ll << 20)) return fail(c, ECMD_EINVAL, "hbm_bytes must be at least 1 MiB");
     const int lds_blocks = c->num_cu * 2, iters = 4096;
     const int hbm_blocks = c->num_cu * 8;
-    HIPCHK(c, c->misc.ensure(sizeof(float) * (size_t)std::max(lds_blocks, hbm_blocks)));
+    HIPCHK(c, need(c, c->misc, sizeof(float) * (size_t)std::max(lds_blocks, hbm_blocks)));
     DevBuf big;
-    hipError_t e = big.ensure((size_t)bytes);
+    hipError_t e = need(c, big, (size_t)bytes);
     if (e != hipSuccess) return fail(c, ECMD_ENOMEM, "cannot allocate %lld bytes", bytes);
     e = hipMemsetAsync(big.p, 0, (size_t)bytes, c->stream);  // first touch outside the timing
     hipEvent_t a = nullptr, b = nullptr;
@@ -1408,7 +1441,8 @@ int ecmd_plan_create(ecmd_ctx* c, const ecmd_sensor* sensor, const ecmd_search* 
     size_t bytes[PB_COUNT];
     plan_sizes(sh, bytes);
     hipError_t e = hipSuccess;
-    for (int k = 0; k < PB_COUNT && e == hipSuccess; ++k) e = p->buf[k].ensure(bytes[k]);
+    for (int k = 0; k < PB_LISTS && e == hipSuccess; ++k) e = need(c, p->buf[k], bytes[k]);
+    if (e == hipSuccess && sh.mcap > 0) e = fit_lists(p->buf[PB_LISTS], sh.nodes_nb, sh.nt, p->sh.mcap);
     if (e != hipSuccess) {
         plan_release(p);
         delete p;
@@ -1500,15 +1534,15 @@ int ecmd_estimate_divergence(ecmd_ctx* c, const ecmd_sensor* sensor, const ecmd_
     float* dy;
     float* dt;
     const bool has_pol = events->p != nullptr;
-    if (has_pol) HIPCHK(c, c->spol.ensure((size_t)std::max(n, 1ll)));
+    if (has_pol) HIPCHK(c, need(c, c->spol, (size_t)std::max(n, 1ll)));
     if (flags & ECMD_DEVICE_PTR) {
-        HIPCHK(c, c->sx.ensure(sizeof(float) * std::max(n, 1ll)));
-        HIPCHK(c, c->sy.ensure(sizeof(float) * std::max(n, 1ll)));
-        HIPCHK(c, c->st.ensure(sizeof(float) * std::max(n, 1ll)));
+        HIPCHK(c, need(c, c->sx, sizeof(float) * std::max(n, 1ll)));
+        HIPCHK(c, need(c, c->sy, sizeof(float) * std::max(n, 1ll)));
+        HIPCHK(c, need(c, c->st, sizeof(float) * std::max(n, 1ll)));
         const int nb = (int)((n + 1023) / 1024);
-        HIPCHK(c, c->keep.ensure(sizeof(int) * (nb + 1)));
-        HIPCHK(c, c->misc.ensure(sizeof(long long)));
-        HIPCHK(c, c->err_flag.ensure(sizeof(int)));
+        HIPCHK(c, need(c, c->keep, sizeof(int) * (nb + 1)));
+        HIPCHK(c, need(c, c->misc, sizeof(long long)));
+        HIPCHK(c, need(c, c->err_flag, sizeof(int)));
         HIPCHK(c, hipMemsetAsync(c->err_flag.p, 0, sizeof(int), c->stream));
         HIPCHK(c, launch_select(c->stream, events->x, events->y, events->t, (const signed char*)events->p, n,
                                 window.t0, window.t1, c->sx.as<float>(), c->sy.as<float>(), c->st.as<float>(),
@@ -1535,9 +1569,9 @@ int ecmd_estimate_divergence(ecmd_ctx* c, const ecmd_sensor* sensor, const ecmd_
             }
         }
         m = (long long)hx.size();
-        HIPCHK(c, c->sx.ensure(sizeof(float) * std::max(m, 1ll)));
-        HIPCHK(c, c->sy.ensure(sizeof(float) * std::max(m, 1ll)));
-        HIPCHK(c, c->st.ensure(sizeof(float) * std::max(m, 1ll)));
+        HIPCHK(c, need(c, c->sx, sizeof(float) * std::max(m, 1ll)));
+        HIPCHK(c, need(c, c->sy, sizeof(float) * std::max(m, 1ll)));
+        HIPCHK(c, need(c, c->st, sizeof(float) * std::max(m, 1ll)));
         if (m) {
             HIPCHK(c, hipMemcpyAsync(c->sx.p, hx.data(), sizeof(float) * m, hipMemcpyHostToDevice, c->stream));
             HIPCHK(c, hipMemcpyAsync(c->sy.p, hy.data(), sizeof(float) * m, hipMemcpyHostToDevice, c->stream));
@@ -1592,7 +1626,7 @@ int ecmd_probe_pixels(ecmd_ctx* c, const ecmd_sensor* sensor, const float* x, co
     if ((rc = stage(c, c->st, t_rel, sizeof(float) * n, flags, &pt))) return rc;
     int* dpix = (int*)pix_out;
     if (!(flags & ECMD_DEVICE_PTR)) {
-        HIPCHK(c, c->pix.ensure(sizeof(int) * std::max(n, (int64_t)1)));
+        HIPCHK(c, need(c, c->pix, sizeof(int) * std::max(n, (int64_t)1)));
         dpix = c->pix.as<int>();
     }
     HIPCHK(c, launch_probe_pixels(c->stream, (const float*)px, (const float*)py, (const float*)pt, n, tau, d,
@@ -1648,12 +1682,12 @@ static int probe_impl(ecmd_ctx* c, const ecmd_sensor* sensor, const float* x, co
     if (d_b) {
         if ((rc = stage(c, c->misc, d_b, sizeof(float) * m, flags, &pb))) return rc;
     }
-    HIPCHK(c, c->hyps.ensure(sizeof(Hyp) * m));
+    HIPCHK(c, need(c, c->hyps, sizeof(Hyp) * m));
     const size_t n_items = (size_t)m * T;  // every hypothesis on every tile
-    HIPCHK(c, c->act.ensure(sizeof(int) * m));
-    HIPCHK(c, c->items.ensure(sizeof(Item) * n_items));
-    HIPCHK(c, c->queues.ensure(sizeof(Queue) * kQueues));
-    HIPCHK(c, c->part.ensure(sizeof(Part) * n_items));
+    HIPCHK(c, need(c, c->act, sizeof(int) * m));
+    HIPCHK(c, need(c, c->items, sizeof(Item) * n_items));
+    HIPCHK(c, need(c, c->queues, sizeof(Queue) * kQueues));
+    HIPCHK(c, need(c, c->part, sizeof(Part) * n_items));
     HIPCHK(c, launch_probe_items(c->stream, (const float*)pa, (const float*)pb, m, tau, T, c->hyps.as<Hyp>(),
                                  c->act.as<int>(), c->items.as<Item>(), c->queues.as<Queue>()));
     unsigned* dimg = nullptr;
@@ -1661,7 +1695,7 @@ static int probe_impl(ecmd_ctx* c, const ecmd_sensor* sensor, const float* x, co
         if (flags & ECMD_DEVICE_PTR) {
             dimg = img_out;
         } else {
-            HIPCHK(c, c->img.ensure(sizeof(unsigned) * (size_t)m * M));
+            HIPCHK(c, need(c, c->img, sizeof(unsigned) * (size_t)m * M));
             dimg = c->img.as<unsigned>();
         }
     }
@@ -1675,7 +1709,7 @@ static int probe_impl(ecmd_ctx* c, const ecmd_sensor* sensor, const float* x, co
     unsigned long long* dS = (unsigned long long*)S;
     long long* dN = (long long*)N;
     if (!(flags & ECMD_DEVICE_PTR)) {
-        HIPCHK(c, c->counts.ensure(16 * (size_t)m));
+        HIPCHK(c, need(c, c->counts, 16 * (size_t)m));
         dS = c->counts.as<unsigned long long>();
         dN = (long long*)dS + m;
     }
@@ -1765,13 +1799,13 @@ int ecmd_downsample(ecmd_ctx* c, const ecmd_sensor* sensor, const float* x, cons
     if ((rc = stage(c, c->sx, x, sizeof(float) * n_total, flags, &px))) return rc;
     if ((rc = stage(c, c->sy, y, sizeof(float) * n_total, flags, &py))) return rc;
     if ((rc = stage(c, c->soff, offsets, sizeof(long long) * (B + 1), flags, &po))) return rc;
-    HIPCHK(c, c->blk.ensure(sizeof(int) * (B + 1)));
+    HIPCHK(c, need(c, c->blk, sizeof(int) * (B + 1)));
     HIPCHK(c, hipMemcpyAsync(c->blk.p, blk.data(), sizeof(int) * (B + 1), hipMemcpyHostToDevice, c->stream));
-    HIPCHK(c, c->counts.ensure(sizeof(unsigned) * (size_t)B * 4096));
+    HIPCHK(c, need(c, c->counts, sizeof(unsigned) * (size_t)B * 4096));
     HIPCHK(c, hipMemsetAsync(c->counts.p, 0, sizeof(unsigned) * (size_t)B * 4096, c->stream));
     uint16_t* dout = out;
     if (!(flags & ECMD_DEVICE_PTR)) {
-        HIPCHK(c, c->img.ensure(sizeof(uint16_t) * (size_t)B * 4096));
+        HIPCHK(c, need(c, c->img, sizeof(uint16_t) * (size_t)B * 4096));
         dout = c->img.as<uint16_t>();
     }
     HIPCHK(c, launch_downsample(c->stream, (const float*)px, (const float*)py, (const long long*)po, B,
@@ -1817,9 +1851,9 @@ static int preproc_impl(ecmd_ctx* c, int kind, const ecmd_sensor* in_s, const ec
     const long long* doff = (const long long*)offsets;
     long long base = off[0];
     if (!(flags & ECMD_DEVICE_PTR)) {
-        HIPCHK(c, c->sx.ensure(sizeof(float) * std::max(n, 1ll)));
-        HIPCHK(c, c->sy.ensure(sizeof(float) * std::max(n, 1ll)));
-        HIPCHK(c, c->st.ensure(sizeof(float) * std::max(n, 1ll)));
+        HIPCHK(c, need(c, c->sx, sizeof(float) * std::max(n, 1ll)));
+        HIPCHK(c, need(c, c->sy, sizeof(float) * std::max(n, 1ll)));
+        HIPCHK(c, need(c, c->st, sizeof(float) * std::max(n, 1ll)));
         if (n) {
             HIPCHK(c, hipMemcpyAsync(c->sx.p, x + base, sizeof(float) * n, hipMemcpyHostToDevice, c->stream));
             HIPCHK(c, hipMemcpyAsync(c->sy.p, y + base, sizeof(float) * n, hipMemcpyHostToDevice, c->stream));
@@ -1828,7 +1862,7 @@ static int preproc_impl(ecmd_ctx* c, int kind, const ecmd_sensor* in_s, const ec
         // staged copies start at index 0: shift the offsets
         std::vector<long long> o0(off);
         for (auto& v : o0) v -= base;
-        HIPCHK(c, c->soff.ensure(sizeof(long long) * (B + 1)));
+        HIPCHK(c, need(c, c->soff, sizeof(long long) * (B + 1)));
         HIPCHK(c, hipMemcpyAsync(c->soff.p, o0.data(), sizeof(long long) * (B + 1), hipMemcpyHostToDevice, c->stream));
         HIPCHK(c, hipStreamSynchronize(c->stream));
         dx = c->sx.as<float>();
@@ -1839,9 +1873,9 @@ static int preproc_impl(ecmd_ctx* c, int kind, const ecmd_sensor* in_s, const ec
     }
     const long long nblk = (n + kPreChunk - 1) / kPreChunk;
     const size_t nb1 = std::max(nblk, 1ll);
-    HIPCHK(c, c->keep.ensure(nb1 * (kPreChunk / 8)));
-    HIPCHK(c, c->err_flag.ensure(sizeof(int) * nb1));
-    HIPCHK(c, c->misc.ensure(sizeof(long long) * (nb1 + 1)));
+    HIPCHK(c, need(c, c->keep, nb1 * (kPreChunk / 8)));
+    HIPCHK(c, need(c, c->err_flag, sizeof(int) * nb1));
+    HIPCHK(c, need(c, c->misc, sizeof(long long) * (nb1 + 1)));
     unsigned long long* words = c->keep.as<unsigned long long>();
     int* blk_cnt = c->err_flag.as<int>();
     const int W = in_s->width, H = in_s->height;
@@ -1853,17 +1887,17 @@ static int preproc_impl(ecmd_ctx* c, int kind, const ecmd_sensor* in_s, const ec
         uint16_t* list = nullptr;
         unsigned long long* hot = nullptr;
         if (nb > 0) {
-            HIPCHK(c, c->cnt_own.ensure(sizeof(int) * nwin * nb));
-            HIPCHK(c, c->cursor.ensure(sizeof(long long) * (nwin * nb + 1)));
-            HIPCHK(c, c->img.ensure(sizeof(uint16_t) * std::max(n, 1ll)));
-            HIPCHK(c, c->counts.ensure(nwin * ((M + 63) / 64) * 8));
+            HIPCHK(c, need(c, c->cnt_own, sizeof(int) * nwin * nb));
+            HIPCHK(c, need(c, c->cursor, sizeof(long long) * (nwin * nb + 1)));
+            HIPCHK(c, need(c, c->img, sizeof(uint16_t) * std::max(n, 1ll)));
+            HIPCHK(c, need(c, c->counts, nwin * ((M + 63) / 64) * 8));
             HIPCHK(c, hipMemsetAsync(c->cnt_own.p, 0, sizeof(int) * nwin * nb, c->stream));
             cnt = c->cnt_own.as<int>();
             cursor = c->cursor.as<long long>();
             list = c->img.as<uint16_t>();
             hot = c->counts.as<unsigned long long>();
         } else {
-            HIPCHK(c, c->counts.ensure(sizeof(unsigned) * M * nwin));
+            HIPCHK(c, need(c, c->counts, sizeof(unsigned) * M * nwin));
             HIPCHK(c, hipMemsetAsync(c->counts.p, 0, sizeof(unsigned) * M * nwin, c->stream));
         }
         HIPCHK(c, launch_hot_keep(c->stream, dx, dy, doff, B, nblk, W, H, nb, cnt, cursor, list, hot,
@@ -1877,7 +1911,7 @@ static int preproc_impl(ecmd_ctx* c, int kind, const ecmd_sensor* in_s, const ec
     float *ox = x_out, *oy = y_out, *ot = t_out;
     long long* ooff = (long long*)offsets_out;
     if (!(flags & ECMD_DEVICE_PTR)) {
-        HIPCHK(c, c->pix.ensure(sizeof(float) * 3 * std::max(n, 1ll) + sizeof(long long) * (B + 1)));
+        HIPCHK(c, need(c, c->pix, sizeof(float) * 3 * std::max(n, 1ll) + sizeof(long long) * (B + 1)));
         ox = c->pix.as<float>();
         oy = ox + std::max(n, 1ll);
         ot = oy + std::max(n, 1ll);
@@ -1918,18 +1952,18 @@ int ecmd_estimate_stream(ecmd_ctx* c, const ecmd_sensor* sensor, const ecmd_even
     if (!(flags & ECMD_DEVICE_PTR)) {
         for (long long i = 1; i < n; ++i)
             if (!(events->t[i] >= events->t[i - 1])) return fail(c, ECMD_EINVAL, "stream times must be sorted");
-        HIPCHK(c, c->counts.ensure(sizeof(double) * std::max(n, 1ll)));
+        HIPCHK(c, need(c, c->counts, sizeof(double) * std::max(n, 1ll)));
         if (n) HIPCHK(c, hipMemcpyAsync(c->counts.p, events->t, sizeof(double) * n, hipMemcpyHostToDevice, c->stream));
         dt = (const double*)c->counts.p;
     }
-    HIPCHK(c, c->misc.ensure(sizeof(long long) * (K + 1)));
+    HIPCHK(c, need(c, c->misc, sizeof(long long) * (K + 1)));
     long long* doff = c->misc.as<long long>();
     HIPCHK(c, launch_stream_bounds(c->stream, dt, n, t_start, tau, K, doff));
     std::vector<long long> off(K + 1);
     HIPCHK(c, hipMemcpyAsync(off.data(), doff, sizeof(long long) * (K + 1), hipMemcpyDeviceToHost, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
     const long long o0 = off[0], m = off[K] - off[0];
-    HIPCHK(c, c->keep.ensure(sizeof(float) * std::max(m, 1ll)));
+    HIPCHK(c, need(c, c->keep, sizeof(float) * std::max(m, 1ll)));
     float* trel = (float*)c->keep.p;
     HIPCHK(c, launch_stream_trel(c->stream, dt, doff, m, K, t_start, tau, trel));
     // batched estimation on the selected range (x, y staged to the device if needed)
@@ -1939,12 +1973,12 @@ int ecmd_estimate_stream(ecmd_ctx* c, const ecmd_sensor* sensor, const ecmd_even
     const float *dx = events->x + o0, *dy = events->y + o0;
     const signed char* dp = events->p ? (const signed char*)events->p + o0 : nullptr;
     if (events->p && !(flags & ECMD_DEVICE_PTR)) {
-        HIPCHK(c, c->spol.ensure((size_t)std::max(m, 1ll)));
+        HIPCHK(c, need(c, c->spol, (size_t)std::max(m, 1ll)));
         if (m) HIPCHK(c, hipMemcpyAsync(c->spol.p, events->p + o0, (size_t)m, hipMemcpyHostToDevice, c->stream));
         dp = c->spol.as<signed char>();
     }
     if (!(flags & ECMD_DEVICE_PTR)) {
-        HIPCHK(c, c->img.ensure(sizeof(float) * 2 * std::max(m, 1ll)));
+        HIPCHK(c, need(c, c->img, sizeof(float) * 2 * std::max(m, 1ll)));
         float* sxy = c->img.as<float>();
         dx = sxy;
         dy = sxy + std::max(m, 1ll);
@@ -2024,16 +2058,16 @@ static int cnn_run(ecmd_cnn* n, const uint16_t* imgs, const float* labels, int32
     const uint16_t* di;
     int rc = cnn_stage_imgs(n, imgs, B, flags, &di);
     if (rc) return rc;
-    HIPCHK(c, n->out.ensure(sizeof(float) * B));
+    HIPCHK(c, need(c, n->out, sizeof(float) * B));
     const float* dl = nullptr;
     if (mode) {
         const void* p;
         if ((rc = stage(c, n->labels, labels, sizeof(float) * B, flags, &p))) return rc;
         dl = (const float*)p;
-        HIPCHK(c, n->pg.ensure(sizeof(float) * (size_t)B * cnn_nparam()));
-        HIPCHK(c, n->lossb.ensure(sizeof(float) * B));
-        HIPCHK(c, n->loss.ensure(sizeof(float)));
-        HIPCHK(c, n->grad.ensure(sizeof(float) * cnn_nparam()));
+        HIPCHK(c, need(c, n->pg, sizeof(float) * (size_t)B * cnn_nparam()));
+        HIPCHK(c, need(c, n->lossb, sizeof(float) * B));
+        HIPCHK(c, need(c, n->loss, sizeof(float)));
+        HIPCHK(c, need(c, n->grad, sizeof(float) * cnn_nparam()));
     }
     HIPCHK(c, cnn_set_lds());
     HIPCHK(c, launch_cnn(c->stream, n->P.as<float>(), di, B, n->out.as<float>(), mode, dl, n->pg.as<float>(),
@@ -2057,8 +2091,8 @@ int ecmd_cnn_create(ecmd_ctx* c, uint64_t seed, ecmd_cnn** out) {
     std::vector<float> p;
     cnn_init_params(seed, p);
     std::vector<float> zero(np, 0.0f);
-    if (n->P.ensure(sizeof(float) * np) != hipSuccess || n->m.ensure(sizeof(float) * np) != hipSuccess ||
-        n->v.ensure(sizeof(float) * np) != hipSuccess) {
+    if (need(c, n->P, sizeof(float) * np) != hipSuccess || need(c, n->m, sizeof(float) * np) != hipSuccess ||
+        need(c, n->v, sizeof(float) * np) != hipSuccess) {
         n->P.release(); n->m.release(); n->v.release();
         delete n;
         return fail(c, ECMD_ENOMEM, "device allocation failed");
@@ -2207,8 +2241,8 @@ int ecmd_estimate_divergence_learned(ecmd_ctx* c, ecmd_cnn* n, const ecmd_sensor
     if (!search) return fail(c, ECMD_EINVAL, "search is NULL");
     HIPCHK(c, hipSetDevice(c->device));
     // downsampled images stay on the device
-    HIPCHK(c, n->imgs.ensure(sizeof(uint16_t) * (size_t)B * 4096));
-    HIPCHK(c, n->seeds.ensure(sizeof(float) * B));
+    HIPCHK(c, need(c, n->imgs, sizeof(uint16_t) * (size_t)B * 4096));
+    HIPCHK(c, need(c, n->seeds, sizeof(float) * B));
     int rc;
     if (flags & ECMD_DEVICE_PTR) {
         rc = ecmd_downsample(c, sensor, x, y, offsets, B, flags, n->imgs.as<uint16_t>());
