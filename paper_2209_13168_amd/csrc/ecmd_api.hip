@@ -1887,10 +1887,14 @@ static int preproc_impl(ecmd_ctx* c, int kind, const ecmd_sensor* in_s, const ec
         uint16_t* list = nullptr;
         unsigned long long* hot = nullptr;
         if (nb > 0) {
-            HIPCHK(c, need(c, c->cnt_own, sizeof(int) * nwin * nb));
-            HIPCHK(c, need(c, c->cursor, sizeof(long long) * (nwin * nb + 1)));
-            HIPCHK(c, need(c, c->img, sizeof(uint16_t) * std::max(n, 1ll)));
-            HIPCHK(c, need(c, c->counts, nwin * ((M + 63) / 64) * 8));
+            hipError_t e = need(c, c->cnt_own, sizeof(int) * nwin * nb);
+            if (e == hipSuccess) e = need(c, c->cursor, sizeof(long long) * (nwin * nb + 1));
+            if (e == hipSuccess) e = need(c, c->img, sizeof(uint16_t) * std::max(n, 1ll));
+            if (e == hipSuccess) e = need(c, c->counts, nwin * ((M + 63) / 64) * 8);
+            if (e == hipErrorOutOfMemory) nb = 0;  // the sorted pixels take 2 bytes an event: without them
+            else HIPCHK(c, e);
+        }
+        if (nb > 0) {
             HIPCHK(c, hipMemsetAsync(c->cnt_own.p, 0, sizeof(int) * nwin * nb, c->stream));
             cnt = c->cnt_own.as<int>();
             cursor = c->cursor.as<long long>();

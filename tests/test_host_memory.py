@@ -1,6 +1,7 @@
-"""Memory that runs out: the lists of the node groups, which a search can do
-without, are cut or left out instead of the call being refused, and are given
-back when another buffer needs the room."""
+"""Memory that runs out: what a call can do without (the lists of the node
+groups, the pixels sorted for the hot-pixel filter) is cut or left out instead
+of the call being refused, and the lists are given back when another buffer
+needs the room."""
 
 import ctypes as C
 
@@ -107,6 +108,20 @@ def plans(rt, spare):
     assert e.value.code == ecmd.ENOMEM and rt.rt_used() == base
 
 
+def hot_pixels(rt, spare, launches):
+    from paper_2209_13168_amd import ecmd
+
+    ctx = ecmd.Context(0, stream=0)
+    sen = ecmd.sensor(346, 260, (173, 130))
+    n = 4 << 20
+    x, off = np.zeros(n, np.float32), np.array([0, n], np.int64)
+    ctx.resample(sen, sen, x, x, x, off, 0.5, 1)  # every buffer but the pixels' own
+    rt.rt_limit(rt.rt_used() + spare)
+    n0 = rt.rt_launches()
+    ctx.hot_pixel_filter(sen, x, x, x, off, 3)
+    assert rt.rt_launches() - n0 == launches and rt.rt_last() == 0
+
+
 SPARE = [200 * MIB, 128 * MIB, 127 * MIB, 9 * MIB, 8 * MIB, 7 * MIB, 0]
 
 
@@ -118,6 +133,12 @@ def test_a_search_takes_the_lists_that_fit(so, spare):
 @pytest.mark.parametrize("spare", SPARE)
 def test_a_plan_takes_the_lists_that_fit(so, spare):
     host_runtime.run(so, __name__, "plans", spare)
+
+
+@pytest.mark.parametrize("spare,launches", [(16 * MIB, 8), (2 * MIB, 5)])
+def test_hot_pixels_without_the_sort(so, spare, launches):
+    """The sorted pixels take 2 bytes an event, the counters in memory 4 a pixel."""
+    host_runtime.run(so, __name__, "hot_pixels", spare, launches)
 
 
 def test_lists_make_room(so):
