@@ -627,7 +627,7 @@ static void set_nodes(Search& sp, int B, int T, long long n_events, int nb, int 
     sp.nmax = nb > 0 && mcap >= 64 && many ? kMaxNodes : 0;
     sp.nwave = nt / 64;
     sp.nlist = mcap * 3 / 8;
-    sp.npad = 0;
+    sp.pad = 0;
     sp.nslots = 2ll * nb;
 }
 

@@ -115,14 +115,17 @@ struct Search {
     long long max_nodes;
     long long gamma_key;  // stop when best K_bar - K_inc <= gamma_key (-1: gamma = 0)
     long long M;          // pixels
+    long long nslots;     // groups are cut so that a step has at least this many items
     int cert;             // endpoint certificates allowed (ECMD_SEARCH_EXACT_BOUNDS not set)
     int nmax;             // nodes of a node group, at most (0: no groups)
     int nwave;            // waves of a node item
     int nlist;            // events a wave's list should hold
-    int npad;
-    long long nslots;     // groups are cut so that a step has at least this many items
     int max_steps;        // a window that has taken this many steps stays as it is
+    int pad;              // (0)
 };
+// The captured rounds are kept under the bytes of this struct: every one is a
+// field's, so that equal searches have equal bytes.
+static_assert(sizeof(Search) == 2 * sizeof(float) + 12 * sizeof(int) + 5 * sizeof(long long), "no padding");
 
 struct WinState {
     unsigned long long Kinc_lo;

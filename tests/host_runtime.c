@@ -28,6 +28,11 @@ long long rt_instantiated(void) { return g_instantiated; }
 /* windows of the next synchronous searches, whose reports (16 bytes each: event
  * records, minus the finished windows, first bad window) say that all ended */
 void rt_windows(int B) { g_windows = B; }
+/* fills the stack below the caller's frame */
+__attribute__((noinline)) void rt_scribble(int v) {
+    volatile char a[1 << 16];
+    for (size_t k = 0; k < sizeof a; ++k) a[k] = (char)v;
+}
 hipError_t rt_last(void) { return g_last; }
 
 static hipError_t fail(hipError_t e) {
