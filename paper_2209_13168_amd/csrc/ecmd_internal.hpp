@@ -179,6 +179,17 @@ struct Queue {
     int next;
 };
 
+// Slots of queue r's k-th hypothesis item and of its k-th node item, 0 <= k <
+// qcap.  The largest search (65535 windows, kMaxF nodes, kMaxTiles segments)
+// has more than 2^32 slots.
+__host__ __device__ constexpr long long hyp_slot(int r, int k, int qcap) { return (long long)r * qcap + k; }
+__host__ __device__ constexpr long long node_slot(int r, int k, int qcap) { return (long long)(r + 1) * qcap - 1 - k; }
+constexpr int kMaxQcap = (65535 + kXcd - 1) / kXcd * 3 * kMaxF * kMaxTiles;
+static_assert(kMaxQcap == 1610612736, "a queue's slots are counted in 31 bits");
+static_assert(hyp_slot(kXcd - 1, kMaxQcap - 1, kMaxQcap) == 12884901887ll, "the last slot");
+static_assert(node_slot(kXcd - 1, 0, kMaxQcap) == 12884901887ll && node_slot(0, kMaxQcap - 1, kMaxQcap) == 0,
+              "the last slot, the first");
+
 // ---------------------------------------------------------------- launchers
 // All launchers enqueue on `s` and return the launch status.
 

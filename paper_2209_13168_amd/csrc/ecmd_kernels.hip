@@ -767,7 +767,7 @@ __device__ __forceinline__ void walk_tile(unsigned* org, const Ring& R, int kx, 
 }
 
 // LDS layout of k_eval: [tile with its border: (tw + 2)(th + 2) counters]
-// (region rounded up to 16 bytes)[reduction scratch][work item, queue sizes].  The
+// (region rounded up to 16 bytes)[reduction scratch][queue sizes, 4 bytes spare].  The
 // reduction scratch is sized for the largest workgroup (1024 threads).
 constexpr int kEvalWaves = kEvalThreads / 64;
 
@@ -805,7 +805,9 @@ __global__ __launch_bounds__(NT) void k_eval(
     unsigned* const tile = smem;
     unsigned long long* const s_red =
         reinterpret_cast<unsigned long long*>(smem + eval_counter_words(g.ring_px));
-    int* const s_item = reinterpret_cast<int*>(s_red + 3 * NW);
+    // the work item, in the scratch between the hypotheses' sums (thread 0
+    // alone has read them last)
+    long long* const s_item = reinterpret_cast<long long*>(s_red);
     if (blockIdx.x == 0 && tid < kXcd && q_reset) {
         q_reset[tid].n_items = 0;
         q_reset[tid].next = 0;
@@ -823,18 +825,18 @@ __global__ __launch_bounds__(NT) void k_eval(
     }
     const int home = blockIdx.x % kXcd;
     int qi = 0;  // queues tried so far, starting at this XCD's own (thread 0 only)
-    int* const qn = s_item + 1;  // queue sizes, read once (thread 0 only; in LDS, not registers)
+    int* const qn = reinterpret_cast<int*>(s_red + 3 * NW);  // queue sizes, read once (thread 0 only; in LDS, not registers)
     if (tid == 0)
         for (int r = 0; r < kXcd; ++r) qn[r] = q[(home + r) % kXcd].n_items;
     for (;;) {
         if (tid == 0) {
-            int got = -1;
+            long long got = -1;
             while (qi < kXcd) {
                 const int r = (home + qi) % kXcd;
                 if (qn[qi] > 0) {
                     const int k = atomicAdd(&q[r].next, 1);
                     if (k < qn[qi]) {
-                        got = r * qcap + k;
+                        got = hyp_slot(r, k, qcap);
                         break;
                     }
                 }
@@ -843,7 +845,7 @@ __global__ __launch_bounds__(NT) void k_eval(
             *s_item = got;
         }
         __syncthreads();
-        const int it = *s_item;
+        const long long it = *s_item;
         __syncthreads();
         if (it < 0) break;
         const Item item = items[it];
@@ -1112,8 +1114,8 @@ constexpr int kNodePhases = 3 * kMaxNodes;
 static_assert(kNodePhases <= 64, "one lane per phase");
 
 // LDS of k_nodes after the counters: [S and count of the last image][phase
-// sums of S][of the count][changes of N, per node][steps, per wave][s_full][work item, queue sizes].
-constexpr int kNodeLds = 16 + 12 * kNodePhases + 4 * kMaxNodes + 4 * kEvalWaves + 4 + 4 * (1 + kXcd);
+// sums of S][of the count][changes of N, per node][steps, per wave][s_full][work item and its queue, queue sizes].
+constexpr int kNodeLds = 16 + 12 * kNodePhases + 4 * kMaxNodes + 4 * kEvalWaves + 4 + 4 * (2 + kXcd);
 size_t nodes_lds_bytes(int ring_px) { return (size_t)eval_counter_words(ring_px) * 4 + kNodeLds; }
 
 // A step (see k_nodes): the counter before in the low 16 bits, then these.
@@ -1158,11 +1160,11 @@ __global__ __launch_bounds__(NT, NT == 1024 ? 4 : 6) void k_nodes(
         const int n4 = eval_counter_words(g.ring_px) >> 2;
         for (int i = tid; i < n4; i += NT) t4[i] = make_uint4(0u, 0u, 0u, 0u);
         unsigned* const rest = reinterpret_cast<unsigned*>(s_fin);
-        for (int i = tid; i < kNodeLds / 4 - 1 - kXcd; i += NT) rest[i] = 0u;
+        for (int i = tid; i < kNodeLds / 4 - 2 - kXcd; i += NT) rest[i] = 0u;
     }
     const int home = blockIdx.x % kXcd;
     int qi = 0;
-    int* const qn = s_item + 1;
+    int* const qn = s_item + 2;
     if (tid == 0)
         for (int r = 0; r < kXcd; ++r) qn[r] = q[(home + r) % kXcd].n_items;
     const int F = HS / 3;
@@ -1174,7 +1176,8 @@ __global__ __launch_bounds__(NT, NT == 1024 ? 4 : 6) void k_nodes(
                 if (qn[qi] > 0) {
                     const int k = atomicAdd(&q[r].next, 1);
                     if (k < qn[qi]) {
-                        got = (r + 1) * qcap - 1 - k;  // node items fill a queue's slots from the end
+                        got = k;
+                        s_item[1] = r;
                         break;
                     }
                 }
@@ -1185,7 +1188,7 @@ __global__ __launch_bounds__(NT, NT == 1024 ? 4 : 6) void k_nodes(
         __syncthreads();
         const int it = *s_item;
         if (it < 0) break;
-        const Item item = items[it];
+        const Item item = items[node_slot(s_item[1], it, qcap)];
         const int w = item.w, t = item.t, m = item.cnt;
         const int ts = t % g.nsp;
         const int tx = ts % g.ntx, ty = ts / g.ntx;
@@ -1779,7 +1782,7 @@ __device__ void emit_items(const Search& sp, int w, const int* tiles, int nt, in
                            Queue* qf) {
     int G = sp.G;
     const int qr = w % kXcd;  // this window's queue
-    Item* qitems = items + (long long)qr * qcap;
+    Item* qitems = items + hyp_slot(qr, 0, qcap);
     __shared__ int s_base;
     if (sp.gslots > 0) {  // this step's items with one hypothesis each, all windows alike
         const long long work = (long long)sp.B * na * nt;
@@ -1806,7 +1809,7 @@ __device__ void emit_items(const Search& sp, int w, const int* tiles, int nt, in
 __device__ void emit_node_items(int w, const int* tiles, int nt, int base, const int* gs, int ng, int nodes,
                                 Item* items, int qcap, Queue* nf) {
     const int qr = w % kXcd;
-    Item* const qlast = items + (long long)(qr + 1) * qcap - 1;
+    Item* const qlast = items + node_slot(qr, 0, qcap);
     __shared__ int s_nbase;
     if (threadIdx.x == 0) s_nbase = (ng * nt) ? atomicAdd(&nf[qr].n_items, ng * nt) : 0;
     __syncthreads();
