@@ -1847,7 +1847,9 @@ __device__ void emit_hyps(const Search& sp, const WinParam& p, int w, int T, con
     // moves per unit of rate (the mean of |ax| + |ay| over the sensor and the
     // window), so lam times a node's width is about the share of the events
     // that change pixel inside it.
-    __shared__ float s_na[kMaxF], s_nb[kMaxF];
+    constexpr unsigned kAlone = 0xFFFFFFFFu;  // (grid indices stay below 2^31)
+    __shared__ unsigned s_ja[kMaxF];  // a grouped node's start on the grid, or kAlone
+    __shared__ float s_na[kMaxF], s_nb[kMaxF];  // its rates there and at its end
     __shared__ int s_ord[kMaxF], s_gs[kMaxF];
     __shared__ int s_ng;
     const float per = (float)most / (float)max(sp.nwave, 1);  // a wave's events of the fullest tile
@@ -1863,7 +1865,8 @@ __device__ void emit_hyps(const Search& sp, const WinParam& p, int w, int T, con
             const float a = rate_of(grid_d(sp.d_lo, sp.d_hi, sp.L, sl[i].ja), p.tau);
             const float b = rate_of(grid_d(sp.d_lo, sp.d_hi, sp.L, sl[i].jb), p.tau);
             in = lam * (b - a) <= share && !(cert && sl[i].kids && sl[i].lc > kinc);
-            s_na[i] = in ? a : INFINITY;
+            s_ja[i] = in ? sl[i].ja : kAlone;
+            s_na[i] = a;
             s_nb[i] = b;
         }
         int tot;
@@ -1894,7 +1897,7 @@ __device__ void emit_hyps(const Search& sp, const WinParam& p, int w, int T, con
         }
         if (h < HS) hy[h] = hp;
         const int node = h < F ? h : (h - F) >> 1;
-        const bool alone = hp.kind != HYP_NONE && !(nodes && s_na[node] < INFINITY);
+        const bool alone = hp.kind != HYP_NONE && !(nodes && s_ja[node] != kAlone);
         int tot;
         const int r = block_rank(alone, sc, turn, tot);
         if (alone) act[na + r] = h;
@@ -1902,12 +1905,15 @@ __device__ void emit_hyps(const Search& sp, const WinParam& p, int w, int T, con
     }
     emit_items(sp, w, tiles, nt, na, items, qcap, qf);
     if (!nodes) return;
-    // the grouped nodes in grid order
+    // The grouped nodes in grid order, as k_nodes takes them.  Nodes are
+    // disjoint, so their starts on the grid differ, where neighbouring grid
+    // points may share a rate (from a depth of about 26 on): by rates a node
+    // of no width could come after its wider neighbour.
     for (int i = threadIdx.x; i < n_sel; i += NTF) {
-        const float a = s_na[i];
-        if (!(a < INFINITY)) continue;
+        const unsigned ja = s_ja[i];
+        if (ja == kAlone) continue;
         int r = 0;
-        for (int k = 0; k < n_sel; ++k) r += (s_na[k] < a || (s_na[k] == a && k < i)) ? 1 : 0;
+        for (int k = 0; k < n_sel; ++k) r += s_ja[k] < ja ? 1 : 0;
         s_ord[r] = i;
         act[na + r] = i;
     }
