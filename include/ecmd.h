@@ -232,7 +232,10 @@ int ecmd_ctx_get_tuning(const ecmd_ctx *ctx, ecmd_tuning *out);
  * three 512-thread workgroups share a CU, then two — each only when it
  * cuts the image into at most 24 tiles — then one 1024-thread workgroup
  * with the whole LDS: the tiling of calls of 3.5 million events or more;
- * smaller calls take the whole LDS and 1024 threads at once);
+ * smaller calls take the last of these at once, which tile_px = INT32_MAX
+ * describes, except those with few workgroups' worth of items: windows of
+ * 600 000 events or more on the mean where the first would give three times
+ * the tiles, and probes of few intervals);
  * polarity != 0 plans the two images of the polarity-aware contrast. */
 typedef struct {
     int32_t L;
