@@ -6,6 +6,7 @@
 #include <hip/hip_runtime_api.h>
 #include <stdlib.h>
 #include <string.h>
+#include <sys/mman.h>
 
 #define MAX_BLOCKS 4096
 static struct { void *p; size_t n; } g_block[MAX_BLOCKS];
@@ -45,8 +46,10 @@ hipError_t hipMalloc(void **p, size_t n) {
     if (n > g_limit || g_used > g_limit - n) return fail(hipErrorOutOfMemory);
     for (int k = 0; k < MAX_BLOCKS; ++k)
         if (!g_block[k].p) {
-            if (posix_memalign(p, 256, n)) return fail(hipErrorOutOfMemory);
-            g_block[k].p = *p;
+            /* zero pages, taken when touched */
+            void *q = mmap(NULL, n, PROT_READ | PROT_WRITE, MAP_PRIVATE | MAP_ANONYMOUS | MAP_NORESERVE, -1, 0);
+            if (q == MAP_FAILED) return fail(hipErrorOutOfMemory);
+            *p = g_block[k].p = q;
             g_block[k].n = n;
             g_used += n;
             if (g_used > g_peak) g_peak = g_used;
@@ -59,7 +62,7 @@ hipError_t hipFree(void *p) {
         if (g_block[k].p == p) {
             g_used -= g_block[k].n;
             g_block[k].p = NULL;
-            free(p);
+            munmap(p, g_block[k].n);
             return hipSuccess;
         }
     return p ? fail(hipErrorInvalidValue) : hipSuccess;
