@@ -974,9 +974,10 @@ static void plan_release(ecmd_batch_plan* p) {
 }
 
 // Validates the sensor, search and limits and fills the shape (zero limits
-// replaced by the values used); sets the context's evaluation kernel up.
+// replaced by the values used); sets the context's evaluation kernel up.  lean:
+// the tiles that take the least memory.
 static int plan_shape(ecmd_ctx* c, const ecmd_sensor* sensor, const ecmd_search* search,
-                      const ecmd_plan_limits* lim, PlanShape& sh) {
+                      const ecmd_plan_limits* lim, bool lean, PlanShape& sh) {
     int rc = check_sensor(c, sensor);
     if (rc) return rc;
     int L = 0;
@@ -995,20 +996,22 @@ static int plan_shape(ecmd_ctx* c, const ecmd_sensor* sensor, const ecmd_search*
     const int npol = lim->polarity ? 2 : 1;
     Geometry& g = sh.g;
     int nt = 0, budget = 0;
-    const auto tiling = [&](long long n_events) {
+    const auto tiling = [&](long long n_events, int windows) {
         return choose_tiling(c->max_lds, c->tune, W, H, sensor->foe_x, sensor->foe_y, npol,
-                             Load{n_events, lim->max_windows, 0}, g, nt, budget);
+                             Load{n_events, windows, 0}, g, nt, budget);
     };
     // an event's tiles over any range lie in its FOE quadrant (no event
     // crosses an FOE line), so it has at most that many copies
     const bool xcut = sensor->foe_x == floorf(sensor->foe_x) && sensor->foe_x > 0.0f && sensor->foe_x < (float)W;
     const bool ycut = sensor->foe_y == floorf(sensor->foe_y) && sensor->foe_y > 0.0f && sensor->foe_y < (float)H;
     const auto copies = [&] { return (long long)(xcut ? g.ntx / 2 : g.ntx) * (ycut ? g.nty / 2 : g.nty); };
-    bool fits = tiling(lim->max_events);
-    // a caller's own limit of records was met on the tiles of a large call,
-    // and other cuts cross other events: it keeps them, unless the limit
-    // holds every copy anyway
-    if (fits && lim->max_records > 0 && lim->max_records / copies() < lim->max_events) fits = tiling(LLONG_MAX);
+    // Where the caller limits the records and the limit does not hold every
+    // copy, the coarsest tiles if it does on those; else the tiles of a large
+    // call, on which it was met (other cuts cross other events).
+    const auto holds = [&] { return lim->max_records == 0 || lim->max_records / copies() >= lim->max_events; };
+    bool fits = tiling(lim->max_events, lean ? INT_MAX : lim->max_windows);
+    if (fits && !holds()) fits = tiling(lim->max_events, INT_MAX);
+    if (fits && !holds()) fits = tiling(LLONG_MAX, 1);
     if (!fits) return fail(c, ECMD_EINVAL, "sensor %dx%d needs more than %d tiles", W, H, kMaxTiles / npol);
     ecmd_plan_limits L2 = *lim;
     // default: twice the grid depth and eight more (a level-synchronous
@@ -1429,27 +1432,34 @@ int ecmd_plan_create(ecmd_ctx* c, const ecmd_sensor* sensor, const ecmd_search* 
     if (!c || !out) return ECMD_EINVAL;
     c->err.clear();
     *out = nullptr;
-    PlanShape sh;
-    int rc = plan_shape(c, sensor, search, lim, sh);
-    if (rc) return rc;
     ecmd_batch_plan* p = new (std::nothrow) ecmd_batch_plan();
     if (!p) return fail(c, ECMD_ENOMEM, "host allocation failed");
-    p->ctx = c;
-    p->sensor = *sensor;
-    p->search = *search;
-    p->sh = sh;
-    size_t bytes[PB_COUNT];
-    plan_sizes(sh, bytes);
     hipError_t e = hipSuccess;
-    for (int k = 0; k < PB_LISTS && e == hipSuccess; ++k) e = need(c, p->buf[k], bytes[k]);
-    if (e == hipSuccess && sh.mcap > 0) e = fit_lists(p->buf[PB_LISTS], sh.nodes_nb, sh.nt, p->sh.mcap);
-    if (e != hipSuccess) {
+    for (int lean = 0; lean < 2; ++lean) {
+        PlanShape& sh = p->sh;
+        int rc = plan_shape(c, sensor, search, lim, lean != 0, sh);
+        if (rc) {
+            delete p;
+            return rc;
+        }
+        size_t bytes[PB_COUNT];
+        plan_sizes(sh, bytes);
+        e = hipSuccess;
+        for (int k = 0; k < PB_LISTS && e == hipSuccess; ++k) e = need(c, p->buf[k], bytes[k]);
+        if (e == hipSuccess && sh.mcap > 0) e = fit_lists(p->buf[PB_LISTS], sh.nodes_nb, sh.nt, sh.mcap);
+        if (e == hipSuccess) break;
         plan_release(p);
+        if (e != hipErrorOutOfMemory) break;
+    }
+    if (e != hipSuccess) {
         delete p;
         HIPCHK(c, e);
     }
+    p->ctx = c;
+    p->sensor = *sensor;
+    p->search = *search;
     c->plans.push_back(p);
-    *lim = sh.lim;
+    *lim = p->sh.lim;
     *out = p;
     return ECMD_OK;
 }
@@ -1493,20 +1503,25 @@ int ecmd_estimate_divergence_batched_noalloc(ecmd_ctx* c, const ecmd_sensor* sen
     lim.max_windows = B;
     lim.max_events = max_events;
     PlanShape sh;
-    int rc = plan_shape(c, sensor, search, &lim, sh);
-    if (rc) return rc;
-    size_t bytes[PB_COUNT];
-    plan_sizes(sh, bytes);
+    size_t at[PB_COUNT], used = 0;
+    for (int lean = 0; lean < 2; ++lean) {
+        int rc = plan_shape(c, sensor, search, &lim, lean != 0, sh);
+        if (rc) return rc;
+        size_t bytes[PB_COUNT];
+        plan_sizes(sh, bytes);
+        used = 0;
+        for (int k = 0; k < PB_LISTS; ++k) {
+            at[k] = used;
+            used += (bytes[k] + 255) / 256 * 256;  // every buffer on a 256-byte boundary
+        }
+        if (used <= kScratchBytes) break;
+    }
     void* base = scratch_address(c->device);
     if (!base) return fail(c, ECMD_EDEVICE, "no scratch address on device %d", c->device);
+    at[PB_LISTS] = used;
     void* b[PB_COUNT];
-    size_t used = 0;
-    for (int k = 0; k < PB_LISTS; ++k) {
-        b[k] = (char*)base + used;
-        used += (bytes[k] + 255) / 256 * 256;  // every buffer on a 256-byte boundary
-    }
+    for (int k = 0; k < PB_COUNT; ++k) b[k] = (char*)base + at[k];
     // the node groups' lists take what is left: shorter ones, or no groups
-    b[PB_LISTS] = (char*)base + used;
     while (sh.mcap >= 64 && used + list_bytes(sh.nodes_nb, sh.nt, sh.mcap) > kScratchBytes) sh.mcap /= 2;
     if (used > kScratchBytes)
         return fail(c, ECMD_ENOMEM,

@@ -143,3 +143,23 @@ def test_hot_pixels_without_the_sort(so, spare, launches):
 
 def test_lists_make_room(so):
     host_runtime.run(so, __name__, "given_back")
+
+
+def coarse_plan(rt):
+    """A plan of one large window: finer tiles where there is room, else the
+    ones that take a third of the records."""
+    from paper_2209_13168_amd import ecmd
+
+    ctx = ecmd.Context(0, stream=0)
+    sen, n = ecmd.sensor(640, 480, (320, 240)), 1_000_000
+    p = ctx.batch_plan(sen, 0.0, 1.5, EPS, 1, n)
+    assert p.limits["max_records"] == 6 * n
+    p.close()
+    rt.rt_limit(rt.rt_used() + 60 * MIB)
+    p = ctx.batch_plan(sen, 0.0, 1.5, EPS, 1, n)
+    assert p.limits["max_records"] == 2 * n and rt.rt_last() == 0
+    p.close()
+
+
+def test_a_plan_takes_the_tiles_that_fit(so):
+    host_runtime.run(so, __name__, "coarse_plan")
