@@ -3,8 +3,8 @@
 // One call = prep (tile binning of every window's events, a1) -> init of the
 // per-window branch and bound (Alg. 1) -> repeated [evaluate hypotheses
 // (a2, a3), frontier step (a4)] until every window is certified.  All
-// search state stays in device memory; the host only launches and polls a
-// single counter of windows still running.
+// search state stays in device memory; the host only launches and reads one
+// report per two rounds.
 #include <limits.h>
 #include <math.h>
 #include <stdarg.h>
@@ -549,7 +549,7 @@ static bool choose_tiling(size_t max_lds, const ecmd_tuning& tu, int W, int H, f
 }
 
 // Persistent workgroup count of the evaluation kernel for `lds` bytes of
-// LDS: as many as fit at once, at most 4 per CU.  The kernel's dynamic LDS
+// LDS: as many as fit at once, at most 8 per CU.  The kernel's dynamic LDS
 // limit is raised to the device maximum once per context, so that every
 // context's launches fit whatever another context set.
 static hipError_t eval_setup(ecmd_ctx* c, int ring_px, int nt, int* nb) {
@@ -617,8 +617,8 @@ static hipError_t fit_lists(DevBuf& lists, int nb, int nt, int& cap) {
 // 346x260 window (4 segments) of 100k events 871 and 944, of 200k 1126 and
 // 1214, of 1M 3350 and 2792; two of 200k 1606 and 1600, four of 100k 1588 and
 // 1412; one 640x480 window (12) of 50k 953 and 1008, of 300k 1589 and 1500,
-// two of 50k 1257 and 1196.  The lists keep a third of their room for windows
-// whose events move more than the mean.
+// two of 50k 1257 and 1196.  Groups are cut to fill three eighths of the lists at
+// the mean motion; the rest is for windows whose events move more.
 constexpr int kMinSegments = 24;
 constexpr long long kManyEvents = 300000;
 

@@ -45,9 +45,12 @@ __device__ __forceinline__ float bits_to_f(uint16_t b) { return __uint_as_float(
 // forward pass is the chain of fused multiply-adds over its weights' order,
 // whichever kernel computes it (a tap on the zero border adds nothing).
 //
-// Bound by the matrix cores' fp32 rate: an image's forward pass is 2304 MFMA
-// of 32 cycles over a CU's four SIMDs (8 us at 2.4 GHz), its backward pass
-// 4864 (16 us).
+// The floor is the matrix cores' fp32 rate: an image's forward pass is 2304
+// MFMA of 32 cycles over a CU's four SIMDs (8 us at 2.4 GHz), its backward
+// pass 4864 (16 us).  Measured 33 us forward (64 images) and 81 us forward and
+// backward (256): bound by the products' operands, which come through LDS, by
+// the parts in which the weights are staged (a barrier before and after each,
+// nothing in flight across it) and by the layers following one another.
 constexpr int kImgThreads = 1024;
 constexpr int kImgWaves = kImgThreads / 64;
 constexpr int kI = 65, kP1 = 33, kP2 = 17, kP3 = 9;       // row lengths of the planes

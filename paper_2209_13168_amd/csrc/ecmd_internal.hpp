@@ -195,8 +195,6 @@ static_assert(node_slot(kXcd - 1, 0, kMaxQcap) == 12884901887ll && node_slot(0, 
 
 hipError_t launch_winparam(hipStream_t s, const Geometry& g, const float* tau, const long long* offsets,
                            int B, float d_lo, float d_hi, WinParam* wp);
-// Counters of the prep (per window and tile: owned events by walk class,
-// guests by bin and walk class).
 // Start of a synchronous call: n_head words of staged input (pinned host
 // memory) to the device, and what the call's kernels count in cleared: nctr
 // counters, B flags, kQueues queues and n_active (the last two may be NULL).
@@ -214,6 +212,8 @@ struct Report {
 // the windows' states too once every window has finished (or if `all`).
 hipError_t launch_report(hipStream_t s, int B, const long long* records, const int* n_active, const int* err_flag,
                          const WinState* st, int all, Report* rep, WinState* hs);
+// Counters of the prep (per window and tile: owned events by walk class,
+// guests by bin and walk class).
 size_t prep_counters(int B, int T);
 // Events per prep workgroup where a call has up to max_events.
 int prep_chunk(long long max_events);

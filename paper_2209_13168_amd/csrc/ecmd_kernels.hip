@@ -2504,7 +2504,7 @@ constexpr int kCheckThreads = 1024;
 // One workgroup: wstat[w] = 0 for a valid window, else ECMD_EINVAL (every
 // window when the valid ones hold more than max_events events); blk = the
 // exclusive prefix of the prep blocks (`chunk` events each) of the valid
-// windows, B + 1 entries; werr, both queue sets and n_active cleared.
+// windows, B + 1 entries; werr, all kQueues queues and n_active cleared.
 // Thread k checks the windows [k * per, (k + 1) * per).
 __global__ __launch_bounds__(kCheckThreads) void k_plan_check(
     const long long* __restrict__ off, const float* __restrict__ tau, int B, float d_hi, int W, int H,
