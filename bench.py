@@ -204,7 +204,10 @@ def roofline(ctx, prof, steps: int, sec: float, last, tkey: dict, peaks=None) ->
         "traffic": traffic,
         "traffic_unit": "HBM bytes per launch",
         "algorithmic_bytes": round(alg_bytes),
-        "kernel": "k_eval",
+        # (the counted operations are those of one evaluation per hypothesis;
+        # k_nodes evaluates up to 24 images in one pass over the events, so the
+        # fraction is the search's rate on that scale, not the kernels' issue rate)
+        "kernel": "k_eval and k_nodes",
         "avg_launch_us": round(avg_launch_s * 1e6, 2),
         "launches_per_step": round(launches / steps, 2),
         "eval_share_of_step": round(eval_s / steps / sec, 3),

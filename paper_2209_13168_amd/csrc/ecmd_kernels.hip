@@ -1109,7 +1109,7 @@ __global__ __launch_bounds__(NT) void k_eval(
 // batch, without and with node groups: 32 windows of 346x260 7.29 and 5.11 ms,
 // 64 of 640x480 40.3 and 23.7 ms, 64 of 1280x720 (0.1M-5M events) 207 and
 // 170 ms; a late step of the 640x480 batch 4.3 and 0.8 ms (with the binning,
-// tiling and host work of today 4.40, 21.7 and 162 ms).
+// tiling and host work of today 4.39, 21.7 and 165 ms).
 constexpr int kNodePhases = 3 * kMaxNodes;
 static_assert(kNodePhases <= 64, "one lane per phase");
 
