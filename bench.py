@@ -71,10 +71,10 @@ EVENT_RECORD_BYTES = 16
 # --calibrate-copy`).  The figures hold only for the kernel sources and the
 # workload they were taken on; for anything else `traffic` is null.
 TRAFFIC = {
-    "sources_sha256": "501d5d03a02dfc6f3f95db98a43bf1b0f189c2ff8e016936a958391d42337323",
+    "sources_sha256": "68a2628df42249582a95ed65acaf97f1822e26e8f85d6ce7d398226cbd922817",
     "workload": {"config": "c5", "windows": 256, "frontier_batch": 96},
-    "fetch_kib": 10605487.5,
-    "write_kib": 523470.4,
+    "fetch_kib": 10610360.0,
+    "write_kib": 523540.9,
     "fetch_bytes_per_kib": 1073741824 / 524305.0,
     "write_bytes_per_kib": 1073741824 / 1048576.0,
 }
